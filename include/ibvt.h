@@ -168,7 +168,10 @@ typedef struct {
   int64_t device_bytes;      /* device memory held by the coupling */
   int64_t assemblies;        /* assemblies done on this handle */
   int64_t subtets;           /* sub-tetrahedra integrated by the last
-                                assembly (11 quadrature points each) */
+                                assembly (11 quadrature points each); 0,
+                                like dist_evals and cut_points, where it
+                                integrated the pieces over their boundary
+                                (FP64, tets of at most 6 cells an axis) */
   int64_t piece_store;       /* 1 if every kept piece's moments are stored
                                 for the reverse mode */
   int64_t dist_evals;        /* plane distances evaluated by the last

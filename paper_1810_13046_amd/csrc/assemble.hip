@@ -10,6 +10,10 @@
 //                  order (key: the cell planes the tet straddles, in
 //                  classes by cut count: vertex slots 10, 12, 16), counted
 //                  and placed per (tet, key) group from the cell ranges.
+//  k_pieces        (FP64, tets of at most kOctantCells cells per axis) the
+//                  pieces' moments and the 32 values ∫ λ_i N_j per pair from
+//                  boundary integrals, without clipped polyhedra; the
+//                  order, k_clip and k_integrate serve the others.
 //  k_clip<T,MAXV>  one lane per pair: clip the tet by the straddled cell
 //                  planes in double (vertex graph in LDS), fan the piece
 //                  into sub-tetrahedra and store them as records.
@@ -28,8 +32,8 @@
 //                  matrix |T|(1+δ_il)/20 (Section 2.1), per vertex in
 //                  incident-tet order.
 
-#include "geometry.hpp"
 #include "internal.hpp"
+#include "moments.hpp"
 
 #include <climits>
 #include <cstdlib>
@@ -152,7 +156,7 @@ __global__ void k_tet_prep(int64_t n_t, const double* __restrict__ X,
                            double* __restrict__ tetgrad, unsigned* flags,
                            unsigned long long* counters) {
   const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  bool zero = false;
+  bool zero = false, wide = false;
   if (t < n_t) {
     double P[4][3];
     bool finite = true;
@@ -217,10 +221,13 @@ __global__ void k_tet_prep(int64_t n_t, const double* __restrict__ X,
       rng[d * n_t + t] = r;
       cnt[d * n_t + t] = int64_t(r.n[0]) * r.n[1] * r.n[2];
       if (int64_t(r.n[0]) * r.n[1] * r.n[2] > kMaxTetCells) atomicOr(flags, kFlagTetSpan);
+      wide |= ok && max(r.n[0], max(r.n[1], r.n[2])) > kOctantCells;
     }
   }
   const uint64_t zm = ballot64(zero);
+  const uint64_t wm = ballot64(wide);
   if (lane_id() == 0 && zm) atomicAdd(&counters[kCntZeroTets], (unsigned long long)popc64(zm));
+  if (lane_id() == 0 && wm) atomicAdd(&counters[kCntWide], (unsigned long long)popc64(wm));
 }
 
 // ---------------------------------------------------------------------------
@@ -587,6 +594,341 @@ __global__ __launch_bounds__(kWave) void k_integrate(
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) store_row<8>(pval + i * plane + (pj - p_begin) * 8, b[i]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// pieces by boundary integrals: candidate test, moments and values in one
+// kernel
+// ---------------------------------------------------------------------------
+
+// The owner ((component, tet) item) of every pair.
+__global__ __launch_bounds__(256) void k_owner(int64_t n_items,
+                                               const int64_t* __restrict__ pair_off,
+                                               int32_t* __restrict__ owner) {
+  const int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (w >= n_items) return;
+  const int64_t e = pair_off[w + 1];
+  for (int64_t p = pair_off[w]; p < e; ++p) owner[p] = int32_t(w);
+}
+
+// Offset of (component d, axis e) by selects on d (a variable index into the
+// kernel argument would copy it to scratch).
+__device__ __forceinline__ int lattice_offset(const LatDesc& ld, int d, int e) {
+  return d == 0 ? ld.off[e] : (d == 1 ? ld.off[3 + e] : ld.off[6 + e]);
+}
+
+// A candidate pair's item and its cell's place k[] in the item's range (no
+// axis longer than kOctantCells: quotients below 216 by float reciprocals).
+struct PairPlace {
+  int d;
+  int64_t t;
+  CellRange r;
+  int k[3];
+};
+
+__device__ __forceinline__ void pair_item(int64_t p, int64_t n_t, const int32_t* owner,
+                                          const CellRange* rng, PairPlace& o) {
+  const int64_t tc = owner[p];
+  o.d = (tc >= n_t) + (tc >= 2 * n_t);
+  o.t = tc - int64_t(o.d) * n_t;
+  o.r = rng[tc];
+}
+
+__device__ __forceinline__ int small_div(int q, int n) {
+  return int((float(q) + 0.5f) * __builtin_amdgcn_rcpf(float(n)));
+}
+
+// Octant terms of a candidate pair, 0 if the cell surely misses the tet: a
+// barycentric coordinate is negative on all of the cell's part of the tet's
+// box.  The coordinates are affine with gradients good to about κ² ulps, κ =
+// box volume / |det|, so the test is left out for flat tets (κ > 256) and
+// asks for a margin of 1e-8 (far above κ² ulps; what it lets through is
+// integrated and dropped by its volume).
+__device__ __forceinline__ int candidate_terms(const PairPlace& o, const double* tetrec,
+                                               const double* tetgrad, const double* tetvol,
+                                               const double* lat, const LatDesc& ld, int& cuts) {
+  double rec[kTetRec], g[12];
+  load_row<kTetRec>(tetrec + o.t * kTetRec, rec);
+  load_row<12>(tetgrad + o.t * 12, g);
+  int terms = 1;
+  cuts = 0;
+  double top[4] = {1.0, 0.0, 0.0, 0.0}, box = 1.0;
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    const double* L = lat + lattice_offset(ld, o.d, e) + o.r.lo[e] + o.k[e];
+    const double mn = fmin(fmin(rec[e], rec[3 + e]), fmin(rec[6 + e], rec[9 + e]));
+    const double mx = fmax(fmax(rec[e], rec[3 + e]), fmax(rec[6 + e], rec[9 + e]));
+    const double a = fmax(mn, L[0]) - rec[e];
+    const double b = fmin(mx, L[1]) - rec[e];
+    box *= mx - mn;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) top[i] += fmax(g[3 * i + e] * a, g[3 * i + e] * b);
+    terms <<= axis_two(o.k[e], o.r.n[e]) ? 1 : 0;
+    cuts += (o.k[e] > 0) + (o.k[e] < o.r.n[e] - 1);
+  }
+  const double least = fmin(fmin(top[0], top[1]), fmin(top[2], top[3]));
+  return least < -1e-8 && box <= 256.0 * 6.0 * tetvol[o.t] ? 0 : terms;
+}
+
+// A queued octant term: its pair relative to the block's first (11 bits),
+// the cell's place (3 bits an axis), the term's index among the pair's and
+// their number less one.
+constexpr int kPieceRange = 2048;  // most candidate pairs of one block
+__device__ __forceinline__ uint32_t term_pack(int rel, const int k[3], int j, int n) {
+  return uint32_t(rel) | uint32_t(k[0] | (k[1] << 3) | (k[2] << 6)) << 11 | uint32_t(j) << 20 |
+         uint32_t(n - 1) << 23;
+}
+
+__device__ __forceinline__ int64_t queued_pair(uint32_t e, int64_t b0, int64_t n_t,
+                                               const int32_t* owner, const CellRange* rng,
+                                               PairPlace& o) {
+  const int64_t p = b0 + int64_t(e & 0x7ffu);
+  pair_item(p, n_t, owner, rng, o);
+  o.k[0] = int((e >> 11) & 7u);
+  o.k[1] = int((e >> 14) & 7u);
+  o.k[2] = int((e >> 17) & 7u);
+  return p;
+}
+
+// Writes the 16 values of every lane's row of the stage to memory, 128
+// bytes of eight rows at a time (one lane, one row: each 16-byte store is
+// a request of its own to the L2).  rel[s]: where row 8 s + lane / 8 goes
+// (times `stride` from `out`, this lane's place in it), or negative.  No
+// load may be pending here: waiting for one waits for the stores before it.
+constexpr int kStageRow = 17;
+__device__ __forceinline__ void store_stage(const double* stage, const int rel[8], double* out,
+                                            int stride) {
+  const int lane = threadIdx.x;
+  const double* src = stage + (lane >> 3) * kStageRow + 2 * (lane & 7);
+  wave_lds_sync();
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const double v[2] = {src[8 * s * kStageRow], src[8 * s * kStageRow + 1]};
+    if (rel[s] >= 0) store_row_nt<2>(out + int64_t(rel[s]) * stride, v);
+  }
+  wave_lds_sync();
+}
+
+// (II)-(III) of the FP64 couplings whose tets span at most kOctantCells
+// cells per axis.  One wave per `range` candidate pairs: 64 candidates at a
+// time are tested against the tet's faces, the octant terms of those left
+// are queued, and whole batches of 64 terms are integrated, one lane each
+// (moments.hpp), so the lanes stay filled (94 % of them active) although a
+// fifth of the candidates is empty.  A pair's terms are consecutive; its
+// first lane adds them in order and turns the 32 moments into the values
+// ∫ λ_i N_j, so a pair's results depend on the pair alone.
+//
+// Measured on 84.4M pairs (4.5M tets on 512 x 256 x 256): 17.3 ms, where the
+// clip (19.6), the integration of its sub-tetrahedra (20.9) and the pair
+// order between them took 41 ms.  Of the 17.3, candidates, set-up and the
+// values take 5.7, the faces 6.2 (FP64 issue: 730 VALU instructions a face)
+// and the 33 GB written 5.4; at 205 registers two waves a SIMD do not hide
+// all of the stores.  Three waves (168 registers) spill and take 18.3;
+// stores of 16 bytes a lane to lines of their own take 0.4 ms more.
+__global__ __launch_bounds__(kWave, 2) void k_pieces(
+    int64_t plane_pairs, int64_t p_begin, int64_t p_end, int range, int64_t n_t,
+    const int32_t* __restrict__ owner, const int64_t* __restrict__ pair_off,
+    const CellRange* __restrict__ rng, const double* __restrict__ tetrec,
+    const double* __restrict__ tetgrad, const double* __restrict__ tetvol,
+    const double* __restrict__ lat, LatDesc ld, double drop_rel, uint8_t* __restrict__ keep,
+    double* __restrict__ pval, double* __restrict__ pmom, int dual, unsigned long long* counters) {
+  constexpr int kQueue = 9 * kWave;
+  // rows 0..11: the tet in octant coordinates; 12..17: the octant's signs
+  // and shifts (here while the faces need the registers); then the stage
+  __shared__ double lds[18 * kWave];
+  __shared__ uint32_t queue[kQueue];
+  static_assert(kWave * kStageRow <= 18 * kWave, "stage");
+  const int lane = threadIdx.x;
+  const int64_t b0 = p_begin + int64_t(blockIdx.x) * range;
+  const int64_t b1 = min<int64_t>(b0 + range, p_end);
+  int filled = 0;
+  uint32_t nk = 0, nd = 0, np = 0;
+  int64_t next = b0;
+  while (next < b1 || filled > 0) {
+    if (filled < kWave && next < b1) {
+      const int64_t p = next + lane;
+      next += kWave;
+      int terms = 0;
+      PairPlace o;
+      if (p < b1) {
+        pair_item(p, n_t, owner, rng, o);
+        const int q = int(p - pair_off[int64_t(o.d) * n_t + o.t]);
+        const int qy = small_div(q, o.r.n[0]), qz = small_div(qy, o.r.n[1]);
+        o.k[0] = q - qy * o.r.n[0];
+        o.k[1] = qy - qz * o.r.n[1];
+        o.k[2] = qz;
+        int cuts;
+        terms = candidate_terms(o, tetrec, tetgrad, tetvol, lat, ld, cuts);
+        if (terms == 0) keep[p] = 0;
+        else np += unsigned(cuts);
+      }
+      int incl = terms;
+      for (int o2 = 1; o2 < kWave; o2 <<= 1) {
+        const int y = __shfl_up(incl, o2, kWave);
+        if (lane >= o2) incl += y;
+      }
+      for (int j = 0; j < terms; ++j)
+        queue[filled + incl - terms + j] = term_pack(int(p - b0), o.k, j, terms);
+      filled += __shfl(incl, kWave - 1, kWave);
+      wave_lds_sync();
+      continue;
+    }
+    // up to 64 terms, whole pairs only
+    int take = min(filled, kWave);
+    if (filled > kWave) {
+      const uint32_t e = queue[kWave - 1];
+      const int j = int((e >> 20) & 7u), n = int(e >> 23) + 1;
+      if (j + 1 < n) take = kWave - 1 - j;
+    }
+    // lanes past the batch repeat its first term: every lane runs the same
+    // code on a term of its own, and what it may write is masked
+    const bool active = lane < take;
+    const uint32_t e = queue[active ? lane : 0];
+    const int term = int((e >> 20) & 7u), terms = int(e >> 23) + 1;
+    double M[kMom];
+#pragma unroll
+    for (int k = 0; k < kMom; ++k) M[k] = 0.0;
+    double sign = 6.0;  // of the term, times 6
+    {
+      PairPlace o;
+      queued_pair(e, b0, n_t, owner, rng, o);
+      double rec[kTetRec];
+      load_row<kTetRec>(tetrec + o.t * kTetRec, rec);
+      int bit = 0;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const double* L = lat + lattice_offset(ld, o.d, a) + o.r.lo[a] + o.k[a];
+        const double lo = L[0], hi = L[1];
+        const double mn = fmin(fmin(rec[a], rec[3 + a]), fmin(rec[6 + a], rec[9 + a]));
+        const bool two = axis_two(o.k[a], o.r.n[a]);
+        const AxisOctant x =
+            axis_octant(o.k[a], o.r.n[a], lo, hi, mn, two && ((term >> bit) & 1));
+        bit += two ? 1 : 0;
+        const double sih = x.sg * recip(hi - lo);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) lds[(3 * v + a) * kWave + lane] = sih * (rec[3 * v + a] - x.c);
+        lds[(12 + a) * kWave + lane] = x.sg;
+        lds[(15 + a) * kWave + lane] = sih * (x.c - lo) - 0.5 * x.sg;
+        sign = x.minus ? -sign : sign;
+      }
+    }
+    wave_lds_sync();
+#pragma unroll 1
+    for (int f = 0; f < 4; ++f) {
+      // faces (1,2,3), (0,3,2), (0,1,3), (0,2,1)
+      const int ia = f == 0 ? 1 : 0, ib = f == 1 ? 3 : (f == 2 ? 1 : 2),
+                ic = f == 1 ? 2 : (f == 3 ? 1 : 3);
+      add_face([&](int v, int a) { return lds[(3 * v + a) * kWave + lane]; }, ia, ib, ic, M);
+    }
+    wave_lds_sync();
+    {
+      const double sg[3] = {lds[12 * kWave + lane], lds[13 * kWave + lane], lds[14 * kWave + lane]};
+      const double sh[3] = {lds[15 * kWave + lane], lds[16 * kWave + lane], lds[17 * kWave + lane]};
+      // M[0] > 0 for a positively oriented tet in octant coordinates; the
+      // stored moments are −6 ∫ s^α
+      centre_moments(M, sg, sh, M[0] > 0.0 ? -sign : sign);
+    }
+    // a pair's terms are consecutive: its first lane adds the others' in order
+    const int most = wave_max(active ? terms : 1);
+#pragma unroll 1
+    for (int j = 1; j < most; ++j) {
+      const double on = term == 0 && j < terms ? 1.0 : 0.0;
+#pragma unroll
+      for (int k = 0; k < kMom; ++k) M[k] = fma(on, __shfl_down(M[k], j, kWave), M[k]);
+    }
+    // the pair again (read again: kept through the faces it would cost
+    // registers the third wave needs)
+    uint32_t e2 = e;
+    asm volatile("" : "+v"(e2));
+    PairPlace o;
+    const int64_t p = queued_pair(e2, b0, n_t, owner, rng, o);
+    double lo[3], h[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double* L = lat + lattice_offset(ld, o.d, a) + o.r.lo[a] + o.k[a];
+      lo[a] = L[0];
+      h[a] = L[1] - L[0];
+    }
+    const double cv = h[0] * h[1] * h[2] * (-1.0 / 6.0);
+    // λ_i in centred coordinates (dual: ψ_i = 5 λ_i − Σ_k λ_k = 5 λ_i − 1),
+    // times the cell's volume
+    double lc[4], lg[4][3];
+    {
+      double g[12], v0[4];
+      load_row<12>(tetgrad + o.t * 12, g);
+      load_row<4>(tetrec + o.t * kTetRec, v0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        lc[i] = i == 0 ? 1.0 : 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          lc[i] += g[3 * i + a] * ((lo[a] - v0[a]) + 0.5 * h[a]);
+          lg[i][a] = g[3 * i + a] * h[a] * (dual ? 5.0 * cv : cv);
+        }
+        lc[i] = (dual ? 5.0 * lc[i] - 1.0 : lc[i]) * cv;
+      }
+    }
+    const double vol = M[0] * cv;
+    const bool lead = active && term == 0;
+    const bool kp = lead && vol > drop_rel * tetvol[o.t];
+    if (lead) keep[p] = kp ? 1 : 0;
+    nk += kp ? 1 : 0;
+    nd += lead && !kp && vol > 0.0 ? 1 : 0;
+    const uint64_t rows = ballot64(kp);
+    double* stage = lds;
+    int rel[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int row = 8 * s + (lane >> 3);
+      rel[s] = (rows >> row) & 1ull ? int(queue[row] & 0x7ffu) : -1;
+    }
+    // (opaque, so that the addresses below are made here and not kept, and
+    // spilled, through the loop)
+    int q = lane & 7;
+    asm volatile("" : "+v"(q));
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) stage[lane * kStageRow + k] = M[16 * half + k];
+      store_stage(stage, rel, pmom + b0 * kMomPad + 16 * half + 2 * q, kMomPad);
+    }
+#pragma unroll
+    for (int k = 0; k < kMom; ++k) finish(M[k]);
+    double F[4][8];
+    mom_hats<double>(M, F);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int v = 2 * half + i;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          stage[lane * kStageRow + 8 * i + j] =
+              lc[v] * F[0][j] + lg[v][0] * F[1][j] + lg[v][1] * F[2][j] + lg[v][2] * F[3][j];
+      }
+      store_stage(stage, rel,
+                  pval + ((2 * half + (q >> 2)) * plane_pairs + (b0 - p_begin)) * 8 + 2 * (q & 3), 8);
+#pragma unroll
+      for (int f = 0; f < 4; ++f)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) finish(F[f][j]);
+    }
+    // the rest of the queue moves to its front
+    const int rest = filled - take;
+    for (int k = 0; k < rest; k += kWave) {
+      const uint32_t x = k + lane < rest ? queue[take + k + lane] : 0;
+      wave_lds_sync();
+      if (k + lane < rest) queue[k + lane] = x;
+      wave_lds_sync();
+    }
+    filled = rest;
+  }
+  const uint32_t sk = wave_sum(nk), sd = wave_sum(nd), sp = wave_sum(np);
+  if (lane == 0) {
+    if (sk) atomicAdd(&counters[kCntPieces], (unsigned long long)sk);
+    if (sd) atomicAdd(&counters[kCntDropped], (unsigned long long)sd);
+    if (sp) atomicAdd(&counters[kCntPlanes], (unsigned long long)sp);
   }
 }
 
@@ -1164,15 +1506,16 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
       return st;
   }
   // read-back 1: the chunks' first pairs (the last entry is the pair count),
-  // the row scratch and spill sizes, and status flags
-  int64_t pat[kMaxChunks + 3];
+  // the row scratch and spill sizes, the wide tets, and status flags
+  int64_t pat[kMaxChunks + 4];
   {
-    const int64_t* src[kMaxChunks + 3];
+    const int64_t* src[kMaxChunks + 4];
     for (int k = 0; k <= nchunk; ++k) src[k] = c->pair_off.as<int64_t>() + tc_at[k];
     int nsrc = nchunk + 1;
     if (!c->matrix_free) {
       src[nsrc++] = c->rowtmpoff.as<int64_t>() + 3 * n_v;
       src[nsrc++] = c->rowspilloff.as<int64_t>() + 3 * n_v;
+      src[nsrc++] = reinterpret_cast<const int64_t*>(counters + kCntWide);
     }
     if ((st = read_counts(c, src, nsrc, pat, s))) return st;
   }
@@ -1183,6 +1526,13 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
   c->n_pairs = n_pairs;
   if (c->matrix_free) return finish_matfree<T>(c, s);
   const int64_t tmp_total = pat[nchunk + 1], spill_total = pat[nchunk + 2];
+  // Boundary integrals (k_pieces) or clipping: FP64 couplings whose tets are
+  // all small enough for the octants' accuracy (kOctantCells) take the
+  // former, 17.3 ms against 41 on the three-body mesh and 0.37 against 1.3 on
+  // 47,916 tets.  Mixed couplings keep the clip: their moments are float
+  // sums over its sub-tetrahedra, and their results are to stay what they
+  // are to the last bit (the octants' would differ by float roundings).
+  const bool octants = sizeof(T) == sizeof(double) && pat[nchunk + 3] == 0;
   int64_t chunk_max = 0;
   for (int k = 0; k < nchunk; ++k) chunk_max = std::max(chunk_max, pat[k + 1] - pat[k]);
   if ((st = ensure(c, c->owner, size_t(n_pairs + 1) * sizeof(int32_t)))) return st;
@@ -1196,21 +1546,79 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
   double* spill_acc = c->rowspill.as<double>();
   uint8_t* spill_flg = c->rowspill.as<uint8_t>() + spill_acc_bytes;
   if ((st = ensure(c, c->pmom, size_t(n_pairs + 1) * kMomPad * sizeof(T)))) return st;
-  if ((st = ensure(c, c->pinfo, size_t(n_pairs + 1) * sizeof(uint64_t)))) return st;
-  // the clip order of one chunk at a time, as pair descriptors
-  if ((st = ensure(c, c->order, size_t(chunk_max + 1) * sizeof(PairDesc)))) return st;
-  // per chunk: the pair descriptors in clip order (k_order_count, scan,
-  // k_order_scatter); the scanned key counts give the clip launches their
-  // class stretches on the device
-  int64_t items_max = 1;
-  for (int k = 0; k < nchunk; ++k) items_max = std::max(items_max, tc_at[k + 1] - tc_at[k]);
-  const int64_t ob_max = ceil_div(items_max, kOrderItems);
-  const size_t hb = (size_t(256 * ob_max) * sizeof(int32_t) + 255) & ~size_t(255);
-  if ((st = ensure(c, c->pscan, hb + size_t(256 * ob_max + 1) * sizeof(int64_t)))) return st;
-  int32_t* ohist = c->pscan.as<int32_t>();
-  int64_t* ofirst = reinterpret_cast<int64_t*>(c->pscan.as<char>() + hb);
   if ((st = side_stream(c))) return st;
   bool masses_done = false;
+  // (IV) the rows of B^d that take pairs of chunk ch: the rows of the
+  // components its items belong to (on this stream: beside the next chunk's
+  // pieces they slow them by more than they take)
+  auto gather_rows = [&](int ch) -> int {
+    ProfScope ps("rows_gather", s);
+    const int64_t d_lo = tc_at[ch] / n_t, d_hi = (tc_at[ch + 1] - 1) / n_t;
+    const int64_t w_begin = d_lo * n_v, n_rows = (d_hi - d_lo + 1) * n_v;
+    k_rows<T><<<blocks_for(ceil_div(n_rows, kRowsPerWave) * kWave, 256), 256, 0, s>>>(
+        n_v, n_t, ch, tc_at[ch], tc_at[ch + 1], pat[ch], chunk_max, w_begin, n_rows,
+        c->vt_ptr.as<int64_t>(), c->vt_tet.as<int32_t>(), c->tets.as<int32_t>(),
+        c->rng.as<CellRange>(), c->pair_off.as<int64_t>(), c->keep.as<uint8_t>(),
+        c->pval.as<T>(), c->ld, c->rowbox.as<RowBox>(), c->rowtmpoff.as<int64_t>(),
+        c->rowtmpcol.as<int32_t>(), c->rowtmpval.as<T>(), c->rownnz.as<int64_t>(),
+        c->rowspilloff.as<int64_t>(), spill_acc, spill_flg);
+    return hip_check(hipGetLastError(), "rows launch");
+  };
+  // the solid masses need only the tet volumes: on the second stream beside
+  // the first chunk's pieces, joined after them
+  auto fork_masses = [&]() -> int {
+    if (masses_done) return IBVT_OK;
+    masses_done = true;
+    return solid_masses(c, c->side);
+  };
+  if constexpr (sizeof(T) == sizeof(double)) if (octants && n_pairs > 0) {
+    // (II)-(III) every piece from its boundary integrals
+    k_owner<<<blocks_for(n_tc, 256), 256, 0, s>>>(n_tc, c->pair_off.as<int64_t>(),
+                                                  c->owner.as<int32_t>());
+    if ((st = hip_check(hipGetLastError(), "owner launch"))) return st;
+    for (int ch = 0; ch < nchunk; ++ch) {
+      const int64_t p0 = pat[ch], nc = pat[ch + 1] - pat[ch];
+      if (nc == 0) continue;
+      const bool fork = !masses_done;
+      if (fork) {
+        if ((st = hip_check(hipEventRecord(c->ev_fork, s), "event")) ||
+            (st = hip_check(hipStreamWaitEvent(c->side, c->ev_fork, 0), "stream wait")) ||
+            (st = fork_masses()) ||
+            (st = hip_check(hipEventRecord(c->ev_join, c->side), "event")))
+          return st;
+      }
+      {
+        ProfScope ps("pieces", s);
+        // candidates per block: about eight rounds of the resident waves, at
+        // most kPieceRange (a block's last, partly filled batch then weighs
+        // little), at least one batch
+        const int64_t range = std::min<int64_t>(
+            kPieceRange, std::max<int64_t>(1, nc / (16384 * kWave)) * kWave);
+        k_pieces<<<dim3(unsigned(ceil_div(nc, range))), kWave, 0, s>>>(
+            chunk_max, p0, p0 + nc, int(range), n_t, c->owner.as<int32_t>(),
+            c->pair_off.as<int64_t>(), c->rng.as<CellRange>(), c->tetrec.as<double>(),
+            c->tetgrad.as<double>(), c->tetvol.as<double>(), c->lat.as<double>(), c->ld, 1e-14,
+            c->keep.as<uint8_t>(), c->pval.as<T>(), c->pmom.as<T>(), c->dual ? 1 : 0, counters);
+      }
+      if ((st = hip_check(hipGetLastError(), "pieces launch"))) return st;
+      if (fork && (st = hip_check(hipStreamWaitEvent(s, c->ev_join, 0), "stream wait"))) return st;
+      if ((st = gather_rows(ch))) return st;
+    }
+  }
+  if (!octants) {
+    if ((st = ensure(c, c->pinfo, size_t(n_pairs + 1) * sizeof(uint64_t)))) return st;
+    // the clip order of one chunk at a time, as pair descriptors
+    if ((st = ensure(c, c->order, size_t(chunk_max + 1) * sizeof(PairDesc)))) return st;
+    // per chunk: the pair descriptors in clip order (k_order_count, scan,
+    // k_order_scatter); the scanned key counts give the clip launches their
+    // class stretches on the device
+    int64_t items_max = 1;
+    for (int k = 0; k < nchunk; ++k) items_max = std::max(items_max, tc_at[k + 1] - tc_at[k]);
+    const int64_t ob_max = ceil_div(items_max, kOrderItems);
+    const size_t hb = (size_t(256 * ob_max) * sizeof(int32_t) + 255) & ~size_t(255);
+    if ((st = ensure(c, c->pscan, hb + size_t(256 * ob_max + 1) * sizeof(int64_t)))) return st;
+    int32_t* ohist = c->pscan.as<int32_t>();
+    int64_t* ofirst = reinterpret_cast<int64_t*>(c->pscan.as<char>() + hb);
   for (int attempt = 0; attempt < 2; ++attempt) {
     const int64_t want = std::max<int64_t>(int64_t(3.25 * double(chunk_max)) + 1024,
                                            c->pool_needed + c->pool_needed / 32 + 1024);
@@ -1266,13 +1674,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
         if ((st = hip_check(hipEventRecord(c->ev_fork, s), "event")) ||
             (st = hip_check(hipStreamWaitEvent(c->side, c->ev_fork, 0), "stream wait")))
           return st;
-        if (!masses_done) {
-          // the solid masses need only the tet volumes: on the second stream
-          // ahead of the first clip's classes 12 and 16, in the wave slots
-          // the LDS-bound clip leaves free (joined with the clip below)
-          if ((st = solid_masses(c, c->side))) return st;
-          masses_done = true;
-        }
+        if ((st = fork_masses())) return st;
         for (int k = 2; k >= 0; --k) {
           hipStream_t ks = k == 0 ? s : c->side;
           const int resident =
@@ -1312,22 +1714,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
             c->pval.as<T>(), c->pmom.as<T>(), c->dual ? 1 : 0);
       }
       if ((st = hip_check(hipGetLastError(), "integrate launch"))) return st;
-      {
-        // (IV) the rows of B^d that take pairs of this chunk: the rows of
-        // the components its items belong to (on this stream: beside the
-        // next chunk's clip they slow it by more than they take)
-        ProfScope ps("rows_gather", s);
-        const int64_t d_lo = tc_at[ch] / n_t, d_hi = (tc_at[ch + 1] - 1) / n_t;
-        const int64_t w_begin = d_lo * n_v, n_rows = (d_hi - d_lo + 1) * n_v;
-        k_rows<T><<<blocks_for(ceil_div(n_rows, kRowsPerWave) * kWave, 256), 256, 0, s>>>(
-            n_v, n_t, ch, tc_at[ch], tc_at[ch + 1], p0, chunk_max, w_begin, n_rows,
-            c->vt_ptr.as<int64_t>(), c->vt_tet.as<int32_t>(), c->tets.as<int32_t>(),
-            c->rng.as<CellRange>(), c->pair_off.as<int64_t>(), c->keep.as<uint8_t>(),
-            c->pval.as<T>(), c->ld, c->rowbox.as<RowBox>(), c->rowtmpoff.as<int64_t>(),
-            c->rowtmpcol.as<int32_t>(), c->rowtmpval.as<T>(), c->rownnz.as<int64_t>(),
-            c->rowspilloff.as<int64_t>(), spill_acc, spill_flg);
-      }
-      if ((st = hip_check(hipGetLastError(), "rows launch"))) return st;
+      if ((st = gather_rows(ch))) return st;
       if (next && (st = hip_check(hipStreamWaitEvent(s, c->ev_sorted, 0), "stream wait")))
         return st;
     }
@@ -1345,6 +1732,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     for (int k = 0; k < nchunk; ++k) c->pool_needed = std::max(c->pool_needed, rb2[k]);
     if (c->pool_needed <= c->pool_cap) break;
     if (attempt == 1) return set_error(IBVT_E_CAPACITY, "piece store could not be sized");
+  }
   }
   // (IV) global assembly: rows of B^d (gathered per chunk above)
   for (int d = 0; d < 3; ++d) {

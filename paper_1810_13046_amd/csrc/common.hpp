@@ -23,7 +23,7 @@ enum Counter : int {
   kCntDropped = 1,
   kCntZeroTets = 2,
   kCntSubtets = 3,
-  kCntUnused4 = 4,
+  kCntWide = 4,  // tets wider than the octant integration takes
   kCntUnused5 = 5,  // 5, 6, 7: unused
   kCntDist = 8,   // signed distances evaluated by the clip
   kCntCutPts = 9, // cut points made by the clip
@@ -110,6 +110,23 @@ __device__ __forceinline__ void store_row(T* __restrict__ dst, const T (&src)[N]
 #pragma unroll
     for (int e = 0; e < W; ++e) v[e] = src[k * W + e];
     d[k] = v;
+  }
+}
+
+// The same past the caches (data that is read again only after much more
+// has been written).
+template <int N, typename T>
+__device__ __forceinline__ void store_row_nt(T* __restrict__ dst, const T (&src)[N]) {
+  static_assert((N * sizeof(T)) % 16 == 0, "row of whole 16-byte words");
+  constexpr int W = 16 / sizeof(T);
+  typedef T V __attribute__((ext_vector_type(W)));
+  V* d = reinterpret_cast<V*>(dst);
+#pragma unroll
+  for (int k = 0; k < N / W; ++k) {
+    V v;
+#pragma unroll
+    for (int e = 0; e < W; ++e) v[e] = src[k * W + e];
+    __builtin_nontemporal_store(v, d + k);
   }
 }
 

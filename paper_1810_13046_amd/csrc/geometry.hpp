@@ -489,19 +489,25 @@ __host__ __device__ __forceinline__ void hat_butterfly(T G[8]) {
   }
 }
 
+// F[0][j] = ∫ N_j and F[1 + e][j] = ∫ s_e N_j from the piece's moments.
+template <typename T>
+__host__ __device__ __forceinline__ void mom_hats(const T* M, T F[4][8]) {
+#pragma unroll
+  for (int f = 0; f < 4; ++f) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      F[f][j] = M[mom_idx((j & 1) + (f == 1), ((j >> 1) & 1) + (f == 2), (j >> 2) + (f == 3))];
+    hat_butterfly<T>(F[f]);
+  }
+}
+
 // ∫ λ_i N_j (i = tet vertex, j = cell corner a + 2b + 4c) from the piece's
 // moments M (any memory), with λ_i(ξ) = LA[i] + LG[i]·ξ: calls
 // put(i, j, value) with the value unscaled like M.
 template <typename T, typename F>
 __host__ __device__ inline void mom_to_b(const T* M, const T LA[4], const T LG[4][3], F&& put) {
-  T Fv[4][8];  // Fv[0][j] = ∫ N_j, Fv[1 + e][j] = ∫ s_e N_j
-#pragma unroll
-  for (int f = 0; f < 4; ++f) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      Fv[f][j] = M[mom_idx((j & 1) + (f == 1), ((j >> 1) & 1) + (f == 2), (j >> 2) + (f == 3))];
-    hat_butterfly<T>(Fv[f]);
-  }
+  T Fv[4][8];
+  mom_hats<T>(M, Fv);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const T lac = LA[i] + T(0.5) * (LG[i][0] + LG[i][1] + LG[i][2]);
