@@ -3,7 +3,8 @@
     python -m paper_1810_13046_amd.build
 
 Every translation unit under csrc/ is compiled to an object in _build/ and
-linked into paper_1810_13046_amd/libibvt.so.  The library exports exactly the
+linked into paper_1810_13046_amd/libibvt.so; the clip tables' initialisers are
+written to _build/ first (csrc/gen_clip_table.py).  The library exports exactly the
 functions declared in include/ibvt.h: a linker version script written from
 the header's declarations keeps every other symbol local.
 """
@@ -19,7 +20,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libibvt.so")
-SOURCES = ["scan.hip", "sort.hip", "assemble.hip", "matfree.hip", "assemble2d.hip", "unstructured.hip", "transpose.hip",
+SOURCES = ["scan.hip", "sort.hip", "clip_table.hip", "assemble.hip", "matfree.hip", "assemble2d.hip", "unstructured.hip", "transpose.hip",
            "apply.hip", "grad.hip", "api.hip", "fsi.hip", "noalloc.hip"]
 ARCH = "gfx950"
 HEADER = os.path.join(os.path.dirname(HERE), "include", "ibvt.h")
@@ -39,7 +40,7 @@ def _hipcc():
 
 def _compile(src):
     obj = os.path.join(OUT, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [_hipcc(), *HIPCC_FLAGS, f"-I{OUT}", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
@@ -68,6 +69,11 @@ def _version_script() -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OUT, exist_ok=True)
+    gen = os.path.join(CSRC, "gen_clip_table.py")
+    r = subprocess.run([sys.executable, gen, os.path.join(OUT, "clip_table.inc")],
+                       capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{gen} failed:\n{r.stderr}")
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), 8)) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + f".tmp{os.getpid()}"

@@ -357,15 +357,27 @@ __global__ __launch_bounds__(kOrderItems) void k_order_scatter(
 // contiguous block of its chunk, so every pair's records are contiguous and
 // in fan order; the unused tail of a chunk is left empty.  The counters are
 // summed per wave and added once at the end.
+//
+// Bound: vector and scalar issue of the walks over the vertex graph, with
+// the LDS (28 bytes per slot and lane) holding two waves a SIMD.  With 10
+// slots (at most three planes) the clip is looked up (table_clip_box): no
+// graph is kept or walked, and ten waves fit a CU instead of eight.  On
+// 84.4M pairs all classes took 19.7 ms with the walks nested by vertex and
+// neighbour, 17.0 with one step or cut of every lane per round, and take
+// 11.0 with the look-up (float records, the other classes beside it).  A piece without a record, where rounding has
+// split a plane's inside or outside, is clipped again by the graph walk,
+// its neighbour words in the lane's own memory.
 template <typename T, int MAXV>
 __global__ __launch_bounds__(kWave) void k_clip(
-    const int64_t* __restrict__ cls_first, const int64_t* __restrict__ cls_end,
+    ClipTables tab, const int64_t* __restrict__ cls_first, const int64_t* __restrict__ cls_end,
     const PairDesc* __restrict__ desc_all, const double* __restrict__ tetrec,
     const double* __restrict__ lat, LatDesc ld, double drop_rel, T* __restrict__ pool,
     int64_t pool_cap, uint64_t* __restrict__ pinfo, unsigned long long* pool_used,
     unsigned* flags, unsigned long long* counters) {
+  constexpr bool kTable = MAXV == 10;
   __shared__ double sx[MAXV * kWave], sy[MAXV * kWave], sz[MAXV * kWave];
-  __shared__ uint32_t snb[MAXV * kWave];
+  __shared__ uint32_t snb[kTable ? 1 : MAXV * kWave];
+  uint32_t own[kTable ? MAXV : 1];
   const int lane = threadIdx.x;
   // this class's stretch of the pair order (read here, so the host needs
   // no class sizes); chunk ~ 1/8 of a wave's expected records (about 3 per
@@ -375,7 +387,10 @@ __global__ __launch_bounds__(kWave) void k_clip(
   const PairDesc* __restrict__ desc = desc_all + first;
   const int chunk = int(min<int64_t>(
       2048, max<int64_t>(1, (3 * n_list) / (8 * int64_t(gridDim.x)))));
-  const PolyView P{sx + lane, sy + lane, sz + lane, snb + lane, kWave, (1u << MAXV) - 1u};
+  const PolyView P = kTable
+                         ? PolyView{sx + lane, sy + lane, sz + lane, own, kWave, (1u << MAXV) - 1u, 1}
+                         : PolyView{sx + lane, sy + lane, sz + lane, snb + lane, kWave,
+                                    (1u << MAXV) - 1u};
   unsigned long long nk = 0, nd = 0, ns = 0;
   ClipCount cc;
   unsigned long long cbase = 0;  // next free record of the wave's chunk
@@ -387,9 +402,10 @@ __global__ __launch_bounds__(kWave) void k_clip(
     double lo[3], hi[3];
     int64_t p = 0;
     uint32_t live = 0;
-    uint64_t seen = 0;
+    EdgeMask<MAXV> seen = 0;
     int want = 0;
-    bool ok = true;
+    bool ok = true, walk = !kTable;
+    uint4 fan = make_uint4(0, 0, 0, 0);
     if (active) {
       int d, ci[3];
       int64_t t;
@@ -397,13 +413,28 @@ __global__ __launch_bounds__(kWave) void k_clip(
       double r[kTetRec];
       load_row<kTetRec>(tetrec + t * kTetRec, r);
       load_tet_box(G, r);
-      live = poly_init_tet(P, G.V, G.det < 0.0);
-      ok = poly_clip_box<MAXV>(P, live, lo, hi, G.mn, G.mx, &cc);
-      if (ok) {
-        want = poly_fan_prepare(P, live, seen);
-        if (want < 0) {
-          ok = false;
-          want = 0;
+      if (kTable) {
+        poly_put_tet(P, G.V, G.det < 0.0);
+        TablePiece q;
+        ClipCount c1 = cc;
+        table_clip_box(P, q, tab, lo, hi, G.mn, G.mx, &c1);
+        walk = q.odd;
+        if (!walk) {
+          cc = c1;
+          live = q.live;
+          if (live) fan = tab.fan[q.graph];
+          want = int(fan.x & 15u);
+        }
+      }
+      if (walk) {
+        live = poly_init_tet(P, G.V, G.det < 0.0);
+        ok = poly_clip_box<MAXV>(P, live, lo, hi, G.mn, G.mx, &cc);
+        if (ok) {
+          want = poly_fan_prepare<MAXV>(P, live, seen);
+          if (want < 0) {
+            ok = false;
+            want = 0;
+          }
         }
       }
     }
@@ -430,12 +461,15 @@ __global__ __launch_bounds__(kWave) void k_clip(
       int nsub = 0;
       if (ok && want > 0) {
         T* rec = pool + my * kRecord;
-        ok = emit_subtets<T>(
-            P, live, seen, lo, hi,
-            [&](int k, const T(&r)[kRecord]) {
-              if (fits && k < want) store_row<kRecord>(rec + int64_t(k) * kRecord, r);
-            },
-            vol6, nsub);
+        auto put = [&](int k, const T(&r)[kRecord]) {
+          if (fits && k < want) store_row<kRecord>(rec + int64_t(k) * kRecord, r);
+        };
+        if (walk) {
+          ok = emit_subtets<T, MAXV>(P, live, seen, lo, hi, put, vol6, nsub);
+        } else {
+          emit_subtets_table<T>(P, live, fan, lo, hi, put, vol6);
+          nsub = want;
+        }
       }
       if (ok && nsub != want) ok = false;
       ns += unsigned(nsub);
@@ -1675,6 +1709,8 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
             (st = hip_check(hipStreamWaitEvent(c->side, c->ev_fork, 0), "stream wait")))
           return st;
         if ((st = fork_masses())) return st;
+        ClipTables tab;
+        if ((st = clip_tables(tab))) return st;
         for (int k = 2; k >= 0; --k) {
           hipStream_t ks = k == 0 ? s : c->side;
           const int resident =
@@ -1682,7 +1718,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
                      : (k == 1 ? resident_blocks(k_clip<T, 12>) : resident_blocks(k_clip<T, kMaxV>));
           const int64_t nb = std::min<int64_t>(ceil_div(nc, kWave), resident);
 #define IBVT_CLIP_ARGS                                                                          \
-  cls_start + 64 * k * ntiles, cls_start + 64 * (k + 1) * ntiles, c->order.as<PairDesc>(),    \
+  tab, cls_start + 64 * k * ntiles, cls_start + 64 * (k + 1) * ntiles, c->order.as<PairDesc>(),    \
       c->tetrec.as<double>(), c->lat.as<double>(), c->ld, 1e-14, c->pool.as<T>(), c->pool_cap,  \
       c->pinfo.as<uint64_t>(), counters + kCntChunkPool + ch, flags, counters
           if (k == 0) k_clip<T, 10><<<dim3(unsigned(nb)), kWave, 0, ks>>>(IBVT_CLIP_ARGS);

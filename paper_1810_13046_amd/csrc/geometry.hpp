@@ -32,6 +32,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace ibvt {
 
 #include "quadrature.inc"
@@ -53,6 +55,33 @@ __host__ __device__ __forceinline__ int nb_find(uint32_t w, int v) {
   return nb_get(w, 0) == v ? 0 : (nb_get(w, 1) == v ? 1 : 2);
 }
 
+// k + 1 modulo 3
+__host__ __device__ __forceinline__ int nb_next(int k) { return k == 2 ? 0 : k + 1; }
+
+// A set of directed edges (vertex slot v, neighbour k), bit 3 v + k.
+template <int NS>
+struct EdgeMaskOf {
+  typedef uint64_t type;
+};
+template <>
+struct EdgeMaskOf<10> {
+  typedef uint32_t type;
+};
+template <int NS>
+using EdgeMask = typename EdgeMaskOf<NS>::type;
+__host__ __device__ __forceinline__ int ctz_edge(uint32_t m) { return __builtin_ctz(m); }
+__host__ __device__ __forceinline__ int ctz_edge(uint64_t m) { return __builtin_ctzll(m); }
+// bit / 3 for bit < 64
+__host__ __device__ __forceinline__ int edge_vertex(int bit) { return (bit * 43) >> 7; }
+// all the edges of the slots of `live`
+template <int NS>
+__host__ __device__ __forceinline__ EdgeMask<NS> live_edges(uint32_t live) {
+  EdgeMask<NS> m = 0;
+#pragma unroll
+  for (int v = 0; v < NS; ++v) m |= EdgeMask<NS>((live >> v) & 1u ? 7u : 0u) << (3 * v);
+  return m;
+}
+
 // Strided view of one piece's vertex graph (`all` = its usable slots: a
 // tet cut by c planes has at most 4 + c faces, hence at most 2(4 + c) − 4
 // vertices, and slot reuse never needs more than that).
@@ -61,21 +90,21 @@ struct PolyView {
   double* py;
   double* pz;
   uint32_t* pnb;
-  int S;
+  int S;                     // stride of the coordinates
   uint32_t all = kAllSlots;  // mask of the slots this view may use
+  int SN = S;                // stride of the neighbour words
   __host__ __device__ double& co(int v, int a) const {
     return (a == 0 ? px : (a == 1 ? py : pz))[v * S];
   }
   __host__ __device__ double& x(int v) const { return px[v * S]; }
   __host__ __device__ double& y(int v) const { return py[v * S]; }
   __host__ __device__ double& z(int v) const { return pz[v * S]; }
-  __host__ __device__ uint32_t& nb(int v) const { return pnb[v * S]; }
+  __host__ __device__ uint32_t& nb(int v) const { return pnb[v * SN]; }
 };
 
-// Load a tetrahedron (vertices V, any orientation); `flip` swaps vertices 2
+// Load a tetrahedron's vertices (any orientation); `flip` swaps vertices 2
 // and 3 so that the stored one is positively oriented.
-__host__ __device__ inline uint32_t poly_init_tet(const PolyView& P, const double V[4][3],
-                                                  bool flip) {
+__host__ __device__ inline void poly_put_tet(const PolyView& P, const double V[4][3], bool flip) {
   for (int v = 0; v < 2; ++v) {
     P.x(v) = V[v][0];
     P.y(v) = V[v][1];
@@ -87,6 +116,12 @@ __host__ __device__ inline uint32_t poly_init_tet(const PolyView& P, const doubl
   P.x(3) = flip ? V[2][0] : V[3][0];
   P.y(3) = flip ? V[2][1] : V[3][1];
   P.z(3) = flip ? V[2][2] : V[3][2];
+}
+
+// The same with its graph.
+__host__ __device__ inline uint32_t poly_init_tet(const PolyView& P, const double V[4][3],
+                                                  bool flip) {
+  poly_put_tet(P, V, flip);
   P.nb(0) = nb_pack(1, 3, 2);
   P.nb(1) = nb_pack(2, 3, 0);
   P.nb(2) = nb_pack(0, 3, 1);
@@ -104,11 +139,15 @@ struct ClipCount {
 
 // sv / den for 0 <= sv <= den, den > 0 (the parameter of a cut point on
 // an edge): the hardware reciprocal refined by two Newton steps, within an
-// ulp or two of the quotient (device code only).
-__device__ __forceinline__ double cut_param(double sv, double den) {
+// ulp or two of the quotient (on the host the quotient's reciprocal).
+__host__ __device__ __forceinline__ double cut_param(double sv, double den) {
+#if defined(__HIP_DEVICE_COMPILE__)
   double r = __builtin_amdgcn_rcp(den);
   r = fma(fma(-den, r, 1.0), r, r);
   r = fma(fma(-den, r, 1.0), r, r);
+#else
+  const double r = 1.0 / den;
+#endif
   return sv * r;
 }
 
@@ -139,32 +178,45 @@ __host__ __device__ __forceinline__ bool poly_clip_by(const PolyView& P, uint32_
     return true;
   }
   const uint32_t in = live & ~out;
-  uint32_t adj = 0;  // outside vertices with an inside neighbour
+  // the edges cut: (u, k) with u outside and its k-th neighbour inside
+  uint32_t adj = 0;
+  EdgeMask<NS> cut = 0;
   for (uint32_t m = out; m; m &= m - 1) {
     const int u = ctz32(m);
     const uint32_t w = P.nb(u);
-    if (((1u << nb_get(w, 0)) | (1u << nb_get(w, 1)) | (1u << nb_get(w, 2))) & in) adj |= 1u << u;
+    const uint32_t e = ((in >> nb_get(w, 0)) & 1u) | (((in >> nb_get(w, 1)) & 1u) << 1) |
+                       (((in >> nb_get(w, 2)) & 1u) << 2);
+    cut |= EdgeMask<NS>(e) << (3 * u);
+    if (e) adj |= 1u << u;
   }
   // free slots: never used, or outside with no inside neighbour
   uint32_t freem = (~live & P.all) | (out & ~adj);
   uint32_t newm = 0;
-  for (uint32_t m = adj; m; m &= m - 1) {
-    const int u = ctz32(m);
-    const double ux = P.x(u), uy = P.y(u), uz = P.z(u);
-    const double su = dist(u);
-    const uint32_t unb = P.nb(u);
-    bool first = true;
-    for (int k = 0; k < 3; ++k) {
+  {
+    // one cut point per round, by u and then k: the lanes of a wave go
+    // through max(cuts) rounds, not max(vertices) x 3
+    int u = -1;
+    double ux = 0.0, uy = 0.0, uz = 0.0, su = 0.0;
+    uint32_t unb = 0;
+    while (cut) {
+      const int bit = ctz_edge(cut);
+      cut &= cut - 1;
+      const int un = edge_vertex(bit), k = bit - 3 * un;
+      const bool first = un != u;
+      if (first) {
+        u = un;
+        ux = P.x(u);
+        uy = P.y(u);
+        uz = P.z(u);
+        su = dist(u);
+        unb = P.nb(u);
+      }
       const int v = nb_get(unb, k);
-      if (!((in >> v) & 1u)) continue;
       const double vx = P.x(v), vy = P.y(v), vz = P.z(v);
       const double sv = dist(v);
       const double t = cut_param(sv, sv - su);
-      int w;
-      if (first) {
-        w = u;  // v's neighbour entry already names u
-        first = false;
-      } else {
+      int w = u;  // v's neighbour entry already names u
+      if (!first) {
         if (!freem) return false;
         w = ctz32(freem);
         freem &= freem - 1;
@@ -180,21 +232,30 @@ __host__ __device__ __forceinline__ bool poly_clip_by(const PolyView& P, uint32_
     }
   }
   // Close the cap: from each new vertex walk around the face on its left
-  // until the next new vertex.
-  for (uint32_t m = newm; m; m &= m - 1) {
-    const int w = ctz32(m);
-    int vcur = w;
-    int vnext = nb_get(P.nb(w), 0);
-    int guard = 0;
-    do {
+  // until the next new vertex; one step of a lane's walks per round.
+  {
+    uint32_t m = newm;
+    int w = 0, vcur = 0, vnext = 0, guard = 0;
+    bool walking = false;
+    while (walking || m) {
+      if (!walking) {
+        w = ctz32(m);
+        m &= m - 1;
+        vcur = w;
+        vnext = nb_get(P.nb(w), 0);
+        guard = 0;
+      }
       const uint32_t nw = P.nb(vnext);
       const int np = nb_find(nw, vcur);
       vcur = vnext;
-      vnext = nb_get(nw, (np + 1) % 3);
+      vnext = nb_get(nw, nb_next(np));
       if (++guard > 3 * kMaxV) return false;
-    } while (!((newm >> vcur) & 1u));
-    P.nb(w) = nb_set(P.nb(w), 2, vcur);
-    P.nb(vcur) = nb_set(P.nb(vcur), 1, w);
+      walking = !((newm >> vcur) & 1u);
+      if (!walking) {
+        P.nb(w) = nb_set(P.nb(w), 2, vcur);
+        P.nb(vcur) = nb_set(P.nb(vcur), 1, w);
+      }
+    }
   }
   live = in | newm;
   if (cc) cc->cuts += uint32_t(__builtin_popcount(newm));
@@ -209,6 +270,108 @@ __host__ __device__ inline bool poly_clip(const PolyView& P, uint32_t& live, int
   return poly_clip_by<NS>(
       P, live, [&](int v) { return sgn * (P.co(v, a) - c); }, [&](int w) { P.co(w, a) = c; },
       cc);
+}
+
+// The same clip by look-up, for the first three planes that cut a tet
+// (gen_clip_table.py): the edges cut, the slots the new vertices take and
+// the graph that results depend on the graph before and the set of vertices
+// outside alone, so no graph is kept and none is walked; the vertex graph's
+// order of slots, neighbours and sub-tetrahedra is reproduced.
+//
+// Records of 128 bits.  Cut records, at [base + outside set]: up to six cuts
+// (u, v, w) of 4 bits each (u outside, v inside, w the new vertex), their
+// number (bits 72..74; 0: no such plane, the piece is left to the walk), the
+// slots in use after it (75..84), the graph's number (85..101) and its base
+// (102..119).  Fan records, by graph number: the count (bits 0..3), then (v,
+// f1, f2) of every sub-tetrahedron.  Graph records, by graph number: the
+// neighbour words, 12 bits a slot.
+struct ClipTables {
+  const uint4* cut;
+  const uint4* fan;
+  const uint4* graph;
+};
+
+struct TablePiece {
+  uint32_t live = 0xFu;  // slots in use (0: empty)
+  uint32_t base = 0;
+  uint32_t graph = 0;
+  bool odd = false;      // no record: the walk has to clip the piece
+};
+
+// One plane (as poly_clip_by), over slots below NS: 4, 6, 8 for the first,
+// second and third plane that may cut.
+template <int NS, typename Dist, typename Place>
+__host__ __device__ __forceinline__ void table_clip_by(const PolyView& P, TablePiece& q,
+                                              const ClipTables& tab, Dist&& dist, Place&& place,
+                                              ClipCount* cc) {
+  if (cc) {
+    cc->planes += 1;
+    cc->dist += uint32_t(__builtin_popcount(q.live));
+  }
+  uint32_t out = 0;
+#pragma unroll
+  for (int v = 0; v < NS; ++v) out |= dist(v) < 0.0 ? 1u << v : 0u;
+  out &= q.live;
+  if (!out) return;
+  if (out == q.live) {
+    q.live = 0;
+    return;
+  }
+  const uint4 r = tab.cut[q.base + out];
+  const int n = int((r.z >> 8) & 7u);
+  uint64_t list = r.x | (uint64_t(r.y) << 32);
+  uint32_t more = r.z & 0xffu;
+  for (int i = 0; i < n; ++i) {
+    const int u = int(list) & 15, v = int(list >> 4) & 15, w = int(list >> 8) & 15;
+    list = (list >> 12) | (uint64_t(more) << 52);
+    more = 0;
+    const double su = dist(u), sv = dist(v);
+    const double t = cut_param(sv, sv - su);
+    const double ux = P.x(u), uy = P.y(u), uz = P.z(u);
+    const double vx = P.x(v), vy = P.y(v), vz = P.z(v);
+    P.x(w) = vx + t * (ux - vx);
+    P.y(w) = vy + t * (uy - vy);
+    P.z(w) = vz + t * (uz - vz);
+    place(w);
+  }
+  q.live = (r.z >> 11) & 0x3ffu;
+  q.graph = (r.z >> 21) | ((r.w & 0x3fu) << 11);
+  q.base = r.w >> 6;
+  if (n == 0) {
+    q.odd = true;
+    q.live = 0;
+  }
+  if (cc) cc->cuts += uint32_t(n);
+}
+
+// Clip by the planes of the box [lo, hi] that the tet straddles, at most
+// three, in the order of poly_clip_box.
+__host__ __device__ __forceinline__ void table_clip_box(const PolyView& P, TablePiece& q,
+                                               const ClipTables& tab, const double lo[3],
+                                               const double hi[3], const double mn[3],
+                                               const double mx[3], ClipCount* cc) {
+  uint32_t planes = 0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (mx[a] <= lo[a] || mn[a] >= hi[a]) q.live = 0;
+    planes |= (mn[a] < lo[a] ? 1u : 0u) << (2 * a) | (mx[a] > hi[a] ? 2u : 0u) << (2 * a);
+  }
+  auto next = [&](auto slots) {
+    if (!q.live || !planes) return;
+    const int bit = ctz32(planes), a = bit >> 1;
+    planes &= planes - 1;
+    const double sgn = (bit & 1) ? -1.0 : 1.0;
+    const double l = a == 0 ? lo[0] : (a == 1 ? lo[1] : lo[2]);
+    const double h = a == 0 ? hi[0] : (a == 1 ? hi[1] : hi[2]);
+    const double c = (bit & 1) ? h : l;
+    double* x = a == 0 ? P.px : (a == 1 ? P.py : P.pz);
+    table_clip_by<decltype(slots)::value>(
+        P, q, tab, [&](int v) { return sgn * (x[v * P.S] - c); }, [&](int w) { x[w * P.S] = c; },
+        cc);
+  };
+  next(std::integral_constant<int, 4>{});
+  next(std::integral_constant<int, 6>{});
+  next(std::integral_constant<int, 8>{});
 }
 
 // Clip by the six planes of the box [lo, hi].  mn/mx bound the original
@@ -231,74 +394,94 @@ __host__ __device__ inline bool poly_clip_box(const PolyView& P, uint32_t& live,
   return true;
 }
 
-// Number of sub-tetrahedra poly_fan will emit: a 3-regular polyhedral graph
-// with V vertices has Σ_faces (deg − 2) = 2V − 4; faces through the apex
-// are skipped.  Returns -1 if a walk exceeds its bound.
-__host__ __device__ inline int poly_fan_count(const PolyView& P, uint32_t live) {
+// Walk the three faces through the apex (the lowest live vertex): their
+// directed edges are marked in `seen` (they give no sub-tetrahedra), and the
+// number of sub-tetrahedra of the fan is returned: Σ_faces (deg − 2) =
+// 2V − 4 for a 3-regular polyhedral graph, minus the apex faces.  One step
+// of a lane's walks per round.  Returns -1 if a walk exceeds its bound.
+template <int NS = kMaxV>
+__host__ __device__ inline int poly_fan_prepare(const PolyView& P, uint32_t live,
+                                                EdgeMask<NS>& seen) {
+  typedef EdgeMask<NS> Mask;
+  seen = 0;
   if (!live) return 0;
   const int apex = ctz32(live);
   int total = 2 * __builtin_popcount(live) - 4;
   const uint32_t aw = P.nb(apex);
-  for (int k = 0; k < 3; ++k) {
-    int prev = apex, cur = nb_get(aw, k), deg = 1, guard = 0;
-    while (cur != apex) {
-      const uint32_t cw = P.nb(cur);
-      const int nxt = nb_get(cw, (nb_find(cw, prev) + 1) % 3);
-      prev = cur;
-      cur = nxt;
-      ++deg;
-      if (++guard > 3 * kMaxV) return -1;
+  seen |= Mask(7) << (3 * apex);
+  int k = 0, prev = apex, cur = nb_get(aw, 0), deg = 1, guard = 0;
+  for (;;) {
+    const uint32_t cw = P.nb(cur);
+    const int nk = nb_next(nb_find(cw, prev));
+    seen |= Mask(1) << (3 * cur + nk);
+    prev = cur;
+    cur = nb_get(cw, nk);
+    ++deg;
+    if (++guard > 3 * kMaxV) return -1;
+    if (cur == apex) {
+      total -= deg - 2;
+      if (++k == 3) break;
+      prev = apex;
+      cur = nb_get(aw, k);
+      deg = 1;
+      guard = 0;
     }
-    total -= deg - 2;
   }
   return total;
 }
 
-// Call fn(apex, f0, f1, f2) for every sub-tetrahedron of the fan
-// decomposition.  Faces are walked with the same rule as the cap closure,
+// Call fn(v, f1, f2, fresh) for the sub-tetrahedra (apex, v, f1, f2) of the
+// fan, the faces not marked in `seen` in the order of their lowest directed
+// edge: v is the face's first vertex and f1, f2 go around it; fresh: the
+// face's first one.  Faces are walked with the same rule as the cap closure,
 // which traverses every face clockwise seen from outside, so each
-// sub-tetrahedron (apex, f0, f1, f2) has a non-positive determinant.
-template <typename F>
-__host__ __device__ inline bool poly_fan(const PolyView& P, uint32_t live, F&& fn) {
-  if (!live) return true;
-  const int apex = ctz32(live);
-  uint64_t seen = 0;
-  for (uint32_t m = live; m; m &= m - 1) {
-    const int v = ctz32(m);
-    const uint32_t vw = P.nb(v);
-    for (int k = 0; k < 3; ++k) {
-      if ((seen >> (3 * v + k)) & 1ull) continue;
-      // pass 1: mark the face's directed edges, look for the apex
-      bool has_apex = (v == apex);
-      int prev = v, cur = nb_get(vw, k);
-      seen |= 1ull << (3 * v + k);
-      int guard = 0;
-      while (cur != v) {
-        has_apex |= (cur == apex);
-        const uint32_t cw = P.nb(cur);
-        const int nk = (nb_find(cw, prev) + 1) % 3;
-        seen |= 1ull << (3 * cur + nk);
-        prev = cur;
-        cur = nb_get(cw, nk);
-        if (++guard > 3 * kMaxV) return false;
-      }
-      if (has_apex) continue;
-      // pass 2: fan from v
-      int f1 = nb_get(vw, k);
+// sub-tetrahedron has a non-positive determinant.  One step per round (a
+// face's last step, back at v, gives none).
+template <int NS, typename F>
+__host__ __device__ __forceinline__ bool poly_fan_faces(const PolyView& P, uint32_t live,
+                                                        EdgeMask<NS> seen, F&& fn) {
+  typedef EdgeMask<NS> Mask;
+  Mask todo = live_edges<NS>(live) & ~seen;
+  int v = 0, prev = 0, f1 = 0, guard = 0;
+  bool walking = false, fresh = false;
+  while (walking || todo) {
+    if (!walking) {
+      const int bit = ctz_edge(todo);
+      todo &= todo - 1;
+      v = edge_vertex(bit);
       prev = v;
+      f1 = nb_get(P.nb(v), bit - 3 * v);
+      walking = true;
+      fresh = true;
       guard = 0;
-      for (;;) {
-        const uint32_t cw = P.nb(f1);
-        const int f2 = nb_get(cw, (nb_find(cw, prev) + 1) % 3);
-        if (f2 == v) break;
-        fn(apex, v, f1, f2);
-        prev = f1;
-        f1 = f2;
-        if (++guard > 3 * kMaxV) return false;
-      }
+    }
+    const uint32_t cw = P.nb(f1);
+    const int nk = nb_next(nb_find(cw, prev));
+    todo &= ~(Mask(1) << (3 * f1 + nk));
+    const int f2 = nb_get(cw, nk);
+    if (f2 == v) {
+      walking = false;
+    } else {
+      fn(v, f1, f2, fresh);
+      fresh = false;
+      prev = f1;
+      f1 = f2;
+      if (++guard > 3 * kMaxV) return false;
     }
   }
   return true;
+}
+
+// Call fn(apex, f0, f1, f2) for every sub-tetrahedron of the fan
+// decomposition.
+template <int NS = kMaxV, typename F>
+__host__ __device__ __forceinline__ bool poly_fan(const PolyView& P, uint32_t live, F&& fn) {
+  if (!live) return true;
+  const int apex = ctz32(live);
+  EdgeMask<NS> seen;
+  if (poly_fan_prepare<NS>(P, live, seen) < 0) return false;
+  return poly_fan_faces<NS>(P, live, seen,
+                            [&](int v, int f1, int f2, bool) { fn(apex, v, f1, f2); });
 }
 
 // The 14 points and weights of the symmetric degree-5 rule on the
@@ -703,42 +886,14 @@ __host__ __device__ __forceinline__ T subtet_det(const T ya[3], const T yv[3], c
          d0[2] * (d1[0] * d2[1] - d1[1] * d2[0]);
 }
 
-// Walk the three faces through the apex (the lowest live vertex) once:
-// their directed edges are marked in `seen` (they give no sub-tetrahedra),
-// and the number of sub-tetrahedra of the fan is returned:
-// Σ_faces (deg − 2) = 2V − 4 for a 3-regular polyhedral graph, minus the
-// apex faces.  Returns -1 if a walk exceeds its bound.
-__host__ __device__ inline int poly_fan_prepare(const PolyView& P, uint32_t live, uint64_t& seen) {
-  seen = 0;
-  if (!live) return 0;
-  const int apex = ctz32(live);
-  int total = 2 * __builtin_popcount(live) - 4;
-  const uint32_t aw = P.nb(apex);
-  for (int k = 0; k < 3; ++k) {
-    seen |= 1ull << (3 * apex + k);
-    int prev = apex, cur = nb_get(aw, k), deg = 1, guard = 0;
-    while (cur != apex) {
-      const uint32_t cw = P.nb(cur);
-      const int nk = (nb_find(cw, prev) + 1) % 3;
-      seen |= 1ull << (3 * cur + nk);
-      prev = cur;
-      cur = nb_get(cw, nk);
-      ++deg;
-      if (++guard > 3 * kMaxV) return -1;
-    }
-    total -= deg - 2;
-  }
-  return total;
-}
-
 // Hand the fan's sub-tetrahedra of a clipped piece to put(k, r) in fan
 // order (k = 0, 1, ...; r = the record: cell-local vertices rounded to T);
 // vol6 receives the piece's 6·volume in cell-local units (double).  The faces
 // not marked in `seen` are walked once each; the apex, the face's first
 // vertex and the previous vertex stay in registers, so each sub-tetrahedron
 // reads one new vertex.
-template <typename T, typename Put>
-__host__ __device__ inline bool emit_subtets(const PolyView& P, uint32_t live, uint64_t seen,
+template <typename T, int NS, typename Put>
+__host__ __device__ inline bool emit_subtets(const PolyView& P, uint32_t live, EdgeMask<NS> seen,
                                              const double lo[3], const double hi[3], Put&& put,
                                              double& vol6, int& nsub) {
   vol6 = 0.0;
@@ -750,51 +905,78 @@ __host__ __device__ inline bool emit_subtets(const PolyView& P, uint32_t live, u
     y[1] = (P.y(v) - lo[1]) * ih[1];
     y[2] = (P.z(v) - lo[2]) * ih[2];
   };
-  const int apex = ctz32(live);
-  double ya[3];
-  local(apex, ya);
+  double ya[3], yv[3] = {0.0, 0.0, 0.0}, y1[3] = {0.0, 0.0, 0.0};
+  local(ctz32(live), ya);
   double vsum = 0.0;
-  for (uint32_t m = live; m; m &= m - 1) {
-    const int v = ctz32(m);
-    if (((seen >> (3 * v)) & 7ull) == 7ull) continue;  // all three faces done
-    const uint32_t vw = P.nb(v);
-    double yv[3];
-    local(v, yv);
-    for (int k = 0; k < 3; ++k) {
-      if ((seen >> (3 * v + k)) & 1ull) continue;
-      seen |= 1ull << (3 * v + k);
-      int prev = v, f1 = nb_get(vw, k), guard = 0;
-      double y1[3];
+  const bool ok = poly_fan_faces<NS>(P, live, seen, [&](int v, int f1, int f2, bool fresh) {
+    if (fresh) {
+      local(v, yv);
       local(f1, y1);
-      for (;;) {
-        const uint32_t cw = P.nb(f1);
-        const int nk = (nb_find(cw, prev) + 1) % 3;
-        seen |= 1ull << (3 * f1 + nk);
-        const int f2 = nb_get(cw, nk);
-        if (f2 == v) break;
-        double y2[3];
-        local(f2, y2);
-        vsum += subtet_det<double>(ya, yv, y1, y2);
-        T r[kRecord];
-        for (int e = 0; e < 3; ++e) {
-          r[e] = T(ya[e]);
-          r[3 + e] = T(yv[e]);
-          r[6 + e] = T(y1[e]);
-          r[9 + e] = T(y2[e]);
-        }
-        put(nsub, r);
-        ++nsub;
-        prev = f1;
-        f1 = f2;
-        y1[0] = y2[0];
-        y1[1] = y2[1];
-        y1[2] = y2[2];
-        if (++guard > 3 * kMaxV) return false;
-      }
     }
+    double y2[3];
+    local(f2, y2);
+    vsum += subtet_det<double>(ya, yv, y1, y2);
+    T r[kRecord];
+    for (int e = 0; e < 3; ++e) {
+      r[e] = T(ya[e]);
+      r[3 + e] = T(yv[e]);
+      r[6 + e] = T(y1[e]);
+      r[9 + e] = T(y2[e]);
+    }
+    put(nsub, r);
+    ++nsub;
+    y1[0] = y2[0];
+    y1[1] = y2[1];
+    y1[2] = y2[2];
+  });
+  vol6 = -vsum;
+  return ok;
+}
+
+// The same for a piece of table_clip_by: the fan's record f.
+template <typename T, typename Put>
+__host__ __device__ __forceinline__ void emit_subtets_table(const PolyView& P, uint32_t live, uint4 f,
+                                                   const double lo[3], const double hi[3],
+                                                   Put&& put, double& vol6) {
+  const double ih[3] = {1.0 / (hi[0] - lo[0]), 1.0 / (hi[1] - lo[1]), 1.0 / (hi[2] - lo[2])};
+  auto local = [&](int v, double y[3]) {
+    y[0] = (P.x(v) - lo[0]) * ih[0];
+    y[1] = (P.y(v) - lo[1]) * ih[1];
+    y[2] = (P.z(v) - lo[2]) * ih[2];
+  };
+  double ya[3], yv[3] = {0.0, 0.0, 0.0}, y1[3] = {0.0, 0.0, 0.0};
+  local(ctz32(live), ya);
+  double vsum = 0.0;
+  const int n = int(f.x & 15u);
+  uint64_t list = (f.x | (uint64_t(f.y) << 32)) >> 4 | (uint64_t(f.z) << 60);
+  uint64_t more = (f.z | (uint64_t(f.w) << 32)) >> 4;
+  int pv = -1, pf = -1;
+  for (int k = 0; k < n; ++k) {
+    const int v = int(list) & 15, f1 = int(list >> 4) & 15, f2 = int(list >> 8) & 15;
+    list = (list >> 12) | (more << 52);
+    more >>= 12;
+    if (v != pv || f1 != pf) {  // a face's first sub-tetrahedron
+      local(v, yv);
+      local(f1, y1);
+    }
+    pv = v;
+    pf = f2;
+    double y2[3];
+    local(f2, y2);
+    vsum += subtet_det<double>(ya, yv, y1, y2);
+    T r[kRecord];
+    for (int e = 0; e < 3; ++e) {
+      r[e] = T(ya[e]);
+      r[3 + e] = T(yv[e]);
+      r[6 + e] = T(y1[e]);
+      r[9 + e] = T(y2[e]);
+    }
+    put(k, r);
+    y1[0] = y2[0];
+    y1[1] = y2[1];
+    y1[2] = y2[2];
   }
   vol6 = -vsum;
-  return true;
 }
 
 // Clip tet ∩ box and call sub(y, det) for every sub-tetrahedron (cell-local
@@ -811,7 +993,7 @@ __host__ __device__ inline bool clip_fan_local(const PolyView& P, const TetGeom&
   cell_lambda<T>(G, lo, hi, LA, LG);
   if (!live) return true;
   double vsum = 0.0;
-  const bool ok = poly_fan(P, live, [&](int q0, int q1, int q2, int q3) {
+  const bool ok = poly_fan<NS>(P, live, [&](int q0, int q1, int q2, int q3) {
     const int qs[4] = {q0, q1, q2, q3};
     double yd[4][3];
     for (int v = 0; v < 4; ++v)

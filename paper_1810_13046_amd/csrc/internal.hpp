@@ -228,6 +228,10 @@ void release(ibvt_coupling* c, DevBuf& b);
 int scan_i64(ibvt_coupling* c, const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
 int scan_i32_to_i64(ibvt_coupling* c, const int32_t* in, int64_t* out, int64_t n, hipStream_t s);
 
+// clip_table.hip: device addresses of the clip tables (current device)
+struct ClipTables;
+int clip_tables(ClipTables& t);
+
 // assemble.hip
 int build_topology(ibvt_coupling* c, hipStream_t s);  // dim + 1 vertices per element
 int assemble_all(ibvt_coupling* c, hipStream_t s);    // dispatches on dim
