@@ -358,15 +358,18 @@ __global__ __launch_bounds__(kOrderItems) void k_order_scatter(
 // in fan order; the unused tail of a chunk is left empty.  The counters are
 // summed per wave and added once at the end.
 //
-// Bound: vector and scalar issue of the walks over the vertex graph, with
-// the LDS (28 bytes per slot and lane) holding two waves a SIMD.  With 10
-// slots (at most three planes) the clip is looked up (table_clip_box): no
-// graph is kept or walked, and ten waves fit a CU instead of eight.  On
-// 84.4M pairs all classes took 19.7 ms with the walks nested by vertex and
-// neighbour, 17.0 with one step or cut of every lane per round, and take
-// 11.0 with the look-up (float records, the other classes beside it).  A piece without a record, where rounding has
-// split a plane's inside or outside, is clipped again by the graph walk,
-// its neighbour words in the lane's own memory.
+// Bound: vector and scalar issue, with the LDS (28 bytes per slot and lane)
+// holding two waves a SIMD where the graph is kept.  The first three planes
+// that cut are looked up (clip_piece_box): with 10 slots no graph is kept or
+// walked and ten waves fit a CU instead of eight; with 12 and 16 slots the
+// graph is written once, after the third, and walked from there.  On 84.4M
+// pairs all classes took 19.7 ms with the walks nested by vertex and
+// neighbour, 17.0 with one step or cut of every lane per round, 11.0 with 10
+// slots looked up and take 10.7 with the look-up in all classes; on the
+// graded 397k-tet plate with its many pairs of four and more planes 3.65
+// became 3.07 by the last step.  A piece without a record, where rounding
+// has split a plane's inside or outside, is clipped again by the graph walk
+// (with 10 slots its neighbour words are in the lane's own memory).
 template <typename T, int MAXV>
 __global__ __launch_bounds__(kWave) void k_clip(
     ClipTables tab, const int64_t* __restrict__ cls_first, const int64_t* __restrict__ cls_end,
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(kWave) void k_clip(
     int64_t pool_cap, uint64_t* __restrict__ pinfo, unsigned long long* pool_used,
     unsigned* flags, unsigned long long* counters) {
   constexpr bool kTable = MAXV == 10;
-  __shared__ double sx[MAXV * kWave], sy[MAXV * kWave], sz[MAXV * kWave];
+  __shared__ double sv[3 * MAXV * kWave];
   __shared__ uint32_t snb[kTable ? 1 : MAXV * kWave];
   uint32_t own[kTable ? MAXV : 1];
   const int lane = threadIdx.x;
@@ -387,10 +390,7 @@ __global__ __launch_bounds__(kWave) void k_clip(
   const PairDesc* __restrict__ desc = desc_all + first;
   const int chunk = int(min<int64_t>(
       2048, max<int64_t>(1, (3 * n_list) / (8 * int64_t(gridDim.x)))));
-  const PolyView P = kTable
-                         ? PolyView{sx + lane, sy + lane, sz + lane, own, kWave, (1u << MAXV) - 1u, 1}
-                         : PolyView{sx + lane, sy + lane, sz + lane, snb + lane, kWave,
-                                    (1u << MAXV) - 1u};
+  const PolyView P = slots_view<MAXV>(sv + lane, snb + lane, own);
   unsigned long long nk = 0, nd = 0, ns = 0;
   ClipCount cc;
   unsigned long long cbase = 0;  // next free record of the wave's chunk
@@ -401,11 +401,7 @@ __global__ __launch_bounds__(kWave) void k_clip(
     TetGeom G;
     double lo[3], hi[3];
     int64_t p = 0;
-    uint32_t live = 0;
-    EdgeMask<MAXV> seen = 0;
-    int want = 0;
-    bool ok = true, walk = !kTable;
-    uint4 fan = make_uint4(0, 0, 0, 0);
+    Piece<MAXV> o;
     if (active) {
       int d, ci[3];
       int64_t t;
@@ -413,35 +409,13 @@ __global__ __launch_bounds__(kWave) void k_clip(
       double r[kTetRec];
       load_row<kTetRec>(tetrec + t * kTetRec, r);
       load_tet_box(G, r);
-      if (kTable) {
-        poly_put_tet(P, G.V, G.det < 0.0);
-        TablePiece q;
-        ClipCount c1 = cc;
-        table_clip_box(P, q, tab, lo, hi, G.mn, G.mx, &c1);
-        walk = q.odd;
-        if (!walk) {
-          cc = c1;
-          live = q.live;
-          if (live) fan = tab.fan[q.graph];
-          want = int(fan.x & 15u);
-        }
-      }
-      if (walk) {
-        live = poly_init_tet(P, G.V, G.det < 0.0);
-        ok = poly_clip_box<MAXV>(P, live, lo, hi, G.mn, G.mx, &cc);
-        if (ok) {
-          want = poly_fan_prepare<MAXV>(P, live, seen);
-          if (want < 0) {
-            ok = false;
-            want = 0;
-          }
-        }
-      }
+      clip_piece_box<MAXV>(P, tab, G, lo, hi, o, &cc);
     }
+    const int want = o.want;
     int incl = want;
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int y = __shfl_up(incl, o, kWave);
-      if (lane >= o) incl += y;
+    for (int s = 1; s < kWave; s <<= 1) {
+      const int y = __shfl_up(incl, s, kWave);
+      if (lane >= s) incl += y;
     }
     const int wave_total = __shfl(incl, kWave - 1, kWave);
     if (wave_total > cleft) {
@@ -459,17 +433,25 @@ __global__ __launch_bounds__(kWave) void k_clip(
       const bool fits = my + want <= pool_cap;
       double vol6 = 0.0;
       int nsub = 0;
+      bool ok = o.ok;
       if (ok && want > 0) {
         T* rec = pool + my * kRecord;
-        auto put = [&](int k, const T(&r)[kRecord]) {
-          if (fits && k < want) store_row<kRecord>(rec + int64_t(k) * kRecord, r);
-        };
-        if (walk) {
-          ok = emit_subtets<T, MAXV>(P, live, seen, lo, hi, put, vol6, nsub);
-        } else {
-          emit_subtets_table<T>(P, live, fan, lo, hi, put, vol6);
-          nsub = want;
-        }
+        ok = fan_local<MAXV>(P, o, lo, hi,
+                             [&](const double* a, const double* b, const double* c,
+                                 const double* d, double) IBVT_INLINE {
+                               T r[kRecord];
+#pragma unroll
+                               for (int e = 0; e < 3; ++e) {
+                                 r[e] = T(a[e]);
+                                 r[3 + e] = T(b[e]);
+                                 r[6 + e] = T(c[e]);
+                                 r[9 + e] = T(d[e]);
+                               }
+                               if (fits && nsub < want)
+                                 store_row<kRecord>(rec + int64_t(nsub) * kRecord, r);
+                               ++nsub;
+                             },
+                             vol6);
       }
       if (ok && nsub != want) ok = false;
       ns += unsigned(nsub);

@@ -38,6 +38,10 @@ namespace ibvt {
 
 #include "quadrature.inc"
 
+// on a lambda: always expanded where it is called (a call would put what it
+// captures in memory)
+#define IBVT_INLINE __attribute__((always_inline))
+
 constexpr int kMaxV = 16;
 constexpr uint32_t kAllSlots = (1u << kMaxV) - 1u;
 
@@ -86,7 +90,7 @@ __host__ __device__ __forceinline__ EdgeMask<NS> live_edges(uint32_t live) {
 // tet cut by c planes has at most 4 + c faces, hence at most 2(4 + c) − 4
 // vertices, and slot reuse never needs more than that).
 struct PolyView {
-  double* px;
+  double* px;                // px, py, pz: equally spaced
   double* py;
   double* pz;
   uint32_t* pnb;
@@ -101,6 +105,17 @@ struct PolyView {
   __host__ __device__ double& z(int v) const { return pz[v * S]; }
   __host__ __device__ uint32_t& nb(int v) const { return pnb[v * SN]; }
 };
+
+// One lane's view of a kernel's NS slots: its column of a wave's coordinate
+// rows (x of every slot, then y, then z) in LDS.  Ten slots are clipped by
+// look-up: their neighbour words, which only a piece without a record
+// needs, are the lane's own.
+template <int NS>
+__host__ __device__ __forceinline__ PolyView slots_view(double* v, uint32_t* column,
+                                                        uint32_t* own) {
+  return NS == 10 ? PolyView{v, v + NS * 64, v + 2 * NS * 64, own, 64, (1u << NS) - 1u, 1}
+                  : PolyView{v, v + NS * 64, v + 2 * NS * 64, column, 64, (1u << NS) - 1u, 64};
+}
 
 // Load a tetrahedron's vertices (any orientation); `flip` swaps vertices 2
 // and 3 so that the stored one is positively oriented.
@@ -128,6 +143,15 @@ __host__ __device__ inline uint32_t poly_init_tet(const PolyView& P, const doubl
   P.nb(3) = nb_pack(1, 2, 0);
   return 0xFu;
 }
+
+// Tet data shared by the clip kernels: vertices, orientation, volume and
+// barycentric gradients.
+struct TetGeom {
+  double V[4][3];
+  double det;      // e1 · (e2 × e3), e_k = V_k − V_0
+  double g[4][3];  // ∇λ_i
+  double mn[3], mx[3];  // bounding box
+};
 
 // Work counts of the clip (for throughput figures): planes clipped by,
 // signed distances evaluated and cut points made.
@@ -291,9 +315,11 @@ struct ClipTables {
   const uint4* graph;
 };
 
+constexpr uint32_t kNoBase = (1u << 18) - 1u;
+
 struct TablePiece {
   uint32_t live = 0xFu;  // slots in use (0: empty)
-  uint32_t base = 0;
+  uint32_t base = 0;     // kNoBase: three planes have cut, there are no further records
   uint32_t graph = 0;
   bool odd = false;      // no record: the walk has to clip the piece
 };
@@ -342,36 +368,6 @@ __host__ __device__ __forceinline__ void table_clip_by(const PolyView& P, TableP
     q.live = 0;
   }
   if (cc) cc->cuts += uint32_t(n);
-}
-
-// Clip by the planes of the box [lo, hi] that the tet straddles, at most
-// three, in the order of poly_clip_box.
-__host__ __device__ __forceinline__ void table_clip_box(const PolyView& P, TablePiece& q,
-                                               const ClipTables& tab, const double lo[3],
-                                               const double hi[3], const double mn[3],
-                                               const double mx[3], ClipCount* cc) {
-  uint32_t planes = 0;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    if (mx[a] <= lo[a] || mn[a] >= hi[a]) q.live = 0;
-    planes |= (mn[a] < lo[a] ? 1u : 0u) << (2 * a) | (mx[a] > hi[a] ? 2u : 0u) << (2 * a);
-  }
-  auto next = [&](auto slots) {
-    if (!q.live || !planes) return;
-    const int bit = ctz32(planes), a = bit >> 1;
-    planes &= planes - 1;
-    const double sgn = (bit & 1) ? -1.0 : 1.0;
-    const double l = a == 0 ? lo[0] : (a == 1 ? lo[1] : lo[2]);
-    const double h = a == 0 ? hi[0] : (a == 1 ? hi[1] : hi[2]);
-    const double c = (bit & 1) ? h : l;
-    double* x = a == 0 ? P.px : (a == 1 ? P.py : P.pz);
-    table_clip_by<decltype(slots)::value>(
-        P, q, tab, [&](int v) { return sgn * (x[v * P.S] - c); }, [&](int w) { x[w * P.S] = c; },
-        cc);
-  };
-  next(std::integral_constant<int, 4>{});
-  next(std::integral_constant<int, 6>{});
-  next(std::integral_constant<int, 8>{});
 }
 
 // Clip by the six planes of the box [lo, hi].  mn/mx bound the original
@@ -430,58 +426,179 @@ __host__ __device__ inline int poly_fan_prepare(const PolyView& P, uint32_t live
   return total;
 }
 
-// Call fn(v, f1, f2, fresh) for the sub-tetrahedra (apex, v, f1, f2) of the
-// fan, the faces not marked in `seen` in the order of their lowest directed
-// edge: v is the face's first vertex and f1, f2 go around it; fresh: the
-// face's first one.  Faces are walked with the same rule as the cap closure,
-// which traverses every face clockwise seen from outside, so each
-// sub-tetrahedron has a non-positive determinant.  One step per round (a
-// face's last step, back at v, gives none).
-template <int NS, typename F>
-__host__ __device__ __forceinline__ bool poly_fan_faces(const PolyView& P, uint32_t live,
-                                                        EdgeMask<NS> seen, F&& fn) {
-  typedef EdgeMask<NS> Mask;
-  Mask todo = live_edges<NS>(live) & ~seen;
-  int v = 0, prev = 0, f1 = 0, guard = 0;
-  bool walking = false, fresh = false;
-  while (walking || todo) {
-    if (!walking) {
-      const int bit = ctz_edge(todo);
-      todo &= todo - 1;
-      v = edge_vertex(bit);
-      prev = v;
-      f1 = nb_get(P.nb(v), bit - 3 * v);
-      walking = true;
-      fresh = true;
-      guard = 0;
-    }
-    const uint32_t cw = P.nb(f1);
-    const int nk = nb_next(nb_find(cw, prev));
-    todo &= ~(Mask(1) << (3 * f1 + nk));
-    const int f2 = nb_get(cw, nk);
-    if (f2 == v) {
-      walking = false;
-    } else {
-      fn(v, f1, f2, fresh);
-      fresh = false;
-      prev = f1;
-      f1 = f2;
-      if (++guard > 3 * kMaxV) return false;
+// A clipped piece: its slots in use, and its fan from a record or, where the
+// graph has been walked, from the graph.
+template <int NS>
+struct Piece {
+  uint32_t live = 0;
+  bool ok = true;     // false: a capacity or walk bound was exceeded
+  bool walk = false;
+  int want = 0;       // sub-tetrahedra of the fan
+  uint4 fan = {0, 0, 0, 0};
+  EdgeMask<NS> seen = 0;
+};
+
+// Clip the tet with vertices V by the planes plane(bit, run) of the mask
+// `planes`, ascending: run(dist, place) clips by one (poly_clip_by's
+// arguments); init() fills P with the tet and its graph.  The first three
+// planes that cut are looked up; then, or without a record, the vertex
+// graph is walked.
+template <int NS, typename Plane>
+__host__ __device__ __forceinline__ void clip_piece(const PolyView& P, const ClipTables& tab,
+                                                    const double V[4][3], bool flip,
+                                                    uint32_t planes, Plane&& plane, Piece<NS>& o,
+                                                    ClipCount* cc) {
+  o = Piece<NS>();
+  poly_put_tet(P, V, flip);
+  TablePiece q;
+  const uint32_t all = planes;
+  const ClipCount before = cc ? *cc : ClipCount();
+  auto look_up = [&](auto slots) IBVT_INLINE {
+    if (!q.live || !planes) return;
+    const int bit = ctz32(planes);
+    planes &= planes - 1;
+    plane(bit, [&](auto&& dist, auto&& place) IBVT_INLINE {
+      table_clip_by<decltype(slots)::value>(P, q, tab, dist, place, cc);
+    });
+  };
+  look_up(std::integral_constant<int, 4>{});
+  look_up(std::integral_constant<int, 6>{});
+  look_up(std::integral_constant<int, 8>{});
+  if (NS > 10)
+    while (q.live && planes && q.base != kNoBase) look_up(std::integral_constant<int, 8>{});
+  if (q.odd) {
+    o.walk = true;
+    o.live = poly_init_tet(P, V, flip);
+    planes = all;
+    if (cc) *cc = before;
+  } else {
+    o.live = q.live;
+    if (NS > 10 && o.live && planes) {
+      // the graph so far, for the planes left
+      o.walk = true;
+      const uint4 g = tab.graph[q.graph];
+      const uint64_t w[2] = {g.x | (uint64_t(g.y) << 32), g.z | (uint64_t(g.w) << 32)};
+#pragma unroll
+      for (int v = 0; v < 10; ++v) {
+        const uint32_t e = uint32_t(12 * v < 64 ? (w[0] >> (12 * v)) | (12 * v > 52 ? w[1] << (64 - 12 * v) : 0)
+                                                : w[1] >> (12 * v - 64));
+        P.nb(v) = (e & 15u) | ((e & 0xf0u) << 4) | ((e & 0xf00u) << 8);
+      }
     }
   }
-  return true;
+  if (o.walk) {
+    while (o.live && planes && o.ok) {
+      const int bit = ctz32(planes);
+      planes &= planes - 1;
+      plane(bit, [&](auto&& dist, auto&& place) IBVT_INLINE {
+        o.ok = poly_clip_by<NS>(P, o.live, dist, place, cc);
+      });
+    }
+    o.want = o.ok ? poly_fan_prepare<NS>(P, o.live, o.seen) : 0;
+    if (o.want < 0) {
+      o.ok = false;
+      o.want = 0;
+    }
+  } else if (o.live) {
+    o.fan = tab.fan[q.graph];
+    o.want = int(o.fan.x & 15u);
+  }
 }
 
-// Call fn(apex, f0, f1, f2) for every sub-tetrahedron of the fan
-// decomposition.
-template <int NS = kMaxV, typename F>
-__host__ __device__ __forceinline__ bool poly_fan(const PolyView& P, uint32_t live, F&& fn) {
-  if (!live) return true;
-  const int apex = ctz32(live);
-  EdgeMask<NS> seen;
-  if (poly_fan_prepare<NS>(P, live, seen) < 0) return false;
-  return poly_fan_faces<NS>(P, live, seen,
-                            [&](int v, int f1, int f2, bool) { fn(apex, v, f1, f2); });
+// The a-th of three values (arguments: chosen among as values, where a choice
+// among elements may become one among their addresses, in memory).
+template <typename T>
+__host__ __device__ __forceinline__ T pick3(int a, T x, T y, T z) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(x), "+v"(y), "+v"(z));
+#endif
+  return a == 0 ? x : (a == 1 ? y : z);
+}
+
+// clip_piece by the box [lo, hi].  mn/mx bound the tet: the piece never
+// leaves them, so a plane the tet does not straddle is skipped, and a box the
+// tet only touches gives an empty piece.  (As poly_clip_box, by look-up.)
+template <int NS>
+__host__ __device__ __forceinline__ void clip_piece_box(const PolyView& P, const ClipTables& tab,
+                                                        const TetGeom& G, const double lo[3],
+                                                        const double hi[3], Piece<NS>& o,
+                                                        ClipCount* cc) {
+  uint32_t planes = 0;
+  bool touch = false;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    touch |= G.mx[a] <= lo[a] || G.mn[a] >= hi[a];
+    planes |= (G.mn[a] < lo[a] ? 1u : 0u) << (2 * a) | (G.mx[a] > hi[a] ? 2u : 0u) << (2 * a);
+  }
+  if (touch) {
+    o = Piece<NS>();
+    return;
+  }
+  auto plane = [&](int bit, auto&& run) IBVT_INLINE {
+    const int a = bit >> 1;
+    const double sgn = (bit & 1) ? -1.0 : 1.0;
+    const double l = pick3(a, lo[0], lo[1], lo[2]), h = pick3(a, hi[0], hi[1], hi[2]);
+    const double c = (bit & 1) ? h : l;
+    double* x = P.px + a * int(P.py - P.px);
+    run([&](int v) IBVT_INLINE { return sgn * (x[v * P.S] - c); },
+        [&](int w) IBVT_INLINE { x[w * P.S] = c; });
+  };
+  clip_piece<NS>(P, tab, G.V, G.det < 0.0, planes, plane, o, cc);
+}
+
+// Call fn(v, f1, f2, fresh) for the sub-tetrahedra (apex, v, f1, f2) of the
+// piece's fan, apex = its lowest slot: the faces without the apex in the
+// order of their lowest directed edge, v the face's first vertex, f1 and f2
+// going around it; fresh: v or f1 is not the last call's v or f2.  Faces are
+// walked with the same rule as the cap closure, which traverses every face
+// clockwise seen from outside, so each sub-tetrahedron has a non-positive
+// determinant.  A lane takes one entry of its record or one step of its
+// walks per round (a face's last step, back at v, gives none): fn is there
+// once for both.
+template <int NS, typename F>
+__host__ __device__ __forceinline__ bool piece_fan(const PolyView& P, const Piece<NS>& o, F&& fn) {
+  typedef EdgeMask<NS> Mask;
+  uint64_t list = (o.fan.x | (uint64_t(o.fan.y) << 32)) >> 4 | (uint64_t(o.fan.z) << 60);
+  uint64_t more = (o.fan.z | (uint64_t(o.fan.w) << 32)) >> 4;
+  Mask todo = live_edges<NS>(o.live) & ~o.seen;
+  int left = o.walk ? 0 : o.want, guard = 0;
+  int v = -1, f1 = 0, f2 = -1, prev = 0;
+  bool walking = false;
+  if (!o.walk) todo = 0;
+  while (left || todo || walking) {
+    bool fresh, give = true;
+    if (!o.walk) {
+      const int nv = int(list) & 15;
+      f1 = int(list >> 4) & 15;
+      fresh = nv != v || f1 != f2;
+      v = nv;
+      f2 = int(list >> 8) & 15;
+      list = (list >> 12) | (more << 52);
+      more >>= 12;
+      --left;
+    } else {
+      fresh = !walking;
+      if (!walking) {
+        const int bit = ctz_edge(todo);
+        todo &= todo - 1;
+        v = edge_vertex(bit);
+        prev = v;
+        f1 = nb_get(P.nb(v), bit - 3 * v);
+        guard = 0;
+      } else {
+        prev = f1;
+        f1 = f2;
+      }
+      const uint32_t cw = P.nb(f1);
+      const int nk = nb_next(nb_find(cw, prev));
+      todo &= ~(Mask(1) << (3 * f1 + nk));
+      f2 = nb_get(cw, nk);
+      walking = give = f2 != v;
+      if (++guard > 3 * kMaxV) return false;
+    }
+    if (give) fn(v, f1, f2, fresh);
+  }
+  return true;
 }
 
 // The 14 points and weights of the symmetric degree-5 rule on the
@@ -781,15 +898,6 @@ __host__ __device__ inline void mom_shape(const T M[kMom], const T LA[4], const 
   }
 }
 
-// Tet data shared by the clip kernels: vertices, orientation, volume and
-// barycentric gradients.
-struct TetGeom {
-  double V[4][3];
-  double det;      // e1 · (e2 × e3), e_k = V_k − V_0
-  double g[4][3];  // ∇λ_i
-  double mn[3], mx[3];  // bounding box
-};
-
 // e1 · (e2 × e3) with e_k = V_k − V_0; c receives the cofactor rows
 // (e2 × e3, e3 × e1, e1 × e2).
 __host__ __device__ inline double tet_det(const double V[4][3], double c[3][3]) {
@@ -886,132 +994,77 @@ __host__ __device__ __forceinline__ T subtet_det(const T ya[3], const T yv[3], c
          d0[2] * (d1[0] * d2[1] - d1[1] * d2[0]);
 }
 
-// Hand the fan's sub-tetrahedra of a clipped piece to put(k, r) in fan
-// order (k = 0, 1, ...; r = the record: cell-local vertices rounded to T);
-// vol6 receives the piece's 6·volume in cell-local units (double).  The faces
-// not marked in `seen` are walked once each; the apex, the face's first
-// vertex and the previous vertex stay in registers, so each sub-tetrahedron
-// reads one new vertex.
-template <typename T, int NS, typename Put>
-__host__ __device__ inline bool emit_subtets(const PolyView& P, uint32_t live, EdgeMask<NS> seen,
-                                             const double lo[3], const double hi[3], Put&& put,
-                                             double& vol6, int& nsub) {
+// Hand the sub-tetrahedra (apex, v, f1, f2) of a piece's fan to put(ya, yv,
+// y1, y2, det) in fan order: their vertices in cell-local coordinates and
+// their determinants (<= 0); vol6 receives the piece's 6·volume in
+// cell-local units.  The apex, the face's first vertex and the previous
+// vertex stay in registers, so each sub-tetrahedron reads one new vertex.
+template <int NS, typename Put>
+__host__ __device__ __forceinline__ bool fan_local(const PolyView& P, const Piece<NS>& o,
+                                                   const double lo[3], const double hi[3],
+                                                   Put&& put, double& vol6) {
   vol6 = 0.0;
-  nsub = 0;
-  if (!live) return true;
+  if (!o.live) return true;
   const double ih[3] = {1.0 / (hi[0] - lo[0]), 1.0 / (hi[1] - lo[1]), 1.0 / (hi[2] - lo[2])};
-  auto local = [&](int v, double y[3]) {
+  auto local = [&](int v, double y[3]) IBVT_INLINE {
     y[0] = (P.x(v) - lo[0]) * ih[0];
     y[1] = (P.y(v) - lo[1]) * ih[1];
     y[2] = (P.z(v) - lo[2]) * ih[2];
   };
   double ya[3], yv[3] = {0.0, 0.0, 0.0}, y1[3] = {0.0, 0.0, 0.0};
-  local(ctz32(live), ya);
+  local(ctz32(o.live), ya);
   double vsum = 0.0;
-  const bool ok = poly_fan_faces<NS>(P, live, seen, [&](int v, int f1, int f2, bool fresh) {
+  const bool ok = piece_fan<NS>(P, o, [&](int v, int f1, int f2, bool fresh) IBVT_INLINE {
     if (fresh) {
       local(v, yv);
       local(f1, y1);
     }
     double y2[3];
     local(f2, y2);
-    vsum += subtet_det<double>(ya, yv, y1, y2);
-    T r[kRecord];
-    for (int e = 0; e < 3; ++e) {
-      r[e] = T(ya[e]);
-      r[3 + e] = T(yv[e]);
-      r[6 + e] = T(y1[e]);
-      r[9 + e] = T(y2[e]);
-    }
-    put(nsub, r);
-    ++nsub;
+    const double det = subtet_det<double>(ya, yv, y1, y2);
+    vsum += det;
+    put(ya, yv, y1, y2, det);
     y1[0] = y2[0];
     y1[1] = y2[1];
     y1[2] = y2[2];
   });
   vol6 = -vsum;
   return ok;
-}
-
-// The same for a piece of table_clip_by: the fan's record f.
-template <typename T, typename Put>
-__host__ __device__ __forceinline__ void emit_subtets_table(const PolyView& P, uint32_t live, uint4 f,
-                                                   const double lo[3], const double hi[3],
-                                                   Put&& put, double& vol6) {
-  const double ih[3] = {1.0 / (hi[0] - lo[0]), 1.0 / (hi[1] - lo[1]), 1.0 / (hi[2] - lo[2])};
-  auto local = [&](int v, double y[3]) {
-    y[0] = (P.x(v) - lo[0]) * ih[0];
-    y[1] = (P.y(v) - lo[1]) * ih[1];
-    y[2] = (P.z(v) - lo[2]) * ih[2];
-  };
-  double ya[3], yv[3] = {0.0, 0.0, 0.0}, y1[3] = {0.0, 0.0, 0.0};
-  local(ctz32(live), ya);
-  double vsum = 0.0;
-  const int n = int(f.x & 15u);
-  uint64_t list = (f.x | (uint64_t(f.y) << 32)) >> 4 | (uint64_t(f.z) << 60);
-  uint64_t more = (f.z | (uint64_t(f.w) << 32)) >> 4;
-  int pv = -1, pf = -1;
-  for (int k = 0; k < n; ++k) {
-    const int v = int(list) & 15, f1 = int(list >> 4) & 15, f2 = int(list >> 8) & 15;
-    list = (list >> 12) | (more << 52);
-    more >>= 12;
-    if (v != pv || f1 != pf) {  // a face's first sub-tetrahedron
-      local(v, yv);
-      local(f1, y1);
-    }
-    pv = v;
-    pf = f2;
-    double y2[3];
-    local(f2, y2);
-    vsum += subtet_det<double>(ya, yv, y1, y2);
-    T r[kRecord];
-    for (int e = 0; e < 3; ++e) {
-      r[e] = T(ya[e]);
-      r[3 + e] = T(yv[e]);
-      r[6 + e] = T(y1[e]);
-      r[9 + e] = T(y2[e]);
-    }
-    put(k, r);
-    y1[0] = y2[0];
-    y1[1] = y2[1];
-    y1[2] = y2[2];
-  }
-  vol6 = -vsum;
 }
 
 // Clip tet ∩ box and call sub(y, det) for every sub-tetrahedron (cell-local
 // coordinates as T, determinant as double).  Also returns the λ
 // coefficients in cell-local coordinates and 6|piece| (cell-local units).
 template <typename T, int NS = kMaxV, typename F>
-__host__ __device__ inline bool clip_fan_local(const PolyView& P, const TetGeom& G,
-                                               const double lo[3], const double hi[3], T LA[4],
-                                               T LG[4][3], double& vol6, F&& sub) {
+__host__ __device__ __forceinline__ bool clip_fan_local(const PolyView& P, const ClipTables& tab,
+                                                        const TetGeom& G, const double lo[3],
+                                                        const double hi[3], T LA[4], T LG[4][3],
+                                                        double& vol6, F&& sub) {
+  Piece<NS> o;
+  clip_piece_box<NS>(P, tab, G, lo, hi, o, nullptr);
   vol6 = 0.0;
-  uint32_t live = poly_init_tet(P, G.V, G.det < 0.0);
-  if (!poly_clip_box<NS>(P, live, lo, hi, G.mn, G.mx)) return false;
-  const double ih[3] = {1.0 / (hi[0] - lo[0]), 1.0 / (hi[1] - lo[1]), 1.0 / (hi[2] - lo[2])};
+  if (!o.ok) return false;
   cell_lambda<T>(G, lo, hi, LA, LG);
-  if (!live) return true;
-  double vsum = 0.0;
-  const bool ok = poly_fan<NS>(P, live, [&](int q0, int q1, int q2, int q3) {
-    const int qs[4] = {q0, q1, q2, q3};
-    double yd[4][3];
-    for (int v = 0; v < 4; ++v)
-      for (int e = 0; e < 3; ++e) yd[v][e] = (P.co(qs[v], e) - lo[e]) * ih[e];
-    double d[3][3];
-    for (int v = 0; v < 3; ++v)
-      for (int e = 0; e < 3; ++e) d[v][e] = yd[v + 1][e] - yd[0][e];
-    const double det = d[0][0] * (d[1][1] * d[2][2] - d[1][2] * d[2][1]) -
-                       d[0][1] * (d[1][0] * d[2][2] - d[1][2] * d[2][0]) +
-                       d[0][2] * (d[1][0] * d[2][1] - d[1][1] * d[2][0]);
-    vsum += det;
-    T y[4][3];
-    for (int v = 0; v < 4; ++v)
-      for (int e = 0; e < 3; ++e) y[v][e] = T(yd[v][e]);
-    sub(y, det);
-  });
-  vol6 = -vsum;
-  return ok;
+  return fan_local<NS>(P, o, lo, hi,
+                       [&](const double* a, const double* b, const double* c, const double* d,
+                           double det) IBVT_INLINE {
+                         T y[4][3];
+#pragma unroll
+                         for (int e = 0; e < 3; ++e) {
+                           y[0][e] = T(a[e]);
+                           y[1][e] = T(b[e]);
+                           y[2][e] = T(c[e]);
+                           y[3][e] = T(d[e]);
+                         }
+#if defined(__HIP_DEVICE_COMPILE__)
+                         // kept in the loop: products with the apex taken out of it
+                         // would round differently from the other vertices'
+#pragma unroll
+                         for (int e = 0; e < 3; ++e) asm volatile("" : "+v"(y[0][e]));
+#endif
+                         sub(y, det);
+                       },
+                       vol6);
 }
 
 }  // namespace ibvt

@@ -35,16 +35,16 @@ __device__ __forceinline__ void dual_weights(T zl[4]) {
 
 template <typename T>
 __global__ __launch_bounds__(kWave) void k_shape_pairs(
-    int64_t n_pairs, int64_t n_t, int64_t n_v, const int32_t* __restrict__ owner,
+    ClipTables tab, int64_t n_pairs, int64_t n_t, int64_t n_v, const int32_t* __restrict__ owner,
     const int64_t* __restrict__ pair_off, const CellRange* __restrict__ rng,
     const uint8_t* __restrict__ keep, const double* __restrict__ X,
     const int32_t* __restrict__ tets, const double* __restrict__ lat, LatDesc ld,
     const T* __restrict__ z, const T* u0, const T* u1, const T* u2, T* __restrict__ pg,
     int dual, unsigned* flags) {
-  __shared__ double sx[kMaxV * kWave], sy[kMaxV * kWave], sz[kMaxV * kWave];
+  __shared__ double sv[3 * kMaxV * kWave];
   __shared__ uint32_t snb[kMaxV * kWave];
   const int lane = threadIdx.x;
-  const PolyView P{sx + lane, sy + lane, sz + lane, snb + lane, kWave};
+  const PolyView P = slots_view<kMaxV>(sv + lane, snb + lane, nullptr);
   bool fail = false;
   for (int64_t p = int64_t(blockIdx.x) * kWave + lane; p < n_pairs;
        p += int64_t(gridDim.x) * kWave) {
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kWave) void k_shape_pairs(
     T LA[4], LG[4][3], A[12], Bs = T(0);
     for (int k = 0; k < 12; ++k) A[k] = T(0);
     double vol6;
-    const bool ok = clip_fan_local<T>(P, G, lo, hi, LA, LG, vol6, [&](const T (&y)[4][3], double det) {
+    const bool ok = clip_fan_local<T>(P, tab, G, lo, hi, LA, LG, vol6, [&](const T (&y)[4][3], double det) {
       subtet_grad<T>(y, T(det), LA, LG, zl, ul, A, Bs);
     });
     if (!ok) {
@@ -359,10 +359,12 @@ int shape_typed(ibvt_coupling* c, const void* z, const void* const u[3], const v
           c->tcorder.as<int32_t>(), pgt, c->dual ? 1 : 0);
   } else {
     const int64_t nb = std::min<int64_t>(ceil_div(c->n_pairs, kWave), int64_t(1) << 22);
+    ClipTables tab;
+    if ((st = clip_tables(tab))) return st;
     ProfScope ps("shape_pairs", s);
     if (nb > 0)
       k_shape_pairs<T><<<dim3(unsigned(nb)), kWave, 0, s>>>(
-        c->n_pairs, c->n_tet, c->n_vert, c->owner.as<int32_t>(), c->pair_off.as<int64_t>(),
+        tab, c->n_pairs, c->n_tet, c->n_vert, c->owner.as<int32_t>(), c->pair_off.as<int64_t>(),
         c->rng.as<CellRange>(), c->keep.as<uint8_t>(), c->X.as<double>(), c->tets.as<int32_t>(),
         c->lat.as<double>(), c->ld, static_cast<const T*>(z), static_cast<const T*>(u[0]),
         static_cast<const T*>(u[1]), static_cast<const T*>(u[2]), pg, c->dual ? 1 : 0, flags);

@@ -128,15 +128,24 @@ struct TcList {
     if (const int64_t i_ = i0_ + threadIdx.x; i_ < n_)                                      \
       if (const int64_t w = int64_t((lst).order[f_ + i_]); true)
 
+// The three kernels below are bound by FP64 issue of the clip and of the
+// 14-point rule, and by two waves a SIMD (LDS, and 220 to 256 VGPRs).
+// 200k-tet beam, cells of 1/192, float, apply / spread / shape: 6.7 /
+// 7.6 / 9.2 ms with the vertex graph walked for every plane, 4.2 / 5.8 / 7.8
+// with the first three planes that cut looked up and one copy of the
+// sub-tetrahedron's code for recorded and walked fans (two: 4.7 / 6.4 / 8.3).
 template <typename T, int MAXV>
 __global__ __launch_bounds__(kWave) void k_mf_tet_apply(
-    TcList lst, int64_t n_t, const CellRange* __restrict__ rng, const double* __restrict__ tetrec,
+    TcList lst, ClipTables tab, int64_t n_t, const CellRange* __restrict__ rng,
+    const double* __restrict__ tetrec,
     const double* __restrict__ lat, LatDesc ld, const T* x0, const T* x1, const T* x2, int dual,
     T* __restrict__ pt, unsigned* flags) {
-  __shared__ double sx[MAXV * kWave], sy[MAXV * kWave], sz[MAXV * kWave];
-  __shared__ uint32_t snb[MAXV * kWave];
+  constexpr bool kTable = MAXV == 10;
+  __shared__ double sv[3 * MAXV * kWave];
+  __shared__ uint32_t snb[kTable ? 1 : MAXV * kWave];
+  uint32_t own[kTable ? MAXV : 1];
   const int lane = threadIdx.x;
-  const PolyView P{sx + lane, sy + lane, sz + lane, snb + lane, kWave, (1u << MAXV) - 1u};
+  const PolyView P = slots_view<MAXV>(sv + lane, snb + lane, own);
   bool fail = false;
   ITEM_LOOP(lst, w) {
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -157,7 +166,7 @@ __global__ __launch_bounds__(kWave) void k_mf_tet_apply(
         T LA[4], LG[4][3], b4[4] = {T(0), T(0), T(0), T(0)};
         double vol6 = 0.0;
         const bool ok = clip_fan_local<T, MAXV>(
-            P, G, lo, hi, LA, LG, vol6, [&](const T (&y)[4][3], double det) {
+            P, tab, G, lo, hi, LA, LG, vol6, [&](const T (&y)[4][3], double det) {
               subtet_quad<T>(y, T(det), [&](T px, T py, T pz, T w) {
                 const T wu = w * trilinear<T>(xl, px, py, pz);
 #pragma unroll
@@ -218,14 +227,16 @@ __global__ __launch_bounds__(256) void k_mf_rows(int64_t n_v, int64_t n_t, int n
 
 template <typename T, int MAXV>
 __global__ __launch_bounds__(kWave) void k_mf_tet_spread(
-    TcList lst, int64_t n_t, int64_t n_v, const CellRange* __restrict__ rng,
+    TcList lst, ClipTables tab, int64_t n_t, int64_t n_v, const CellRange* __restrict__ rng,
     const double* __restrict__ tetrec, const int32_t* __restrict__ tets,
     const double* __restrict__ lat, LatDesc ld, const T* __restrict__ ys, double alpha, int dual,
     T* o0, T* o1, T* o2, unsigned* flags) {
-  __shared__ double sx[MAXV * kWave], sy[MAXV * kWave], sz[MAXV * kWave];
-  __shared__ uint32_t snb[MAXV * kWave];
+  constexpr bool kTable = MAXV == 10;
+  __shared__ double sv[3 * MAXV * kWave];
+  __shared__ uint32_t snb[kTable ? 1 : MAXV * kWave];
+  uint32_t own[kTable ? MAXV : 1];
   const int lane = threadIdx.x;
-  const PolyView P{sx + lane, sy + lane, sz + lane, snb + lane, kWave, (1u << MAXV) - 1u};
+  const PolyView P = slots_view<MAXV>(sv + lane, snb + lane, own);
   bool fail = false;
   ITEM_LOOP(lst, w) {
     TetCells tc;
@@ -251,7 +262,7 @@ __global__ __launch_bounds__(kWave) void k_mf_tet_spread(
       for (int j = 0; j < 8; ++j) b8[j] = T(0);
       double vol6 = 0.0;
       const bool ok = clip_fan_local<T, MAXV>(
-          P, G, lo, hi, LA, LG, vol6, [&](const T (&y)[4][3], double det) {
+          P, tab, G, lo, hi, LA, LG, vol6, [&](const T (&y)[4][3], double det) {
             subtet_quad<T>(y, T(det), [&](T px, T py, T pz, T w) {
               T wv = T(0);
 #pragma unroll
@@ -287,14 +298,16 @@ __global__ __launch_bounds__(kWave) void k_mf_tet_spread(
 
 template <typename T, int MAXV>
 __global__ __launch_bounds__(kWave) void k_mf_tet_shape(
-    TcList lst, int64_t n_t, int64_t n_v, const CellRange* __restrict__ rng,
+    TcList lst, ClipTables tab, int64_t n_t, int64_t n_v, const CellRange* __restrict__ rng,
     const double* __restrict__ tetrec, const int32_t* __restrict__ tets,
     const double* __restrict__ lat, LatDesc ld, const T* __restrict__ z, const T* u0,
     const T* u1, const T* u2, int dual, double* __restrict__ pgt, unsigned* flags) {
-  __shared__ double sx[MAXV * kWave], sy[MAXV * kWave], sz[MAXV * kWave];
-  __shared__ uint32_t snb[MAXV * kWave];
+  constexpr bool kTable = MAXV == 10;
+  __shared__ double sv[3 * MAXV * kWave];
+  __shared__ uint32_t snb[kTable ? 1 : MAXV * kWave];
+  uint32_t own[kTable ? MAXV : 1];
   const int lane = threadIdx.x;
-  const PolyView P{sx + lane, sy + lane, sz + lane, snb + lane, kWave, (1u << MAXV) - 1u};
+  const PolyView P = slots_view<MAXV>(sv + lane, snb + lane, own);
   bool fail = false;
   ITEM_LOOP(lst, w) {
     double acc[12];
@@ -323,7 +336,7 @@ __global__ __launch_bounds__(kWave) void k_mf_tet_shape(
 #pragma unroll
         for (int k = 0; k < 12; ++k) A[k] = T(0);
         double vol6 = 0.0;
-        const bool ok = clip_fan_local<T, MAXV>(P, G, lo, hi, LA, LG, vol6,
+        const bool ok = clip_fan_local<T, MAXV>(P, tab, G, lo, hi, LA, LG, vol6,
                                           [&](const T (&y)[4][3], double det) {
                                             subtet_grad<T>(y, T(det), LA, LG, zl, ul, A, Bs);
                                           });
@@ -400,9 +413,9 @@ inline TcList class_list(ibvt_coupling* c, int k) {
 // Launch kernel kern<MAXV> for the three slot classes on stream s.
 #define IBVT_MF_CLASSES(KERN, T, ...)                                                   \
   do {                                                                                  \
-    KERN<T, 10><<<class_blocks(3 * n_t, 0), kWave, 0, s>>>(class_list(c, 0), __VA_ARGS__); \
-    KERN<T, 12><<<class_blocks(3 * n_t, 1), kWave, 0, s>>>(class_list(c, 1), __VA_ARGS__); \
-    KERN<T, 16><<<class_blocks(3 * n_t, 2), kWave, 0, s>>>(class_list(c, 2), __VA_ARGS__); \
+    KERN<T, 10><<<class_blocks(3 * n_t, 0), kWave, 0, s>>>(class_list(c, 0), tab, __VA_ARGS__); \
+    KERN<T, 12><<<class_blocks(3 * n_t, 1), kWave, 0, s>>>(class_list(c, 1), tab, __VA_ARGS__); \
+    KERN<T, 16><<<class_blocks(3 * n_t, 2), kWave, 0, s>>>(class_list(c, 2), tab, __VA_ARGS__); \
   } while (0)
 
 template <typename T>
@@ -410,6 +423,8 @@ int apply_B_typed(ibvt_coupling* c, const void* const x[3], void* y, bool lumped
                   hipStream_t s) {
   const int64_t n_t = c->n_tet, n_v = c->n_vert;
   T* pt = c->pval.as<T>();  // 3 n_t x 4, sized by the assembly
+  ClipTables tab;
+  if (int st = clip_tables(tab)) return st;
   ProfScope ps("mf_apply", s);
   if (n_t > 0)
     IBVT_MF_CLASSES(k_mf_tet_apply, T,
@@ -426,6 +441,8 @@ template <typename T>
 int apply_Bt_typed(ibvt_coupling* c, const void* ys, void* const out[3], double alpha,
                    hipStream_t s) {
   const int64_t n_t = c->n_tet;
+  ClipTables tab;
+  if (int st = clip_tables(tab)) return st;
   ProfScope ps("mf_spread", s);
   if (n_t > 0)
     IBVT_MF_CLASSES(k_mf_tet_spread, T,
@@ -445,6 +462,8 @@ int shape_typed_mf(ibvt_coupling* c, const void* z, const void* const u[3], cons
   double* pgt = c->work2.as<double>();
   unsigned* flags = c->flags_dev.as<unsigned>();
   if ((st = hip_check(hipMemsetAsync(flags, 0, sizeof(unsigned), s), "memset"))) return st;
+  ClipTables tab;
+  if ((st = clip_tables(tab))) return st;
   {
     ProfScope ps("mf_shape", s);
     if (n_t > 0)

@@ -35,7 +35,8 @@ __host__ __device__ __forceinline__ int lam_index(int a, int i) {
 // λ_i = δ_i0 + g_i·y and μ_j = e_j + h_j·y,
 // ∫ λ_i μ_j = δ_i0 e_j M0 + δ_i0 h_j·M1 + e_j g_i·M1 + g_iᵀ M2 h_j.
 // Returns false if a capacity or walk bound fails.
-__host__ __device__ inline bool tet_pair_values(const PolyView& P, const double (&rs)[kURec],
+__host__ __device__ inline bool tet_pair_values(const PolyView& P, const ClipTables& tab,
+                                                const double (&rs)[kURec],
                                                 const double (&rf)[kURec], double (&acc)[16],
                                                 double& vol, double* lam = nullptr) {
   for (int k = 0; k < 16; ++k) acc[k] = 0.0;
@@ -46,25 +47,28 @@ __host__ __device__ inline bool tet_pair_values(const PolyView& P, const double 
   double V[4][3];
   for (int k = 0; k < 4; ++k)
     for (int e = 0; e < 3; ++e) V[k][e] = rs[3 * k + e];
-  uint32_t live = poly_init_tet(P, V, rs[24] < 0.0);
-  // half-space of the fluid tet opposite its vertex k: μ_k >= 0 (unrolled, so
-  // the record is indexed with constants)
+  // half-space of the fluid tet opposite its vertex k: μ_k >= 0 (the gradient
+  // by selects, so the record is indexed with constants)
+  auto plane = [&](int k, auto&& run) IBVT_INLINE {
+    double g[3];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (live && !fail) {
-      const double* gk = rf + 12 + 3 * k;
-      const double d0 = (k == 0) ? 1.0 : 0.0;
-      auto dist = [&](int v) {
-        return d0 + gk[0] * (P.x(v) - rf[0]) + gk[1] * (P.y(v) - rf[1]) +
-               gk[2] * (P.z(v) - rf[2]);
-      };
-      if (!poly_clip_by<kUSlots>(P, live, dist, [](int) {}, nullptr)) fail = true;
-    }
-  }
-  if (!live || fail) return !fail;
+    for (int e = 0; e < 3; ++e)
+      g[e] = k == 0 ? rf[12 + e] : (k == 1 ? rf[15 + e] : (k == 2 ? rf[18 + e] : rf[21 + e]));
+    const double d0 = (k == 0) ? 1.0 : 0.0;
+    run(
+        [&](int v) IBVT_INLINE {
+          return d0 + g[0] * (P.x(v) - rf[0]) + g[1] * (P.y(v) - rf[1]) +
+                 g[2] * (P.z(v) - rf[2]);
+        },
+        [](int) IBVT_INLINE {});
+  };
+  Piece<kUSlots> o;
+  clip_piece<kUSlots>(P, tab, V, rs[24] < 0.0, 0xFu, plane, o, nullptr);
+  if (!o.live || !o.ok) return o.ok;
+  const int a = ctz32(o.live);
   // moments of the piece: M0, M1[3], M2 (xx, xy, xz, yy, yz, zz)
   double m0 = 0.0, m1[3] = {0.0, 0.0, 0.0}, m2[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  const bool ok = poly_fan(P, live, [&](int a, int b, int c, int d) {
+  const bool ok = piece_fan<kUSlots>(P, o, [&](int b, int c, int d, bool) IBVT_INLINE {
     const int vv[4] = {a, b, c, d};
     double y[4][3];
     for (int q = 0; q < 4; ++q) {
