@@ -185,7 +185,7 @@ void release_all(ibvt_coupling* c) {
   DevBuf* bufs[] = {&c->lat,      &c->X,         &c->tets,      &c->vt_ptr,    &c->vt_tet,
                     &c->tetvol,   &c->tetrec,    &c->rng,       &c->pmom,      &c->cnt,
                     &c->pair_off, &c->owner,     &c->pval,      &c->keep,      &c->rownnz,
-                    &c->mark,     &c->cidx,      &c->tbuf,      &c->mlump,     &c->minv,
+                    &c->mark,     &c->tcnt,      &c->tbuf,      &c->mlump,     &c->minv,
                     &c->Mval32,   &c->Mdiag_inv, &c->flags_dev, &c->counters,  &c->scan_tmp,
                     &c->work,     &c->work2,     &c->zbuf,      &c->pool,      &c->pinfo,
                     &c->order,    &c->pscan,     &c->rowbox,    &c->rowcap,    &c->rowtmpoff,
@@ -855,7 +855,7 @@ int coupling_release_scratch(ibvt_coupling* c, hipStream_t stream) {
   if (c->dim != 3 || c->unstructured) return IBVT_OK;
   c->stream = stream;
   for (DevBuf* b : {&c->pool, &c->pinfo, &c->rowtmpcol, &c->rowtmpval, &c->rowbox, &c->rowcap,
-                    &c->rowtmpoff, &c->tbuf, &c->pscan, &c->mark, &c->cidx, &c->rowspilloff,
+                    &c->rowtmpoff, &c->tbuf, &c->pscan, &c->mark, &c->rowspilloff,
                     &c->rowspill})
     release(c, *b);
   // the matrix-free products keep their per-tet buffer and item order

@@ -1515,14 +1515,16 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     if ((st = hip_check(hipGetLastError(), "row box launch"))) return st;
     if ((st = scan_i64(c, c->rowcap.as<int64_t>(), c->rowtmpoff.as<int64_t>(), 3 * n_v, s)))
       return st;
-    k_row_spill_cap<<<blocks_for(3 * n_v, 256), 256, 0, s>>>(3 * n_v, c->rowbox.as<RowBox>(),
-                                                            c->rowcap.as<int64_t>());
-    if ((st = hip_check(hipGetLastError(), "row spill launch"))) return st;
-    if ((st = scan_i64(c, c->rowcap.as<int64_t>(), c->rowspilloff.as<int64_t>(), 3 * n_v, s)))
-      return st;
+    if (nchunk > 1) {  // (in one chunk no row is spilled)
+      k_row_spill_cap<<<blocks_for(3 * n_v, 256), 256, 0, s>>>(3 * n_v, c->rowbox.as<RowBox>(),
+                                                              c->rowcap.as<int64_t>());
+      if ((st = hip_check(hipGetLastError(), "row spill launch"))) return st;
+      if ((st = scan_i64(c, c->rowcap.as<int64_t>(), c->rowspilloff.as<int64_t>(), 3 * n_v, s)))
+        return st;
+    }
   }
   // read-back 1: the chunks' first pairs (the last entry is the pair count),
-  // the row scratch and spill sizes, the wide tets, and status flags
+  // the row scratch size, the wide tets, the spill size, and status flags
   int64_t pat[kMaxChunks + 4];
   {
     const int64_t* src[kMaxChunks + 4];
@@ -1530,8 +1532,8 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     int nsrc = nchunk + 1;
     if (!c->matrix_free) {
       src[nsrc++] = c->rowtmpoff.as<int64_t>() + 3 * n_v;
-      src[nsrc++] = c->rowspilloff.as<int64_t>() + 3 * n_v;
       src[nsrc++] = reinterpret_cast<const int64_t*>(counters + kCntWide);
+      if (nchunk > 1) src[nsrc++] = c->rowspilloff.as<int64_t>() + 3 * n_v;
     }
     if ((st = read_counts(c, src, nsrc, pat, s))) return st;
   }
@@ -1541,14 +1543,14 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     return set_error(IBVT_E_CAPACITY, "2^31 or more (tet, cell) pairs");
   c->n_pairs = n_pairs;
   if (c->matrix_free) return finish_matfree<T>(c, s);
-  const int64_t tmp_total = pat[nchunk + 1], spill_total = pat[nchunk + 2];
+  const int64_t tmp_total = pat[nchunk + 1], spill_total = nchunk > 1 ? pat[nchunk + 3] : 0;
   // Boundary integrals (k_pieces) or clipping: FP64 couplings whose tets are
   // all small enough for the octants' accuracy (kOctantCells) take the
   // former, 17.3 ms against 41 on the three-body mesh and 0.37 against 1.3 on
   // 47,916 tets.  Mixed couplings keep the clip: their moments are float
   // sums over its sub-tetrahedra, and their results are to stay what they
   // are to the last bit (the octants' would differ by float roundings).
-  const bool octants = sizeof(T) == sizeof(double) && pat[nchunk + 3] == 0;
+  const bool octants = sizeof(T) == sizeof(double) && pat[nchunk + 2] == 0;
   int64_t chunk_max = 0;
   for (int k = 0; k < nchunk; ++k) chunk_max = std::max(chunk_max, pat[k + 1] - pat[k]);
   if ((st = ensure(c, c->owner, size_t(n_pairs + 1) * sizeof(int32_t)))) return st;
@@ -1580,6 +1582,16 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
         c->rowspilloff.as<int64_t>(), spill_acc, spill_flg);
     return hip_check(hipGetLastError(), "rows launch");
   };
+  // row pointers of B^d; their last entries are the nonzeros
+  auto count_rows = [&]() -> int {
+    int64_t* out[3];
+    for (int d = 0; d < 3; ++d) {
+      c->B[d].nrows = n_v;
+      out[d] = c->B[d].rowptr.as<int64_t>();
+    }
+    return scan_i64_rows(c, c->rownnz.as<int64_t>(), out, 3, n_v, s);
+  };
+  int64_t nnzs[3] = {-1, -1, -1};
   // the solid masses need only the tet volumes: on the second stream beside
   // the first chunk's pieces, joined after them
   auto fork_masses = [&]() -> int {
@@ -1642,16 +1654,19 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
         (st = ensure(c, c->pool, size_t(want) * kRecord * sizeof(T))))
       return st;
     c->pool_cap = int64_t(c->pool.cap / (kRecord * sizeof(T)));
-    // clear the clip's counters (the zero-tet count of the preparation stays)
-    for (int k : {int(kCntPieces), int(kCntDropped), int(kCntSubtets), int(kCntDist),
-                  int(kCntCutPts), int(kCntPlanes)})
-      if ((st = hip_check(hipMemsetAsync(counters + k, 0, sizeof(unsigned long long), s),
+    // again: clear the clip's counters (the zero-tet count of the preparation
+    // stays)
+    if (attempt > 0) {
+      for (int k : {int(kCntPieces), int(kCntDropped), int(kCntSubtets), int(kCntDist),
+                    int(kCntCutPts), int(kCntPlanes)})
+        if ((st = hip_check(hipMemsetAsync(counters + k, 0, sizeof(unsigned long long), s),
+                            "memset")))
+          return st;
+      if ((st = hip_check(hipMemsetAsync(counters + kCntChunkPool, 0,
+                                         kMaxChunks * sizeof(unsigned long long), s),
                           "memset")))
         return st;
-    if ((st = hip_check(hipMemsetAsync(counters + kCntChunkPool, 0,
-                                       kMaxChunks * sizeof(unsigned long long), s),
-                        "memset")))
-      return st;
+    }
     // Chunks with pairs, in order.  Per chunk: the clip's classes 12 and 16
     // run on the side stream beside class 10 (they fill its tail), and the
     // next chunk's pair order is made on the side stream while this chunk
@@ -1737,35 +1752,33 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
         return st;
     }
 
-    // read-back 2: records each chunk asked for, flags
-    int64_t rb2[kMaxChunks];
+    // read-back 2: records each chunk asked for, nonzeros of the three
+    // components, flags
+    if ((st = count_rows())) return st;
+    int64_t rb2[kMaxChunks + 3];
     {
-      const int64_t* src[kMaxChunks];
+      const int64_t* src[kMaxChunks + 3];
       for (int k = 0; k < nchunk; ++k)
         src[k] = reinterpret_cast<const int64_t*>(counters + kCntChunkPool + k);
-      if ((st = read_counts(c, src, nchunk, rb2, s))) return st;
+      for (int d = 0; d < 3; ++d) src[nchunk + d] = c->B[d].rowptr.as<int64_t>() + n_v;
+      if ((st = read_counts(c, src, nchunk + 3, rb2, s))) return st;
     }
     if ((st = flags_status(c->host_flags))) return st;
     c->pool_needed = 0;
     for (int k = 0; k < nchunk; ++k) c->pool_needed = std::max(c->pool_needed, rb2[k]);
+    for (int d = 0; d < 3; ++d) nnzs[d] = rb2[nchunk + d];
     if (c->pool_needed <= c->pool_cap) break;
     if (attempt == 1) return set_error(IBVT_E_CAPACITY, "piece store could not be sized");
   }
   }
   // (IV) global assembly: rows of B^d (gathered per chunk above)
-  for (int d = 0; d < 3; ++d) {
-    c->B[d].nrows = n_v;
-    if ((st = scan_i64(c, c->rownnz.as<int64_t>() + d * n_v, c->B[d].rowptr.as<int64_t>(), n_v, s)))
-      return st;
-  }
-  // read-back 3: nonzeros of the three components, flags
-  int64_t nnzs[3] = {0, 0, 0};
-  {
+  if (nnzs[0] < 0) {
+    if ((st = count_rows())) return st;
     const int64_t* src[3] = {c->B[0].rowptr.as<int64_t>() + n_v, c->B[1].rowptr.as<int64_t>() + n_v,
                              c->B[2].rowptr.as<int64_t>() + n_v};
     if ((st = read_counts(c, src, 3, nnzs, s))) return st;
+    if ((st = flags_status(c->host_flags))) return st;
   }
-  if ((st = flags_status(c->host_flags))) return st;
   for (int d = 0; d < 3; ++d) {
     const int64_t nnz = nnzs[d];
     c->B[d].nnz = nnz;
@@ -1783,18 +1796,25 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
         c->B[0].val.as<T>(), c->B[1].val.as<T>(), c->B[2].val.as<T>());
   }
   if ((st = hip_check(hipGetLastError(), "rows compact launch"))) return st;
-  for (int d = 0; d < 3; ++d) {
+  const int64_t* touched[3];
+  {
     ProfScope ps("transpose", s);
-    if ((st = transpose_one<T>(c, d, s))) return st;
+    if ((st = transposes<T>(c, 3, touched, s))) return st;
   }
   // masses, unless they ran beside the first clip (no pairs at all)
   if (!masses_done && (st = solid_masses(c, s))) return st;
-  // read-back 4: the counters of the assembly, flags
-  int64_t cnt[kCntSlots];
+  // read-back 3: the counters of the assembly, the rows of B^dT, flags
+  int64_t cnt[kCntSlots + 3];
   {
-    const int64_t* src[kCntSlots];
+    const int64_t* src[kCntSlots + 3];
     for (int k = 0; k < kCntSlots; ++k) src[k] = reinterpret_cast<const int64_t*>(counters + k);
-    if ((st = read_counts(c, src, kCntSlots, cnt, s))) return st;
+    int n = kCntSlots;
+    for (int d = 0; d < 3; ++d)
+      if (touched[d]) src[n++] = touched[d];
+    if ((st = read_counts(c, src, n, cnt, s))) return st;
+    n = kCntSlots;
+    for (int d = 0; d < 3; ++d)
+      if (touched[d]) c->Bt[d].nrows = cnt[n++];
   }
   c->stats.pairs = n_pairs;
   c->stats.pieces = cnt[kCntPieces];

@@ -539,10 +539,27 @@ int assemble2_typed(ibvt_coupling* c, hipStream_t s) {
   }
   if ((st = hip_check(hipGetLastError(), "prep launch"))) return st;
   if ((st = scan_i64(c, c->cnt.as<int64_t>(), c->pair_off.as<int64_t>(), 2 * n_t, s))) return st;
-  if ((st = check_flags(c, s))) return st;
-  int64_t n_pairs = 0;
-  if ((st = read_back(c, &n_pairs, c->pair_off.as<int64_t>() + 2 * n_t, sizeof(int64_t), s)))
+  // the rows' boxes need the cell ranges alone
+  if ((st = ensure(c, c->rowbox, size_t(2 * n_v + 1) * 4 * sizeof(int32_t)))) return st;
+  if ((st = ensure(c, c->rowcap, size_t(2 * n_v + 1) * sizeof(int64_t)))) return st;
+  if ((st = ensure(c, c->rowtmpoff, size_t(2 * n_v + 1) * sizeof(int64_t)))) return st;
+  {
+    ProfScope ps("rows_box", s);
+    k_row_box2<<<blocks_for(2 * n_v, 256), 256, 0, s>>>(
+        n_v, n_t, c->vt_ptr.as<int64_t>(), c->vt_tet.as<int32_t>(), c->rng.as<CellRange>(),
+        c->rowbox.as<int32_t>(), c->rowcap.as<int64_t>());
+  }
+  if ((st = scan_i64(c, c->rowcap.as<int64_t>(), c->rowtmpoff.as<int64_t>(), 2 * n_v, s)))
     return st;
+  // read-back 1: pairs, the row scratch size, flags
+  int64_t got[2];
+  {
+    const int64_t* src[2] = {c->pair_off.as<int64_t>() + 2 * n_t,
+                             c->rowtmpoff.as<int64_t>() + 2 * n_v};
+    if ((st = read_counts(c, src, 2, got, s))) return st;
+  }
+  if ((st = flags_status(c->host_flags))) return st;
+  const int64_t n_pairs = got[0], tmp_total = got[1];
   if (n_pairs >= (int64_t(1) << 31) - 1)
     return set_error(IBVT_E_CAPACITY, "2^31 or more (triangle, cell) pairs");
   c->n_pairs = n_pairs;
@@ -562,20 +579,6 @@ int assemble2_typed(ibvt_coupling* c, hipStream_t s) {
   }
   if ((st = hip_check(hipGetLastError(), "pairs launch"))) return st;
   // rows
-  if ((st = ensure(c, c->rowbox, size_t(2 * n_v + 1) * 4 * sizeof(int32_t)))) return st;
-  if ((st = ensure(c, c->rowcap, size_t(2 * n_v + 1) * sizeof(int64_t)))) return st;
-  if ((st = ensure(c, c->rowtmpoff, size_t(2 * n_v + 1) * sizeof(int64_t)))) return st;
-  {
-    ProfScope ps("rows_box", s);
-    k_row_box2<<<blocks_for(2 * n_v, 256), 256, 0, s>>>(
-        n_v, n_t, c->vt_ptr.as<int64_t>(), c->vt_tet.as<int32_t>(), c->rng.as<CellRange>(),
-        c->rowbox.as<int32_t>(), c->rowcap.as<int64_t>());
-  }
-  if ((st = scan_i64(c, c->rowcap.as<int64_t>(), c->rowtmpoff.as<int64_t>(), 2 * n_v, s)))
-    return st;
-  int64_t tmp_total = 0;
-  if ((st = read_back(c, &tmp_total, c->rowtmpoff.as<int64_t>() + 2 * n_v, sizeof(int64_t), s)))
-    return st;
   if ((st = ensure(c, c->rowtmpcol, size_t(tmp_total + 1) * sizeof(int32_t)))) return st;
   if ((st = ensure(c, c->rowtmpval, size_t(tmp_total + 1) * sizeof(T)))) return st;
   {
@@ -587,16 +590,21 @@ int assemble2_typed(ibvt_coupling* c, hipStream_t s) {
         c->rowtmpcol.as<int32_t>(), c->rowtmpval.as<T>(), c->rownnz.as<int64_t>());
   }
   if ((st = hip_check(hipGetLastError(), "rows launch"))) return st;
-  for (int d = 0; d < 2; ++d) {
-    c->B[d].nrows = n_v;
-    if ((st = scan_i64(c, c->rownnz.as<int64_t>() + d * n_v, c->B[d].rowptr.as<int64_t>(), n_v,
-                       s)))
-      return st;
+  // read-back 2: nonzeros of the two components
+  int64_t nnzs[2];
+  {
+    int64_t* out[2];
+    const int64_t* src[2];
+    for (int d = 0; d < 2; ++d) {
+      c->B[d].nrows = n_v;
+      out[d] = c->B[d].rowptr.as<int64_t>();
+      src[d] = out[d] + n_v;
+    }
+    if ((st = scan_i64_rows(c, c->rownnz.as<int64_t>(), out, 2, n_v, s))) return st;
+    if ((st = read_counts(c, src, 2, nnzs, s))) return st;
   }
   for (int d = 0; d < 2; ++d) {
-    int64_t nnz = 0;
-    if ((st = read_back(c, &nnz, c->B[d].rowptr.as<int64_t>() + n_v, sizeof(int64_t), s)))
-      return st;
+    const int64_t nnz = nnzs[d];
     c->B[d].nnz = nnz;
     if (nnz >= (int64_t(1) << 31) - 1)
       return set_error(IBVT_E_CAPACITY, "more than 2^31 nonzeros in one component of B");
@@ -611,9 +619,10 @@ int assemble2_typed(ibvt_coupling* c, hipStream_t s) {
         c->B[1].col.as<int32_t>(), c->B[0].val.as<T>(), c->B[1].val.as<T>());
   }
   if ((st = hip_check(hipGetLastError(), "rows compact launch"))) return st;
-  for (int d = 0; d < 2; ++d) {
+  const int64_t* touched[3];
+  {
     ProfScope ps("transpose", s);
-    if ((st = transpose_one<T>(c, d, s))) return st;
+    if ((st = transposes<T>(c, 2, touched, s))) return st;
   }
   {
     ProfScope ps("masses", s);
@@ -629,18 +638,30 @@ int assemble2_typed(ibvt_coupling* c, hipStream_t s) {
           c->Mdiag_inv.as<double>());
   }
   if ((st = hip_check(hipGetLastError(), "mass launch"))) return st;
-  unsigned long long cnt[kCntSlots];
-  if ((st = read_back(c, cnt, counters, sizeof(cnt), s))) return st;
+  // read-back 3: the counters, the rows of B^dT, flags
+  int64_t cnt[5];
+  {
+    const int64_t* src[5];
+    int n = 0;
+    for (int k : {int(kCntPieces), int(kCntDropped), int(kCntZeroTets)})
+      src[n++] = reinterpret_cast<const int64_t*>(counters + k);
+    for (int d = 0; d < 2; ++d)
+      if (touched[d]) src[n++] = touched[d];
+    if ((st = read_counts(c, src, n, cnt, s))) return st;
+    n = 3;
+    for (int d = 0; d < 2; ++d)
+      if (touched[d]) c->Bt[d].nrows = cnt[n++];
+  }
   c->stats.pairs = n_pairs;
-  c->stats.pieces = int64_t(cnt[kCntPieces]);
-  c->stats.dropped = int64_t(cnt[kCntDropped]);
-  c->stats.zero_tets = int64_t(cnt[kCntZeroTets]);
+  c->stats.pieces = cnt[0];
+  c->stats.dropped = cnt[1];
+  c->stats.zero_tets = cnt[2];
   c->stats.subtets = 0;
   c->stats.dist_evals = 0;
   c->stats.cut_points = 0;
   c->mom_valid = true;
   c->stats.assemblies += 1;
-  return check_flags(c, s);
+  return flags_status(c->host_flags);
 }
 
 template <typename T>

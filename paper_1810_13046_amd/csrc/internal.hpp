@@ -185,8 +185,8 @@ struct ibvt_coupling {
   ibvt::DevBuf rowspill;     // double partial node sums + uint8 touched flags of rows that
                              // take pairs of several chunks
   ibvt::Csr B[3], Bt[3];
-  ibvt::DevBuf mark;         // int32 n_fluid + 1 (transposes of small operators)
-  ibvt::DevBuf cidx;         // int64 n_fluid + 1 (transposes of small operators)
+  ibvt::DevBuf mark;         // int32 per fluid node and sums (transposes of small operators)
+  ibvt::DevBuf tcnt;         // their touched nodes (int64 per component)
   ibvt::DevBuf tbuf;         // transpose scratch (bucket records and tables)
   ibvt::DevBuf mlump;        // double n_vert
   ibvt::DevBuf minv;         // T n_vert
@@ -226,6 +226,9 @@ void release(ibvt_coupling* c, DevBuf& b);
 
 // scan.hip: exclusive prefix sum; out has n+1 entries, out[n] = total.
 int scan_i64(ibvt_coupling* c, const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
+// m <= 3 arrays of n entries, one after the other at in, to out[0..m)
+int scan_i64_rows(ibvt_coupling* c, const int64_t* in, int64_t* const* out, int m, int64_t n,
+                  hipStream_t s);
 int scan_i32_to_i64(ibvt_coupling* c, const int32_t* in, int64_t* out, int64_t n, hipStream_t s);
 
 // clip_table.hip: device addresses of the clip tables (current device)
@@ -266,9 +269,10 @@ int assemble_all_2d(ibvt_coupling* c, hipStream_t s);
 int shape_gradient_2d(ibvt_coupling* c, const void* z, const void* const u[3], const void* us,
                       int mass, double alpha, double* gX, hipStream_t s);
 
-// transpose.hip
+// transpose.hip: B^dT, d < n.  Its rows' number is left on the device, at
+// touched[d] (to be read into Bt[d].nrows), or set (touched[d] null).
 template <typename T>
-int transpose_one(ibvt_coupling* c, int d, hipStream_t s);
+int transposes(ibvt_coupling* c, int n, const int64_t** touched, hipStream_t s);
 
 // sort.hip: stable sorts by small integer keys (n < 2^31).
 // A nonzero carried through the small operators' transpose: its value and

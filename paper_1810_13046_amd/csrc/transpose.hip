@@ -22,11 +22,17 @@
 //                     its own (a row's vertices are distinct); the block
 //                     writes the bucket's columns, values, row pointers and
 //                     row map.
-// Small operators take a counting sort over the whole lattice instead
-// (column marks and their prefix sum, column counts, a scatter into slots,
-// then each row of B^dT put in vertex order by ranking).  Atomics only
-// reserve space; every position follows from the (node, vertex) order, so
-// the result is deterministic either way.
+// Small operators take a counting sort over the whole lattice instead, the
+// components together and without waiting for a count:
+//   k_tcount          nonzeros per lattice node.
+//   k_tsums, k_tscan  per tile of nodes: its touched nodes and its nonzeros,
+//                     and their prefix sums.
+//   k_ttiles          row map, row pointers and each node's end in B^dT.
+//   k_tscatter        every nonzero takes a slot of its row.
+//   k_trow_order      each row of B^dT put in vertex order by ranking.
+// Atomics only reserve space; every position follows from the (node, vertex)
+// order, so the result is deterministic either way.
+#include <algorithm>
 #include <climits>
 #include <cstdlib>
 #include <type_traits>
@@ -37,17 +43,6 @@ namespace ibvt {
 
 namespace {
 
-__global__ void k_mark(int64_t nnz, const int32_t* __restrict__ col, int32_t* __restrict__ mark) {
-  const int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (k < nnz) mark[col[k]] = 1;
-}
-
-__global__ void k_compact(int64_t n, const int32_t* __restrict__ mark,
-                          const int64_t* __restrict__ cidx, int32_t* __restrict__ rowmap) {
-  const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j < n && mark[j]) rowmap[cidx[j]] = int32_t(j);
-}
-
 // A nonzero carried through the counting sort: its value and its row.
 template <typename T>
 using ValRow = std::conditional_t<std::is_same<T, float>::value, SortVal32, SortVal64>;
@@ -55,35 +50,164 @@ using ValRow = std::conditional_t<std::is_same<T, float>::value, SortVal32, Sort
 constexpr int kKeyLanes = 16;  // lanes per row of B^d in the counting sort's scatter
 
 // Counting sort for small operators, where the bucket path's fixed launches
-// dominate.  tcnt[c] = nonzeros of B^d in compacted column c (integer
-// atomics).
-__global__ void k_tcount(int64_t nnz, const int32_t* __restrict__ col,
-                         const int64_t* __restrict__ cidx, int32_t* __restrict__ tcnt) {
+// dominate: one component of a launch.  The components share every launch
+// and no count is waited for: bound by launches and the reading of the
+// lattice's counters, 32 us for a 144-tet beam on 32^3 cells, 220 us for 47,916
+// tets on 128^3 and 430 for 200,232 on 192^3, where component by component with
+// marks, two scans and a read-back for each they were 201, 322 and 598.
+template <typename T>
+struct TOne {
+  const int64_t* rowptr;  // B^d
+  const int32_t* col;
+  const T* val;
+  int64_t nnz;
+  int32_t* node;          // per lattice node (whole tiles): count, then end in B^dT
+  uint64_t* sum;          // per tile of nodes: touched nodes << 32 | nonzeros, then before it
+  int64_t tiles;
+  int64_t tile0;          // its first tile among the launch's
+  int64_t* touched;
+  int64_t* trowptr;       // B^dT
+  int32_t* rowmap;
+  int32_t* tcol;
+  T* tval;
+  ValRow<T>* vr;
+};
+template <typename T>
+struct TBatch {
+  TOne<T> c[3];
+  int n;
+};
+
+constexpr unsigned kTOrderBlocks = 4096;  // four rows each, then the next
+constexpr int kTThreads = 256;
+constexpr int kTItems = 16;
+constexpr int kTTile = kTThreads * kTItems;
+
+// (grid.y: the component)
+template <typename T>
+__global__ __launch_bounds__(256) void k_tcount(TBatch<T> b) {
+  const TOne<T>& c = blockIdx.y == 0 ? b.c[0] : (blockIdx.y == 1 ? b.c[1] : b.c[2]);
   const int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (k < nnz) atomicAdd(&tcnt[cidx[col[k]]], 1);
+  if (k < c.nnz) atomicAdd(&c.node[c.col[k]], 1);
 }
 
-// Every nonzero (i, j) of B^d takes a slot of row cidx[j] of B^dT by counting
-// that row's tcnt down (the slot order depends on timing; k_trow_order puts
+template <typename T>
+__device__ __forceinline__ const TOne<T>& tile_component(const TBatch<T>& b) {
+  const int64_t t = blockIdx.x;
+  return b.n > 2 && t >= b.c[2].tile0 ? b.c[2] : (b.n > 1 && t >= b.c[1].tile0 ? b.c[1] : b.c[0]);
+}
+
+// A thread's kTItems consecutive nodes of tile t.
+__device__ __forceinline__ void tile_nodes(const int32_t* node, int64_t t, int32_t (&v)[kTItems]) {
+  load_row<kTItems>(node + t * kTTile + int64_t(threadIdx.x) * kTItems, v);
+}
+__device__ __forceinline__ uint64_t nodes_sum(const int32_t (&v)[kTItems]) {
+  uint64_t s = 0;
+#pragma unroll
+  for (int k = 0; k < kTItems; ++k) s += v[k] > 0 ? (uint64_t(1) << 32) + uint32_t(v[k]) : 0;
+  return s;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kTThreads) void k_tsums(TBatch<T> b) {
+  __shared__ uint64_t red[kTThreads / kWave];
+  const TOne<T>& c = tile_component(b);
+  const int64_t t = int64_t(blockIdx.x) - c.tile0;
+  int32_t v[kTItems];
+  tile_nodes(c.node, t, v);
+  const int64_t s = wave_sum(int64_t(nodes_sum(v)));
+  if (lane_id() == 0) red[threadIdx.x / kWave] = uint64_t(s);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint64_t x = 0;
+    for (int w = 0; w < kTThreads / kWave; ++w) x += red[w];
+    c.sum[t] = x;
+  }
+}
+
+// Exclusive prefix of one value per thread across the block, and the total.
+template <int THREADS>
+__device__ __forceinline__ uint64_t block_prefix(uint64_t v, uint64_t (&sh)[THREADS / kWave],
+                                                 uint64_t& total) {
+  uint64_t x = v;
+  const int l = lane_id(), w = threadIdx.x / kWave;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint64_t y = __shfl_up((unsigned long long)x, o, kWave);
+    if (l >= o) x += y;
+  }
+  if (l == kWave - 1) sh[w] = x;
+  __syncthreads();
+  uint64_t pre = 0;
+  total = 0;
+  for (int k = 0; k < THREADS / kWave; ++k) {
+    if (k < w) pre += sh[k];
+    total += sh[k];
+  }
+  __syncthreads();
+  return pre + x - v;
+}
+
+// One block per component scans its tiles' sums in place and ends its row
+// pointers (fewer than 2^31 nonzeros and lattice nodes: the halves of a sum
+// do not overflow).
+template <typename T>
+__global__ __launch_bounds__(1024) void k_tscan(TBatch<T> b) {
+  __shared__ uint64_t sh[1024 / kWave];
+  const TOne<T>& c = blockIdx.x == 0 ? b.c[0] : (blockIdx.x == 1 ? b.c[1] : b.c[2]);
+  const int64_t per = ceil_div(c.tiles, 1024);
+  const int64_t b0 = int64_t(threadIdx.x) * per, b1 = min<int64_t>(c.tiles, b0 + per);
+  uint64_t s = 0;
+  for (int64_t t = b0; t < b1; ++t) s += c.sum[t];
+  uint64_t total;
+  uint64_t pre = block_prefix<1024>(s, sh, total);
+  for (int64_t t = b0; t < b1; ++t) {
+    const uint64_t v = c.sum[t];
+    c.sum[t] = pre;
+    pre += v;
+  }
+  if (threadIdx.x == 0) {
+    *c.touched = int64_t(total >> 32);
+    c.trowptr[total >> 32] = c.nnz;
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kTThreads) void k_ttiles(TBatch<T> b) {
+  __shared__ uint64_t sh[kTThreads / kWave];
+  const TOne<T>& c = tile_component(b);
+  const int64_t t = int64_t(blockIdx.x) - c.tile0;
+  int32_t v[kTItems];
+  tile_nodes(c.node, t, v);
+  uint64_t total;
+  uint64_t at = c.sum[t] + block_prefix<kTThreads>(nodes_sum(v), sh, total);
+  const int64_t n0 = t * kTTile + int64_t(threadIdx.x) * kTItems;
+#pragma unroll
+  for (int k = 0; k < kTItems; ++k) {
+    if (v[k] > 0) {
+      const uint32_t row = uint32_t(at >> 32), q = uint32_t(at);
+      c.rowmap[row] = int32_t(n0 + k);
+      c.trowptr[row] = int64_t(q);
+      c.node[n0 + k] = int32_t(q + uint32_t(v[k]));
+      at += (uint64_t(1) << 32) + uint32_t(v[k]);
+    }
+  }
+}
+
+// Every nonzero (i, j) of B^d takes a slot of node j's row of B^dT by
+// counting its end down (the slot order depends on timing; k_trow_order puts
 // each row in vertex order afterwards).
 template <typename T>
-__global__ __launch_bounds__(256) void k_tscatter(int64_t n_rows, const int64_t* __restrict__ rowptr,
-                                                  const int32_t* __restrict__ col,
-                                                  const T* __restrict__ val,
-                                                  const int64_t* __restrict__ cidx,
-                                                  const int64_t* __restrict__ trowptr,
-                                                  int32_t* __restrict__ tcnt,
-                                                  ValRow<T>* __restrict__ vr) {
+__global__ __launch_bounds__(256) void k_tscatter(TBatch<T> b, int64_t n_rows) {
+  const TOne<T>& c = blockIdx.y == 0 ? b.c[0] : (blockIdx.y == 1 ? b.c[1] : b.c[2]);
   const int64_t i = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kKeyLanes;
   const int lane = threadIdx.x % kKeyLanes;
   if (i >= n_rows) return;
-  for (int64_t k = rowptr[i] + lane; k < rowptr[i + 1]; k += kKeyLanes) {
-    const int64_t cc = cidx[col[k]];
-    const int slot = atomicSub(&tcnt[cc], 1) - 1;
+  const int64_t end = c.rowptr[i + 1];
+  for (int64_t k = c.rowptr[i] + lane; k < end; k += kKeyLanes) {
     ValRow<T> x;
-    x.v = val[k];
+    x.v = c.val[k];
     x.r = int32_t(i);
-    vr[trowptr[cc] + slot] = x;
+    c.vr[atomicSub(&c.node[c.col[k]], 1) - 1] = x;
   }
 }
 
@@ -91,33 +215,32 @@ __global__ __launch_bounds__(256) void k_tscatter(int64_t n_rows, const int64_t*
 // place in ascending vertex order is the number of the row's entries with a
 // smaller vertex.  The row is read in tiles of kWave entries whose vertices
 // are broadcast lane by lane.  Positions do not depend on the slot order
-// k_tscatter left, so the result is deterministic.
+// k_tscatter left, so the result is deterministic.  The number of rows is
+// on the device: the waves loop over them.
 template <typename T>
-__global__ __launch_bounds__(256) void k_trow_order(int64_t n_rows,
-                                                    const int64_t* __restrict__ trowptr,
-                                                    const ValRow<T>* __restrict__ vr,
-                                                    int32_t* __restrict__ tcol,
-                                                    T* __restrict__ tval) {
-  const int64_t r = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
+__global__ __launch_bounds__(256) void k_trow_order(TBatch<T> bt) {
+  const TOne<T>& c = blockIdx.y == 0 ? bt.c[0] : (blockIdx.y == 1 ? bt.c[1] : bt.c[2]);
   const int lane = lane_id();
-  if (r >= n_rows) return;  // the whole wave
-  const int64_t b = trowptr[r];
-  const int L = __builtin_amdgcn_readfirstlane(int(trowptr[r + 1] - b));
-  for (int c0 = 0; c0 < L; c0 += kWave) {
-    const bool mine = c0 + lane < L;
-    ValRow<T> x;
-    x.v = T(0);
-    x.r = INT_MAX;
-    if (mine) x = vr[b + c0 + lane];
-    int rank = 0;
-    for (int m0 = 0; m0 < L; m0 += kWave) {
-      const int y = (m0 + lane < L) ? vr[b + m0 + lane].r : INT_MAX;
-      const int nm = L - m0 < kWave ? L - m0 : kWave;
-      for (int m = 0; m < nm; ++m) rank += __builtin_amdgcn_readlane(y, m) < x.r ? 1 : 0;
-    }
-    if (mine) {
-      tcol[b + rank] = x.r;
-      tval[b + rank] = x.v;
+  const int64_t rows = *c.touched, step = int64_t(gridDim.x) * (blockDim.x / kWave);
+  for (int64_t r = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave; r < rows; r += step) {
+    const int64_t b = c.trowptr[r];
+    const int L = __builtin_amdgcn_readfirstlane(int(c.trowptr[r + 1] - b));
+    for (int c0 = 0; c0 < L; c0 += kWave) {
+      const bool mine = c0 + lane < L;
+      ValRow<T> x;
+      x.v = T(0);
+      x.r = INT_MAX;
+      if (mine) x = c.vr[b + c0 + lane];
+      int rank = 0;
+      for (int m0 = 0; m0 < L; m0 += kWave) {
+        const int y = (m0 + lane < L) ? c.vr[b + m0 + lane].r : INT_MAX;
+        const int nm = L - m0 < kWave ? L - m0 : kWave;
+        for (int m = 0; m < nm; ++m) rank += __builtin_amdgcn_readlane(y, m) < x.r ? 1 : 0;
+      }
+      if (mine) {
+        c.tcol[b + rank] = x.r;
+        c.tval[b + rank] = x.v;
+      }
     }
   }
 }
@@ -477,53 +600,63 @@ inline unsigned blocks_for(int64_t n, int threads) {
   return unsigned(ceil_div(n > 0 ? n : 1, threads));
 }
 
-// Counting sort over the whole lattice (small operators; nnz == 0 too).
+// Counting sort over the whole lattice (small operators; nnz == 0 too) of
+// the n components in ds.  The counts of touched nodes stay on the device,
+// in touched: B^dT's arrays are sized by what the counts cannot exceed.
 template <typename T>
-int transpose_counting(ibvt_coupling* c, int d, hipStream_t s) {
-  const int64_t nf = c->n_fluid[d];
-  const Csr& B = c->B[d];
-  Csr& Bt = c->Bt[d];
+int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** touched,
+                       hipStream_t s) {
+  TBatch<T> b{};
+  b.n = n;
+  int64_t tiles = 0, nnz = 0, nnz_max = 0, rows_max = 0;
+  for (int k = 0; k < n; ++k) {
+    b.c[k].tile0 = tiles;
+    b.c[k].tiles = ceil_div(c->n_fluid[ds[k]], kTTile);
+    tiles += b.c[k].tiles;
+  }
   int st;
-  if ((st = ensure(c, c->mark, size_t(nf + 1) * sizeof(int32_t)))) return st;
-  if ((st = ensure(c, c->cidx, size_t(nf + 1) * sizeof(int64_t)))) return st;
-  if ((st = hip_check(hipMemsetAsync(c->mark.p, 0, size_t(nf) * sizeof(int32_t), s), "memset")))
-    return st;
-  if (B.nnz)
-    k_mark<<<blocks_for(B.nnz, 256), 256, 0, s>>>(B.nnz, B.col.as<int32_t>(), c->mark.as<int32_t>());
-  if ((st = scan_i32_to_i64(c, c->mark.as<int32_t>(), c->cidx.as<int64_t>(), nf, s))) return st;
-  int64_t touched = 0;
-  {
-    const int64_t* src[1] = {c->cidx.as<int64_t>() + nf};
-    if ((st = read_counts(c, src, 1, &touched, s))) return st;
+  const size_t node_b = size_t(tiles) * kTTile * sizeof(int32_t);
+  if ((st = ensure(c, c->mark, node_b + size_t(tiles) * sizeof(uint64_t)))) return st;
+  if ((st = ensure(c, c->tcnt, 3 * sizeof(int64_t)))) return st;
+  for (int k = 0; k < n; ++k) {
+    const Csr& B = c->B[ds[k]];
+    Csr& Bt = c->Bt[ds[k]];
+    TOne<T>& o = b.c[k];
+    const int64_t rows = std::min<int64_t>(B.nnz, c->n_fluid[ds[k]]);
+    Bt.nnz = B.nnz;
+    if ((st = ensure(c, Bt.rowptr, size_t(rows + 1) * sizeof(int64_t)))) return st;
+    if ((st = ensure(c, Bt.rowmap, size_t(rows + 1) * sizeof(int32_t)))) return st;
+    if ((st = ensure(c, Bt.col, size_t(B.nnz + 1) * sizeof(int32_t)))) return st;
+    if ((st = ensure(c, Bt.val, size_t(B.nnz + 1) * sizeof(T)))) return st;
+    o.rowptr = B.rowptr.template as<int64_t>();
+    o.col = B.col.template as<int32_t>();
+    o.val = B.val.template as<T>();
+    o.nnz = B.nnz;
+    o.node = c->mark.as<int32_t>() + o.tile0 * kTTile;
+    o.sum = reinterpret_cast<uint64_t*>(c->mark.as<char>() + node_b) + o.tile0;
+    o.touched = c->tcnt.as<int64_t>() + ds[k];
+    o.trowptr = Bt.rowptr.template as<int64_t>();
+    o.rowmap = Bt.rowmap.template as<int32_t>();
+    o.tcol = Bt.col.template as<int32_t>();
+    o.tval = Bt.val.template as<T>();
+    touched[ds[k]] = o.touched;
+    nnz += B.nnz;
+    nnz_max = std::max(nnz_max, B.nnz);
+    rows_max = std::max(rows_max, rows);
   }
-  Bt.nrows = touched;
-  Bt.nnz = B.nnz;
-  if ((st = ensure(c, Bt.rowptr, size_t(touched + 1) * sizeof(int64_t)))) return st;
-  if ((st = ensure(c, Bt.rowmap, size_t(touched + 1) * sizeof(int32_t)))) return st;
-  if ((st = ensure(c, Bt.col, size_t(B.nnz + 1) * sizeof(int32_t)))) return st;
-  if ((st = ensure(c, Bt.val, size_t(B.nnz + 1) * sizeof(T)))) return st;
-  k_compact<<<blocks_for(nf, 256), 256, 0, s>>>(nf, c->mark.as<int32_t>(), c->cidx.as<int64_t>(),
-                                                Bt.rowmap.as<int32_t>());
-  if (B.nnz == 0) {
-    int64_t z = 0;
-    return hip_check(hipMemcpyAsync(Bt.rowptr.p, &z, sizeof(z), hipMemcpyHostToDevice, s),
-                     "rowptr");
+  if ((st = ensure(c, c->tbuf, size_t(nnz) * sizeof(ValRow<T>)))) return st;
+  for (int64_t k = 0, at = 0; k < n; at += b.c[k++].nnz) b.c[k].vr = c->tbuf.as<ValRow<T>>() + at;
+  if ((st = hip_check(hipMemsetAsync(c->mark.p, 0, node_b, s), "memset"))) return st;
+  const unsigned un = unsigned(n);
+  if (nnz_max) k_tcount<T><<<dim3(blocks_for(nnz_max, 256), un), 256, 0, s>>>(b);
+  k_tsums<T><<<unsigned(tiles), kTThreads, 0, s>>>(b);
+  k_tscan<T><<<un, 1024, 0, s>>>(b);
+  if (nnz_max) {
+    k_ttiles<T><<<unsigned(tiles), kTThreads, 0, s>>>(b);
+    k_tscatter<T><<<dim3(blocks_for(c->n_vert * kKeyLanes, 256), un), 256, 0, s>>>(b, c->n_vert);
+    k_trow_order<T><<<dim3(std::min(blocks_for(rows_max * kWave, 256), kTOrderBlocks), un), 256, 0,
+                      s>>>(b);
   }
-  // row pointers of B^dT from the per-column counts, then the scatter into
-  // slots and the per-row ordering
-  int32_t* tcnt = c->mark.as<int32_t>();  // the marks are no longer needed
-  if ((st = hip_check(hipMemsetAsync(tcnt, 0, size_t(touched) * sizeof(int32_t), s), "memset")))
-    return st;
-  k_tcount<<<blocks_for(B.nnz, 256), 256, 0, s>>>(B.nnz, B.col.as<int32_t>(),
-                                                  c->cidx.as<int64_t>(), tcnt);
-  if ((st = scan_i32_to_i64(c, tcnt, Bt.rowptr.as<int64_t>(), touched, s))) return st;
-  if ((st = ensure(c, c->tbuf, size_t(B.nnz) * sizeof(ValRow<T>)))) return st;
-  ValRow<T>* vr = c->tbuf.as<ValRow<T>>();
-  k_tscatter<T><<<blocks_for(c->n_vert * kKeyLanes, 256), 256, 0, s>>>(
-      c->n_vert, B.rowptr.as<int64_t>(), B.col.as<int32_t>(), B.val.as<T>(),
-      c->cidx.as<int64_t>(), Bt.rowptr.as<int64_t>(), tcnt, vr);
-  k_trow_order<T><<<blocks_for(touched * kWave, 256), 256, 0, s>>>(
-      touched, Bt.rowptr.as<int64_t>(), vr, Bt.col.as<int32_t>(), Bt.val.as<T>());
   return hip_check(hipGetLastError(), "transpose launch");
 }
 
@@ -594,14 +727,27 @@ int transpose_buckets(ibvt_coupling* c, int d, hipStream_t s) {
 
 }  // namespace
 
+// Components with fewer nonzeros than the bucket transpose is for go through
+// the counting sort together; larger ones that have too many vertices for
+// the buckets do so one by one (their scratch is as large as they are).
 template <typename T>
-int transpose_one(ibvt_coupling* c, int d, hipStream_t s) {
-  return c->B[d].nnz >= bucket_nnz() && c->n_vert < kBucketMaxVert
-             ? transpose_buckets<T>(c, d, s)
-             : transpose_counting<T>(c, d, s);
+int transposes(ibvt_coupling* c, int n, const int64_t** touched, hipStream_t s) {
+  const int64_t limit = bucket_nnz();
+  int small[3], ns = 0, st;
+  for (int d = 0; d < n; ++d) {
+    touched[d] = nullptr;
+    if (c->B[d].nnz < limit) {
+      small[ns++] = d;
+    } else if (c->n_vert < kBucketMaxVert) {
+      if ((st = transpose_buckets<T>(c, d, s))) return st;
+    } else if ((st = transpose_counting<T>(c, &d, 1, touched, s))) {
+      return st;
+    }
+  }
+  return ns ? transpose_counting<T>(c, small, ns, touched, s) : IBVT_OK;
 }
 
-template int transpose_one<float>(ibvt_coupling*, int, hipStream_t);
-template int transpose_one<double>(ibvt_coupling*, int, hipStream_t);
+template int transposes<float>(ibvt_coupling*, int, const int64_t**, hipStream_t);
+template int transposes<double>(ibvt_coupling*, int, const int64_t**, hipStream_t);
 
 }  // namespace ibvt

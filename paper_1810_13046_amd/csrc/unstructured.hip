@@ -354,7 +354,8 @@ __global__ void k_list_u(int64_t n_pairs, const int32_t* __restrict__ cand,
 // the graph walk, 418 us with the first three that cut looked up.
 template <typename T>
 __global__ __launch_bounds__(kWave) void k_pairs_u(
-    ClipTables tab, int64_t n_list, const int32_t* __restrict__ list, int64_t n_s,
+    ClipTables tab, const int64_t* __restrict__ n_list, const int32_t* __restrict__ list,
+    int64_t n_s,
     const int64_t* __restrict__ off,
     const int32_t* __restrict__ pf, const double* __restrict__ srec,
     const double* __restrict__ frec, double drop_rel, int dual, uint8_t* __restrict__ keep,
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(kWave) void k_pairs_u(
   const PolyView P = slots_view<kUSlots>(sv + lane, snb + lane, nullptr);
   const int64_t q = int64_t(blockIdx.x) * kWave + lane;
   bool kept = false, dropped = false, fail = false;
-  if (q < n_list) {
+  if (q < *n_list) {
     const int64_t p = list[q];
     const int64_t s = pair_owner(p, n_s, off);
     const int64_t f = pf[p];
@@ -663,25 +664,10 @@ __global__ __launch_bounds__(256) void k_rows_compact_u(
 // Rows of B by the LDS row gather; returns -1 (nothing written to B) when
 // some row has more than kURowMax distinct columns.
 template <typename T>
-int rows_by_lds(ibvt_coupling* c, int64_t n_pairs, hipStream_t s) {
+int rows_by_lds(ibvt_coupling* c, int64_t n_tmp, hipStream_t s) {
   const int64_t n_v = c->n_vert;
   int st;
-  if ((st = ensure(c, c->rowcap, size_t(n_v + 1) * sizeof(int64_t)))) return st;
-  if ((st = ensure(c, c->rowtmpoff, size_t(n_v + 1) * sizeof(int64_t)))) return st;
   if ((st = ensure(c, c->rownnz, size_t(n_v + 1) * sizeof(int64_t)))) return st;
-  {
-    ProfScope ps("rows_box", s);
-    if (n_v > 0)
-      k_row_cap_u<<<blocks_for(n_v, 256), 256, 0, s>>>(n_v, c->vt_ptr.as<int64_t>(),
-                                                       c->vt_tet.as<int32_t>(),
-                                                       c->pair_off.as<int64_t>(),
-                                                       c->rowcap.as<int64_t>());
-    if ((st = scan_i64(c, c->rowcap.as<int64_t>(), c->rowtmpoff.as<int64_t>(), n_v, s)))
-      return st;
-  }
-  int64_t n_tmp = 0;
-  if ((st = read_back(c, &n_tmp, c->rowtmpoff.as<int64_t>() + n_v, sizeof(int64_t), s)))
-    return st;
   if ((st = ensure(c, c->rowtmpcol, size_t(n_tmp + 1) * sizeof(int32_t)))) return st;
   if ((st = ensure(c, c->rowtmpval, size_t(n_tmp + 1) * sizeof(T)))) return st;
   auto* counters = c->counters.as<unsigned long long>();
@@ -699,11 +685,15 @@ int rows_by_lds(ibvt_coupling* c, int64_t n_pairs, hipStream_t s) {
     if ((st = hip_check(hipGetLastError(), "row gather launch"))) return st;
     if ((st = scan_i64(c, c->rownnz.as<int64_t>(), B.rowptr.as<int64_t>(), n_v, s))) return st;
   }
-  unsigned long long over = 0;
-  if ((st = read_back(c, &over, counters + kCntRowOverflow, sizeof(over), s))) return st;
-  if (over) return -1;
-  int64_t nnz = 0;
-  if ((st = read_back(c, &nnz, B.rowptr.as<int64_t>() + n_v, sizeof(int64_t), s))) return st;
+  // read-back 2: rows too wide, nonzeros
+  int64_t got[2];
+  {
+    const int64_t* src[2] = {reinterpret_cast<const int64_t*>(counters + kCntRowOverflow),
+                             B.rowptr.as<int64_t>() + n_v};
+    if ((st = read_counts(c, src, 2, got, s))) return st;
+  }
+  if (got[0]) return -1;
+  const int64_t nnz = got[1];
   B.nnz = nnz;
   if ((st = ensure(c, B.col, size_t(nnz + 1) * sizeof(int32_t)))) return st;
   if ((st = ensure(c, B.val, size_t(nnz + 1) * sizeof(T)))) return st;
@@ -806,8 +796,8 @@ int assemble_u_typed(ibvt_coupling* c, hipStream_t s) {
   const size_t tmp_bytes = (size_t(n_s + 1) * kSearchCap * sizeof(int32_t) + 255) & ~size_t(255);
   if ((st = ensure(c, c->ucoo, tmp_bytes + 256))) return st;
   int32_t* stmp = c->ucoo.as<int32_t>();
-  unsigned* ovf = reinterpret_cast<unsigned*>(c->ucoo.as<char>() + tmp_bytes);
-  if ((st = hip_check(hipMemsetAsync(ovf, 0, sizeof(unsigned), s), "memset"))) return st;
+  unsigned* ovf = reinterpret_cast<unsigned*>(c->ucoo.as<char>() + tmp_bytes);  // read as int64
+  if ((st = hip_check(hipMemsetAsync(ovf, 0, sizeof(int64_t), s), "memset"))) return st;
   {
     ProfScope ps("tree_search", s);
     if (n_s > 0)
@@ -818,10 +808,29 @@ int assemble_u_typed(ibvt_coupling* c, hipStream_t s) {
   }
   if ((st = hip_check(hipGetLastError(), "search launch"))) return st;
   if ((st = scan_i64(c, c->cnt.as<int64_t>(), c->pair_off.as<int64_t>(), n_s, s))) return st;
-  if ((st = check_flags(c, s))) return st;
-  int64_t n_pairs = 0;
-  if ((st = read_back(c, &n_pairs, c->pair_off.as<int64_t>() + n_s, sizeof(int64_t), s)))
-    return st;
+  // the rows' scratch needs the pair counts alone
+  if ((st = ensure(c, c->rowcap, size_t(n_v + 1) * sizeof(int64_t)))) return st;
+  if ((st = ensure(c, c->rowtmpoff, size_t(n_v + 1) * sizeof(int64_t)))) return st;
+  {
+    ProfScope ps("rows_box", s);
+    if (n_v > 0)
+      k_row_cap_u<<<blocks_for(n_v, 256), 256, 0, s>>>(n_v, c->vt_ptr.as<int64_t>(),
+                                                       c->vt_tet.as<int32_t>(),
+                                                       c->pair_off.as<int64_t>(),
+                                                       c->rowcap.as<int64_t>());
+    if ((st = scan_i64(c, c->rowcap.as<int64_t>(), c->rowtmpoff.as<int64_t>(), n_v, s)))
+      return st;
+  }
+  // read-back 1: pairs, tets that found too many, the row scratch size, flags
+  int64_t got[3];
+  {
+    const int64_t* src[3] = {c->pair_off.as<int64_t>() + n_s, reinterpret_cast<int64_t*>(ovf),
+                             c->rowtmpoff.as<int64_t>() + n_v};
+    if ((st = read_counts(c, src, 3, got, s))) return st;
+  }
+  if ((st = flags_status(c->host_flags))) return st;
+  const int64_t n_pairs = got[0];
+  const bool over = got[1] != 0;
   if (n_pairs >= (int64_t(1) << 31) / 16)
     return set_error(IBVT_E_CAPACITY, "too many (solid tet, fluid tet) pairs");
   c->n_pairs = n_pairs;
@@ -829,8 +838,6 @@ int assemble_u_typed(ibvt_coupling* c, hipStream_t s) {
   if ((st = ensure(c, c->keep, size_t(n_pairs + 1)))) return st;
   if ((st = ensure(c, c->pval, size_t(n_pairs + 1) * 16 * sizeof(T)))) return st;
   if ((st = ensure(c, c->pmom, size_t(n_pairs + 1) * kULam * sizeof(T)))) return st;
-  unsigned over = 0;
-  if ((st = read_back(c, &over, ovf, sizeof(over), s))) return st;
   {
     ProfScope ps("tree_search", s);
     if (n_s > 0 && over)  // some tet found more than kSearchCap: traverse again
@@ -851,7 +858,6 @@ int assemble_u_typed(ibvt_coupling* c, hipStream_t s) {
     int32_t* cand = c->ucoo.as<int32_t>();
     int64_t* pos = reinterpret_cast<int64_t*>(c->ucoo.as<char>() + cb);
     int32_t* list = reinterpret_cast<int32_t*>(c->ucoo.as<char>() + cb + pb);
-    int64_t n_list = 0;
     {
       ProfScope ps("pairs_filter", s);
       k_sep_u<<<blocks_for(n_pairs, 256), 256, 0, s>>>(
@@ -861,41 +867,47 @@ int assemble_u_typed(ibvt_coupling* c, hipStream_t s) {
       k_list_u<<<blocks_for(n_pairs, 256), 256, 0, s>>>(n_pairs, cand, pos, list);
       if ((st = hip_check(hipGetLastError(), "filter launch"))) return st;
     }
-    if ((st = read_back(c, &n_list, pos + n_pairs, sizeof(int64_t), s))) return st;
     ClipTables tab;
     if ((st = clip_tables(tab))) return st;
     ProfScope ps("pairs_tet", s);
-    if (n_list > 0)
-      k_pairs_u<T><<<unsigned(ceil_div(n_list, kWave)), kWave, 0, s>>>(
-          tab, n_list, list, n_s, c->pair_off.as<int64_t>(), c->owner.as<int32_t>(),
+    // the number left stays on the device: the blocks beyond it end at once
+    k_pairs_u<T><<<unsigned(ceil_div(n_pairs, kWave)), kWave, 0, s>>>(
+          tab, pos + n_pairs, list, n_s, c->pair_off.as<int64_t>(), c->owner.as<int32_t>(),
           c->tetrec.as<double>(), c->frec.as<double>(), 1e-14, c->dual ? 1 : 0,
           c->keep.as<uint8_t>(), c->pval.as<T>(), c->pmom.as<T>(), flags, counters);
   }
   if ((st = hip_check(hipGetLastError(), "pairs launch"))) return st;
   // (IV) B: rows gathered in LDS, or by sorting the entries when a row is
   // too wide for that
-  if ((st = rows_by_lds<T>(c, n_pairs, s)) > 0) return st;
+  if ((st = rows_by_lds<T>(c, got[2], s)) > 0) return st;
   if (st < 0 && (st = rows_by_sort<T>(c, n_pairs, s))) return st;
+  const int64_t* touched[3];
   {
     ProfScope ps("transpose", s);
-    if ((st = transpose_one<T>(c, 0, s))) return st;
+    if ((st = transposes<T>(c, 1, touched, s))) return st;
+  }
+  if ((st = solid_masses(c, s))) return st;
+  // the counters, the rows of B^T, flags
+  int64_t cnt[3];
+  {
+    const int64_t* src[3] = {reinterpret_cast<const int64_t*>(counters + kCntPieces),
+                             reinterpret_cast<const int64_t*>(counters + kCntDropped), touched[0]};
+    if ((st = read_counts(c, src, touched[0] ? 3 : 2, cnt, s))) return st;
+    if (touched[0]) c->Bt[0].nrows = cnt[2];
   }
   // the three velocity components share the fluid nodes: one B
   c->B[1] = c->B[2] = c->B[0];
   c->Bt[1] = c->Bt[2] = c->Bt[0];
-  if ((st = solid_masses(c, s))) return st;
-  unsigned long long cnt[kCntSlots];
-  if ((st = read_back(c, cnt, counters, sizeof(cnt), s))) return st;
   c->stats.pairs = n_pairs;
-  c->stats.pieces = int64_t(cnt[kCntPieces]);
-  c->stats.dropped = int64_t(cnt[kCntDropped]);
+  c->stats.pieces = cnt[0];
+  c->stats.dropped = cnt[1];
   c->stats.zero_tets = 0;
   c->stats.subtets = 0;
   c->stats.dist_evals = 0;
   c->stats.cut_points = 0;
   c->mom_valid = false;
   c->stats.assemblies += 1;
-  return check_flags(c, s);
+  return flags_status(c->host_flags);
 }
 
 // Reverse mode, one lane per (component d, solid tet s) walking the tet's
