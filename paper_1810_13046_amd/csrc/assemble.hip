@@ -42,7 +42,7 @@ namespace ibvt {
 
 namespace {
 
-constexpr int kRowNodes = 80;   // LDS box nodes per row per pass in k_rows
+constexpr int kRowNodes = 640;  // LDS box nodes of a wave's rows per pass in k_rows
 
 __device__ __forceinline__ int upper_bound_d(const double* L, int n, double x) {
   int lo = 0, hi = n;  // first index with L[idx] > x
@@ -1052,27 +1052,26 @@ __device__ __forceinline__ uint32_t div_magic(uint32_t q, uint32_t m) {
   return m ? __umulhi(q, m) : q;
 }
 
-constexpr int kRowsPerWave = 8;  // rows served by one wavefront in k_rows
-
-// Maximum of x over the kRowsPerWave row groups of a wavefront (lanes
-// hl, hl + H, ...), for loop bounds common to all of them.
+// Maximum of x over the row groups of a wavefront (lanes hl, hl + H, ...),
+// for loop bounds common to all of them.
+template <int H>
 __device__ __forceinline__ int64_t rows_max(int64_t x) {
-  for (int o = kWave / kRowsPerWave; o < kWave; o <<= 1) x = max(x, __shfl_xor(x, o, kWave));
+  for (int o = H; o < kWave; o <<= 1) x = max(x, __shfl_xor(x, o, kWave));
   return x;
 }
 
 // Gather the pieces of the incident tets into the row's node box, kept in
-// LDS kRowNodes nodes at a time.  Each wavefront serves kRowsPerWave rows,
-// H = 64 / kRowsPerWave lanes each, so the memory latency of one row's steps
-// overlaps the others'.  The row's incident tets are taken in ascending
-// order; for each, the lanes take its pairs (cells), H at a time, each lane
-// loading its pair's 8 values of this vertex at once, and the values are
-// added corner by corner: for one corner the cells of one tet are distinct,
+// LDS 640 / RPW nodes at a time.  Each wavefront serves RPW rows, H = 64 / RPW
+// lanes each, so the memory latency of one row's steps overlaps the others'.
+// The row's incident tets are taken in ascending order; for each, the lanes
+// take its pairs (cells), H at a time, each lane loading its pair's 8 values
+// of this vertex at once, and the values are added eight cells after eight
+// cells, corner by corner: for one corner the cells of one tet are distinct,
 // so are the nodes they add to, and every node sums its contributions in
-// the order (tet, corner) whatever the timing (deterministic, no value
-// atomics outside LDS).  Per batch of H incident tets, each tet's offsets
-// are set up once in LDS.  Touched nodes are written column-sorted at
-// tmp_off[w].
+// the order (tet, eight cells, corner) whatever the timing and RPW
+// (deterministic, no value atomics outside LDS).  Per batch of H incident
+// tets, each tet's offsets are set up once in LDS.  Touched nodes are written
+// column-sorted at tmp_off[w].
 //
 // One launch per pair chunk ch (items [tc_lo, tc_hi), pairs from p_base,
 // values in pval planes of plane_pairs pairs), over the rows w_begin ..
@@ -1080,8 +1079,12 @@ __device__ __forceinline__ int64_t rows_max(int64_t x) {
 // whose pairs lie in several chunks starts from zero in its first chunk,
 // keeps its node sums (double) and touched flags in its spill space between
 // the chunks, and is written in its last; the chunks come in tet order, so
-// every node still sums in (tet, corner) order.
-template <typename T>
+// every node still sums in that order.
+//
+// Bound: with few or wide rows the chain of a row's steps (a load and eight
+// LDS adds each, and again for every 640 / RPW nodes of its box); with many
+// rows the LDS adds.  rows_per_wave chooses.
+template <typename T, int RPW>
 __global__ __launch_bounds__(256) void k_rows(
     int64_t n_v, int64_t n_t, int ch, int64_t tc_lo, int64_t tc_hi, int64_t p_base,
     int64_t plane_pairs, int64_t w_begin, int64_t n_rows, const int64_t* __restrict__ vt_ptr,
@@ -1092,16 +1095,17 @@ __global__ __launch_bounds__(256) void k_rows(
     int32_t* __restrict__ tmp_col, T* __restrict__ tmp_val, int64_t* __restrict__ rownnz,
     const int64_t* __restrict__ spill_off, double* __restrict__ spill_acc,
     uint8_t* __restrict__ spill_flg) {
-  constexpr int H = kWave / kRowsPerWave;  // lanes per row
-  constexpr int RB = 4 * kRowsPerWave;     // rows per block
-  __shared__ double s_acc[RB][kRowNodes];  // summed in double in both precisions
-  __shared__ uint8_t s_flag[RB][kRowNodes];
+  constexpr int H = kWave / RPW;   // lanes per row
+  constexpr int RB = 4 * RPW;      // rows per block
+  constexpr int NODES = kRowNodes / RPW;
+  __shared__ double s_acc[RB][NODES];  // summed in double in both precisions
+  __shared__ uint8_t s_flag[RB][NODES];
   __shared__ int4 s_m0[RB][H], s_m1[RB][H];
   const int lane = lane_id();
   const int h = lane / H, hl = lane % H;
-  const int slot = kRowsPerWave * (threadIdx.x / kWave) + h;  // this row's LDS slot
+  const int slot = RPW * (threadIdx.x / kWave) + h;  // this row's LDS slot
   const int64_t wl =
-      kRowsPerWave * ((int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave) + h;
+      RPW * ((int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave) + h;
   const int64_t w = w_begin + wl;
   double* acc = s_acc[slot];
   uint8_t* flg = s_flag[slot];
@@ -1128,11 +1132,11 @@ __global__ __launch_bounds__(256) void k_rows(
   for (int j = 0; j < 8; ++j) coff[j] = (j & 1) + bn0 * (((j >> 1) & 1) + bn1 * (j >> 2));
   const int64_t vplane = plane_pairs * 8;
   // loop bounds common to the row groups of the wave (each masks its own work)
-  const int64_t total_max = rows_max(total);
+  const int64_t total_max = rows_max<H>(total);
   const int64_t ntet = end - beg;
-  const int64_t ntet_max = rows_max(ntet);
-  for (int64_t c0 = 0; c0 < total_max; c0 += kRowNodes) {
-    const int span = int(max<int64_t>(0, min<int64_t>(kRowNodes, total - c0)));
+  const int64_t ntet_max = rows_max<H>(ntet);
+  for (int64_t c0 = 0; c0 < total_max; c0 += NODES) {
+    const int span = int(max<int64_t>(0, min<int64_t>(NODES, total - c0)));
     for (int k = hl; k < span; k += H) {
       acc[k] = first ? 0.0 : spill_acc[so + c0 + k];
       flg[k] = first ? 0 : spill_flg[so + c0 + k];
@@ -1161,7 +1165,7 @@ __global__ __launch_bounds__(256) void k_rows(
                            int(magic_div(uint32_t(max(r.n[1], 1)))));
       }
       wave_lds_sync();
-      const int nk_max = int(rows_max(int64_t(nk)));
+      const int nk_max = int(rows_max<H>(int64_t(nk)));
       for (int kk = 0; kk < nk_max; ++kk) {
         int4 m0 = make_int4(0, 0, 0, 0), m1 = make_int4(0, 0, 0, 0);
         if (kk < nk) {
@@ -1169,7 +1173,7 @@ __global__ __launch_bounds__(256) void k_rows(
           m1 = M1[kk];
         }
         const int cnt = m0.w;
-        const int cnt_max = int(rows_max(int64_t(cnt)));
+        const int cnt_max = int(rows_max<H>(int64_t(cnt)));
         const int64_t kbase = int64_t((unsigned long long)(unsigned)m0.x |
                                       ((unsigned long long)(unsigned)m0.y << 32));
         const uint32_t n0 = uint32_t(m1.x) & 0xffffu, n1 = uint32_t(m1.x) >> 16;
@@ -1188,17 +1192,20 @@ __global__ __launch_bounds__(256) void k_rows(
             add = keep[ko] != 0;
             load_row<8>(pval + int64_t(m0.z) * vplane + (ko - p_base) * 8, v);
           }
-          // corner by corner: the cells of one tet are distinct, so one
-          // corner's adds go to distinct nodes
+          // eight cells after eight cells, corner by corner: the cells of one
+          // tet are distinct, so one corner's adds go to distinct nodes
+          for (int g = 0; g < H / 8 && q0 + 8 * g < cnt_max; ++g)
+            if (H == 8 || hl / 8 == g) {
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int lin = base + coff[j];
-            if (add && lin >= 0 && lin < span) {
-              __hip_atomic_fetch_add(&acc[lin], double(v[j]), __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_WAVEFRONT);
-              flg[lin] = 1;
+              for (int j = 0; j < 8; ++j) {
+                const int lin = base + coff[j];
+                if (add && lin >= 0 && lin < span) {
+                  __hip_atomic_fetch_add(&acc[lin], double(v[j]), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WAVEFRONT);
+                  flg[lin] = 1;
+                }
+              }
             }
-          }
         }
       }
     }
@@ -1208,11 +1215,11 @@ __global__ __launch_bounds__(256) void k_rows(
         spill_acc[so + c0 + k] = acc[k];
         spill_flg[so + c0 + k] = flg[k];
       }
-    const int span_max = int(rows_max(int64_t(span)));
+    const int span_max = int(rows_max<H>(int64_t(span)));
     for (int k0 = 0; k0 < span_max; k0 += H) {
       const int k = k0 + hl;
       const bool tch = last && k < span && flg[k] != 0;
-      const uint32_t m = uint32_t(ballot64(tch) >> (H * h)) & uint32_t((uint64_t(1) << H) - 1);
+      const uint64_t m = (ballot64(tch) >> (H * h)) & (~uint64_t(0) >> (kWave - H));
       if (tch) {
         // the box lies inside the lattice, whose node count fits int32
         const uint32_t lin = uint32_t(c0 + k);
@@ -1221,15 +1228,34 @@ __global__ __launch_bounds__(256) void k_rows(
         const int64_t gx = b.lo[0] + int64_t(lin - r * uint32_t(bn0));
         const int64_t gy = b.lo[1] + int64_t(r - zq * uint32_t(bn1));
         const int64_t gz = b.lo[2] + int64_t(zq);
-        const int64_t pos = outpos + __popc(m & ((1u << hl) - 1u));
+        const int64_t pos = outpos + popc64(m & ((uint64_t(1) << hl) - 1));
         tmp_col[pos] = int32_t(gx + NX * (gy + NY * gz));
         tmp_val[pos] = T(acc[k]);
       }
-      outpos += __popc(m);
+      outpos += popc64(m);
     }
     wave_lds_sync();
   }
   if (live && last && hl == 0) rownnz[w] = outpos - start;
+}
+
+// Rows a wave of k_rows serves.  The LDS of a block lets 20 waves live on a
+// CU, about 5,000 on the card: while the rows are few, or a tet's cells more
+// than a group's lanes, more lanes for each row shorten its chain of steps.
+// Microseconds with 8 / 4 / 2 / 1 rows a wave, by rows and cells per
+// (component, tet):
+//      189, 26:  248 / 126 /  68 /  61       3,240,  9:   99 /  51 /  46 /   43
+//    5,733, 19:  208 / 118 /  63 /  87       5,586, 38:  619 / 304 / 183 /  135
+//    8,064,  9:  108 /  55 /  52 /  75      15,900, 36:  760 / 350 / 266 /  288
+//   16,500, 16:  169 /  88 / 125 / 180      21,417,  5:   48 /  57 /  72 /  121
+//   28,944, 10:  243 / 172 / 172 / 249      56,025,  8:  144 / 155 / 218 /  359
+//  112,632, 10:  440 / 368 / 523 / 861     242,208, 14: 1216 / 896 / 1264 / 2129
+//  2,497,551, 6: 5.30 / 6.85 / 10.6 / 17.4 ms
+int rows_per_wave(int64_t n_rows, int64_t n_pairs, int64_t n_items) {
+  const bool wide = n_pairs > 32 * n_items;
+  if (n_rows <= 3500 || (wide && n_rows <= 6000)) return 1;
+  if (n_rows <= 10000 || (wide && n_rows <= 20000)) return 2;
+  return n_rows <= 20000 || n_pairs > 9 * n_items ? 4 : 8;
 }
 
 // Copy each row from the box-capacity scratch into the CSR arrays.
@@ -1573,7 +1599,10 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     ProfScope ps("rows_gather", s);
     const int64_t d_lo = tc_at[ch] / n_t, d_hi = (tc_at[ch + 1] - 1) / n_t;
     const int64_t w_begin = d_lo * n_v, n_rows = (d_hi - d_lo + 1) * n_v;
-    k_rows<T><<<blocks_for(ceil_div(n_rows, kRowsPerWave) * kWave, 256), 256, 0, s>>>(
+    const int rpw = rows_per_wave(n_rows, n_pairs, n_tc);
+    const auto rows = rpw == 1 ? k_rows<T, 1>
+                               : (rpw == 2 ? k_rows<T, 2> : (rpw == 4 ? k_rows<T, 4> : k_rows<T, 8>));
+    rows<<<blocks_for(ceil_div(n_rows, rpw) * kWave, 256), 256, 0, s>>>(
         n_v, n_t, ch, tc_at[ch], tc_at[ch + 1], pat[ch], chunk_max, w_begin, n_rows,
         c->vt_ptr.as<int64_t>(), c->vt_tet.as<int32_t>(), c->tets.as<int32_t>(),
         c->rng.as<CellRange>(), c->pair_off.as<int64_t>(), c->keep.as<uint8_t>(),
