@@ -853,7 +853,9 @@ __host__ __device__ inline void mom_shape(const T M[kMom], const T LA[4], const 
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int a = j & 1, b = (j >> 1) & 1, c = j >> 2;
-    Bs += Uc[j] * (W0 * M[mom_idx(a, b, c)] + WG[0] * M[mom_idx(a + 1, b, c)] +
+    // (the first two products' rounding is spelt out: which of them is fused
+    // would depend on the code around)
+    Bs += Uc[j] * (fma(W0, M[mom_idx(a, b, c)], WG[0] * M[mom_idx(a + 1, b, c)]) +
                    WG[1] * M[mom_idx(a, b + 1, c)] + WG[2] * M[mom_idx(a, b, c + 1)]);
   }
   // quadratic monomials β: 1, s_x, s_y, s_z, s_x², s_y², s_z², s_x s_y, s_x s_z, s_y s_z

@@ -98,15 +98,21 @@ __global__ __launch_bounds__(kWave) void k_shape_pairs(
 }
 
 // Pair terms from the stored piece moments (no clipping, no quadrature),
-// summed over the pieces of each (component, tet): one lane per (component,
-// tet) walks the tet's pairs in cell order, so the tet's geometry, vertex
+// summed over the pieces of each (component, tet): L lanes per (component,
+// tet) walk the tet's pairs in cell order, so the tet's geometry, vertex
 // weights and lattice are set up once per lane.  The lanes take the items
 // in the order of their pair counts (order[]), so the walks of a wave have
 // about the same length.  Sums in double to pgt[(d, t)][12] (vertex a,
 // axis k at a*3 + k).  With TWO, a second
 // contraction (solid weights z2, fluid field v, factor alpha2) is added from
 // the same moments: both adjoints' terms in one pass over the store.
-template <typename T, bool TWO>
+//
+// L > 1: each lane takes every L-th pair, the L terms of a round meet in LDS,
+// and lane k adds component k's in pair order: the same sums as one lane's.
+// Bound: with few items the chain of a lane's pairs (some 3 us each, their
+// loads one after the other), with many the moments' reading (128 bytes a
+// pair, 256 in double) and the terms' issue.  shape_lanes chooses L.
+template <typename T, bool TWO, int L>
 __global__ __launch_bounds__(256) void k_shape_tet(
     int64_t n_t, int64_t n_v, const int64_t* __restrict__ pair_off,
     const CellRange* __restrict__ rng, const uint8_t* __restrict__ keep,
@@ -115,8 +121,11 @@ __global__ __launch_bounds__(256) void k_shape_tet(
     const T* __restrict__ z, const T* u0, const T* u1, const T* u2, const T* __restrict__ z2,
     const T* v0, const T* v1, const T* v2, double alpha2, const int32_t* __restrict__ order,
     double* __restrict__ pgt, int dual) {
-  const int64_t item = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (item >= 3 * n_t) return;
+  // terms of the wave's pairs, a lane's own per row (L > 1)
+  __shared__ T sx[L > 1 ? 256 : 1][TWO ? 25 : 13];
+  const int64_t item = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / L;
+  const int g = threadIdx.x % L;
+  if (item >= 3 * n_t) return;  // all L lanes
   const int64_t w = order[item];
   const int d = int(w / n_t);
   const int64_t t = w - int64_t(d) * n_t;
@@ -141,9 +150,9 @@ __global__ __launch_bounds__(256) void k_shape_tet(
       if (dual) dual_weights<T>(zl2);
     }
     const int64_t NX = ld.n[3 * d + 0], NY = ld.n[3 * d + 1];
-    const double* L0 = lat + ld.off[3 * d + 0];
-    const double* L1 = lat + ld.off[3 * d + 1];
-    const double* L2 = lat + ld.off[3 * d + 2];
+    const double* lat0 = lat + ld.off[3 * d + 0];
+    const double* lat1 = lat + ld.off[3 * d + 1];
+    const double* lat2 = lat + ld.off[3 * d + 2];
     double rec[kTetRec];
     load_row<kTetRec>(tetrec + t * kTetRec, rec);
     TetGeom G;
@@ -151,15 +160,15 @@ __global__ __launch_bounds__(256) void k_shape_tet(
       for (int e = 0; e < 3; ++e) G.V[k][e] = rec[3 * k + e];
     tet_geom(G);
     const CellRange r = rng[w];
-    for (int64_t p = p0; p < p1; ++p) {
-      if (!keep[p]) continue;
+    // a pair's terms, to be added to acc: one(k, x) and alpha2 times two(k, x)
+    auto terms = [&](int64_t p, auto&& one, auto&& two) IBVT_INLINE {
       const uint32_t q = uint32_t(p - p0);
       const uint32_t qy = q / uint32_t(r.n[0]);
       const uint32_t qz = qy / uint32_t(r.n[1]);
       const int ci[3] = {r.lo[0] + int(q - qy * uint32_t(r.n[0])),
                          r.lo[1] + int(qy - qz * uint32_t(r.n[1])), r.lo[2] + int(qz)};
-      const double lo[3] = {L0[ci[0]], L1[ci[1]], L2[ci[2]]};
-      const double hi[3] = {L0[ci[0] + 1], L1[ci[1] + 1], L2[ci[2] + 1]};
+      const double lo[3] = {lat0[ci[0]], lat1[ci[1]], lat2[ci[2]]};
+      const double hi[3] = {lat0[ci[0] + 1], lat1[ci[1] + 1], lat2[ci[2] + 1]};
       const int64_t n000 = ci[0] + NX * (ci[1] + NY * int64_t(ci[2]));
       T ul[8];
 #pragma unroll
@@ -177,7 +186,7 @@ __global__ __launch_bounds__(256) void k_shape_tet(
       for (int k = 0; k < 3; ++k) {
         const T ih = T(1.0 / (hi[k] - lo[k]));
 #pragma unroll
-        for (int a = 0; a < 4; ++a) acc[a * 3 + k] += double(sc * ih * (A[a * 3 + k] + LG[a][k] * Bs));
+        for (int a = 0; a < 4; ++a) one(a * 3 + k, sc * ih * (A[a * 3 + k] + LG[a][k] * Bs));
       }
       if (TWO) {
         T vl[8];
@@ -190,12 +199,71 @@ __global__ __launch_bounds__(256) void k_shape_tet(
           const T ih = T(1.0 / (hi[k] - lo[k]));
 #pragma unroll
           for (int a = 0; a < 4; ++a)
-            acc[a * 3 + k] += alpha2 * double(sc * ih * (A[a * 3 + k] + LG[a][k] * Bs));
+            two(a * 3 + k, sc * ih * (A[a * 3 + k] + LG[a][k] * Bs));
+        }
+      }
+    };
+    if constexpr (L == 1) {
+      for (int64_t p = p0; p < p1; ++p) {
+        if (!keep[p]) continue;
+        terms(
+            p, [&](int k, T x) IBVT_INLINE { acc[k] += double(x); },
+            [&](int k, T x) IBVT_INLINE { acc[k] += alpha2 * double(x); });
+      }
+    } else {
+      T* mine = sx[threadIdx.x];
+      const T* rows = sx[threadIdx.x - g];
+      for (int64_t q0 = p0; q0 < p1; q0 += L) {
+        const int64_t p = q0 + g;
+        wave_lds_sync();
+        if (p < p1 && keep[p]) {
+          terms(
+              p, [&](int k, T x) IBVT_INLINE { mine[k] = x; },
+              [&](int k, T x) IBVT_INLINE { mine[12 + k] = x; });
+        } else {
+#pragma unroll
+          for (int k = 0; k < (TWO ? 24 : 12); ++k) mine[k] = T(0);
+        }
+        wave_lds_sync();
+        // component k's terms in pair order (those of pairs left out are 0)
+        constexpr int stride = TWO ? 25 : 13;
+#pragma unroll
+        for (int j = 0; j < (12 + L - 1) / L; ++j) {
+          const int k = g + j * L;
+          if (k < 12)
+#pragma unroll
+            for (int l = 0; l < L; ++l) {
+              acc[j] += double(rows[l * stride + k]);
+              if (TWO) acc[j] += alpha2 * double(rows[l * stride + 12 + k]);
+            }
         }
       }
     }
   }
-  store_row<12>(pgt + w * 12, acc);
+  if constexpr (L == 1) {
+    store_row<12>(pgt + w * 12, acc);
+  } else {
+#pragma unroll
+    for (int j = 0; j < (12 + L - 1) / L; ++j)
+      if (g + j * L < 12) pgt[w * 12 + g + j * L] = acc[j];
+  }
+}
+
+// Lanes for each (component, tet) in k_shape_tet: more while the items are few.
+// Microseconds with 1 / 4 / 8 / 16, by items and pairs per item (float):
+//      432, 26:   95 /  31 /  20 /  18       3,402,  5:   27 /  12 /   9 /   9
+//   13,050,  6:   27 /  13 /  12 /  18      12,150, 13:   73 /  26 /  22 /  19
+//   24,624, 19:   76 /  33 /  35 /  38      23,976, 38:  192 /  68 /  56 /  54
+//   36,162,  5:   28 /  21 /  22 /  33     104,400,  5:   39 /  37 /  48 /  85
+//  289,296,  5:   81 /  94 / 133 / 243     289,296,  8:  128 / 122 / 150 / 247
+//  1,190,250, 14: 641 / 727 / 974 / 1233    13,510,206, 6: 3.70 / 4.56 / 6.52 / 11.6 ms
+// and in double 143,748, 10: 230 / 161 / 191 / 253.
+int shape_lanes(int64_t items, int64_t pairs) {
+  if (items <= 4000 || (items <= 16000 && pairs > 12 * items) ||
+      (items <= 30000 && pairs > 24 * items))
+    return 16;
+  if (items <= 30000) return 8;
+  return items <= 150000 || (items <= 300000 && pairs > 8 * items) ? 4 : 1;
 }
 
 // Sort key of (component, tet) w: its pair count, clamped to 255.
@@ -339,24 +407,31 @@ int shape_typed(ibvt_coupling* c, const void* z, const void* const u[3], const v
   }
   if (c->mom_valid) {
     ProfScope ps("shape_moments", s);
-    const unsigned nb = unsigned(ceil_div(3 * c->n_tet, 256));
     const T* zz = static_cast<const T*>(z);
-    const T* u0 = static_cast<const T*>(u[0]);
-    const T* u1 = static_cast<const T*>(u[1]);
-    const T* u2 = static_cast<const T*>(u[2]);
-    if (c->n_tet > 0 && z2)
-      k_shape_tet<T, true><<<nb, 256, 0, s>>>(
-          c->n_tet, c->n_vert, c->pair_off.as<int64_t>(), c->rng.as<CellRange>(),
-          c->keep.as<uint8_t>(), c->pmom.as<T>(), c->tetrec.as<double>(), c->lat.as<double>(),
-          c->tets.as<int32_t>(), c->ld, zz, u0, u1, u2, static_cast<const T*>(z2),
-          static_cast<const T*>(v[0]), static_cast<const T*>(v[1]), static_cast<const T*>(v[2]),
-          alpha2 / alpha, c->tcorder.as<int32_t>(), pgt, c->dual ? 1 : 0);
-    else if (c->n_tet > 0)
-      k_shape_tet<T, false><<<nb, 256, 0, s>>>(
-          c->n_tet, c->n_vert, c->pair_off.as<int64_t>(), c->rng.as<CellRange>(),
-          c->keep.as<uint8_t>(), c->pmom.as<T>(), c->tetrec.as<double>(), c->lat.as<double>(),
-          c->tets.as<int32_t>(), c->ld, zz, u0, u1, u2, nullptr, nullptr, nullptr, nullptr, 0.0,
-          c->tcorder.as<int32_t>(), pgt, c->dual ? 1 : 0);
+    const T* const* uf = reinterpret_cast<const T* const*>(u);
+    const T* const none[3] = {nullptr, nullptr, nullptr};
+    const T* const* vf = z2 ? reinterpret_cast<const T* const*>(v) : none;
+    auto launch = [&](auto two, auto lanes) {
+      constexpr int L = decltype(lanes)::value;
+      k_shape_tet<T, decltype(two)::value, L>
+          <<<unsigned(ceil_div(3 * c->n_tet * L, 256)), 256, 0, s>>>(
+              c->n_tet, c->n_vert, c->pair_off.as<int64_t>(), c->rng.as<CellRange>(),
+              c->keep.as<uint8_t>(), c->pmom.as<T>(), c->tetrec.as<double>(), c->lat.as<double>(),
+              c->tets.as<int32_t>(), c->ld, zz, uf[0], uf[1], uf[2], static_cast<const T*>(z2),
+              vf[0], vf[1], vf[2], z2 ? alpha2 / alpha : 0.0, c->tcorder.as<int32_t>(), pgt,
+              c->dual ? 1 : 0);
+    };
+    auto lanes = [&](auto two) {
+      const int g = shape_lanes(3 * c->n_tet, c->n_pairs);
+      if (g == 16) launch(two, std::integral_constant<int, 16>{});
+      else if (g == 8) launch(two, std::integral_constant<int, 8>{});
+      else if (g == 4) launch(two, std::integral_constant<int, 4>{});
+      else launch(two, std::integral_constant<int, 1>{});
+    };
+    if (c->n_tet > 0) {
+      if (z2) lanes(std::true_type{});
+      else lanes(std::false_type{});
+    }
   } else {
     const int64_t nb = std::min<int64_t>(ceil_div(c->n_pairs, kWave), int64_t(1) << 22);
     ClipTables tab;
