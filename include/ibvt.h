@@ -431,6 +431,8 @@ int coupling_info(const ibvt_coupling* c, ibvt_info* info);
  *   moments, per-tet data).  For callers that hold couplings between
  *   reassemblies; the next reassembly allocates the scratch again.  Other
  *   couplings: nothing is released.  Stream-ordered on `stream`.
+ *   Also gives back what freed couplings left for the next ones on this GPU
+ *   (coupling_free).
  *   Errors: IBVT_E_INVALID (NULL handle).
  */
 int coupling_release_scratch(ibvt_coupling* c, hipStream_t stream);
@@ -475,7 +477,9 @@ int coupling_export_csr(const ibvt_coupling* c, int comp, int transposed, int64_
                         int32_t* row_map);
 
 /* coupling_free — release the handle and its device memory (synchronizes
- * the device).  NULL is a no-op. */
+ * the device).  NULL is a no-op.  Up to 1 GiB of the memory (none of a
+ * caller's allocator's) stays with the library for the couplings made next
+ * on the GPU, until coupling_release_scratch or an allocation needs it. */
 void coupling_free(ibvt_coupling* c);
 
 /* ibvt_status_string — static text for a status code. */

@@ -66,6 +66,87 @@ namespace {
 std::mutex g_alloc_mu;
 ibvt_alloc g_alloc{};  // allocator of new handles (null members: hipMallocAsync)
 
+// What the freed handles of one GPU leave for the next ones, so that a
+// coupling made for one call (the autograd form without a kept coupling) costs
+// no driver work: device buffers, oldest first and kShelfBytes at most, and a
+// few second streams with their events and pinned read-back blocks.  On
+// 47,916 tets the driver took 8 ms of such a call's 10.6 for them (HIP's own
+// pools give their memory back to the driver when nothing of them is in use).
+// Only coupling_free puts things here, after it has waited for the device, so
+// a taker may use them on any stream; everything is under the mutex.
+// coupling_release_scratch gives all of it back, and so does an allocation
+// that fails.
+constexpr int kMaxDevices = 64;
+constexpr size_t kShelfBytes = size_t(1) << 30;
+constexpr size_t kShelfMost = 4;
+struct Shelf {
+  std::mutex mu;
+  std::vector<DevBuf> bufs;
+  size_t bytes = 0;
+  std::vector<SideStream> side;
+  std::vector<int64_t*> rb;
+};
+
+Shelf* shelf_at(int dev) {
+  static Shelf* const shelves = new Shelf[kMaxDevices];  // (never destroyed: handles may outlive it)
+  return dev >= 0 && dev < kMaxDevices ? &shelves[dev] : nullptr;
+}
+
+int current_device() {
+  int dev = -1;
+  return hipGetDevice(&dev) == hipSuccess ? dev : -1;
+}
+
+// The shelf of the handle's GPU; none when the call's stream is another
+// GPU's than the current one, or the memory comes from the caller.
+Shelf* shelf_of(ibvt_coupling* c) {
+  if (c->alloc.alloc) return nullptr;
+  if (c->device == -1) {
+    hipDevice_t sd = -1;
+    c->device = current_device();
+    if (c->stream && (hipStreamGetDevice(c->stream, &sd) != hipSuccess || int(sd) != c->device))
+      c->device = -2;
+  }
+  return shelf_at(c->device);
+}
+
+// The smallest kept buffer of bytes to 9/8 bytes + 64 KiB.
+bool take_buffer(Shelf* h, DevBuf& b, size_t bytes) {
+  if (!h) return false;
+  std::lock_guard<std::mutex> g(h->mu);
+  size_t best = h->bufs.size();
+  for (size_t k = 0; k < h->bufs.size(); ++k)
+    if (h->bufs[k].cap >= bytes && h->bufs[k].cap - bytes <= bytes / 8 + (size_t(64) << 10) &&
+        (best == h->bufs.size() || h->bufs[k].cap < h->bufs[best].cap))
+      best = k;
+  if (best == h->bufs.size()) return false;
+  b = h->bufs[best];
+  h->bytes -= b.cap;
+  h->bufs.erase(h->bufs.begin() + int64_t(best));
+  return true;
+}
+
+// An idle buffer onto the shelf; the oldest ones leave it for the driver.
+void put_buffer(Shelf* h, DevBuf& b) {
+  std::lock_guard<std::mutex> g(h->mu);
+  size_t out = 0;
+  for (; out < h->bufs.size() && h->bytes + b.cap > kShelfBytes; ++out) {
+    h->bytes -= h->bufs[out].cap;
+    (void)hipFreeAsync(h->bufs[out].p, nullptr);
+  }
+  h->bufs.erase(h->bufs.begin(), h->bufs.begin() + int64_t(out));
+  h->bufs.push_back(b);
+  h->bytes += b.cap;
+}
+
+void drop_buffers(Shelf* h) {
+  if (!h) return;
+  std::lock_guard<std::mutex> g(h->mu);
+  for (DevBuf& b : h->bufs) (void)hipFreeAsync(b.p, nullptr);
+  h->bufs.clear();
+  h->bytes = 0;
+}
+
 // Stream-ordered release of one buffer through the handle's allocator.
 hipError_t free_buffer(ibvt_coupling* c, void* p) {
   if (c->alloc.free) {
@@ -100,7 +181,18 @@ int ensure(ibvt_coupling* c, DevBuf& b, size_t bytes) {
     b.p = c->alloc.alloc(want, c->stream, c->alloc.ctx);
     if (!b.p) return set_error(IBVT_E_NOMEM, "the coupling's allocator returned NULL");
   } else {
+    Shelf* h = shelf_of(c);
+    if (take_buffer(h, b, want)) {
+      c->device_bytes += int64_t(b.cap);
+      return IBVT_OK;
+    }
     hipError_t e = hipMallocAsync(&b.p, want, c->stream);
+    if (e == hipErrorOutOfMemory && h) {  // what is kept may be in the way
+      (void)hipGetLastError();
+      drop_buffers(h);
+      (void)hipStreamSynchronize(nullptr);
+      e = hipMallocAsync(&b.p, want, c->stream);
+    }
     if (e != hipSuccess) {
       b.p = nullptr;
       (void)hipGetLastError();
@@ -114,12 +206,102 @@ int ensure(ibvt_coupling* c, DevBuf& b, size_t bytes) {
 
 void release(ibvt_coupling* c, DevBuf& b) {
   if (b.p) {
-    (void)free_buffer(c, b.p);
+    Shelf* h = c->idle && b.cap <= kShelfBytes ? shelf_of(c) : nullptr;
+    if (h) put_buffer(h, b);
+    else (void)free_buffer(c, b.p);
     c->device_bytes -= int64_t(b.cap);
   }
   b.p = nullptr;
   b.cap = 0;
 }
+
+namespace {
+void destroy_side(SideStream& x) {
+  for (hipEvent_t e : {x.fork, x.join, x.sorted})
+    if (e) (void)hipEventDestroy(e);
+  if (x.stream) (void)hipStreamDestroy(x.stream);
+  x = SideStream{};
+}
+}  // namespace
+
+int host_block(ibvt_coupling* c) {
+  if (c->host_rb) return IBVT_OK;
+  if (Shelf* h = shelf_of(c)) {
+    std::lock_guard<std::mutex> g(h->mu);
+    if (!h->rb.empty()) {
+      c->host_rb = h->rb.back();
+      h->rb.pop_back();
+    }
+  }
+  void* p = nullptr;
+  int st = IBVT_OK;
+  if (!c->host_rb) {
+    st = hip_check(hipHostMalloc(&p, kHostBlock * sizeof(int64_t), hipHostMallocDefault),
+                   "hipHostMalloc");
+    if (st) return st;
+    c->host_rb = static_cast<int64_t*>(p);
+  }
+  st = hip_check(hipHostGetDevicePointer(&p, c->host_rb, 0), "hipHostGetDevicePointer");
+  if (st) {
+    (void)hipHostFree(c->host_rb);
+    c->host_rb = nullptr;
+    return st;
+  }
+  c->host_rb_dev = static_cast<int64_t*>(p);
+  return IBVT_OK;
+}
+
+int side_stream(ibvt_coupling* c) {
+  if (c->side.stream) return IBVT_OK;
+  if (Shelf* h = shelf_of(c)) {
+    std::lock_guard<std::mutex> g(h->mu);
+    if (!h->side.empty()) {
+      c->side = h->side.back();
+      h->side.pop_back();
+      return IBVT_OK;
+    }
+  }
+  SideStream y;
+  int st = hip_check(hipStreamCreateWithFlags(&y.stream, hipStreamNonBlocking), "stream");
+  for (hipEvent_t* e : {&y.fork, &y.join, &y.sorted})
+    if (!st) st = hip_check(hipEventCreateWithFlags(e, hipEventDisableTiming), "event");
+  if (st) destroy_side(y);
+  else c->side = y;
+  return st;
+}
+
+namespace {
+// The finished handle's stream and block to its shelf, or destroyed when that
+// has enough.
+void shelve(ibvt_coupling* c) {
+  if (Shelf* h = shelf_of(c)) {
+    std::lock_guard<std::mutex> g(h->mu);
+    if (c->side.stream && h->side.size() < kShelfMost) {
+      h->side.push_back(c->side);
+      c->side = SideStream{};
+    }
+    if (c->host_rb && h->rb.size() < kShelfMost) {
+      h->rb.push_back(c->host_rb);
+      c->host_rb = nullptr;
+    }
+  }
+  destroy_side(c->side);
+  if (c->host_rb) (void)hipHostFree(c->host_rb);
+  c->host_rb = nullptr;
+}
+
+// Everything the handle's shelf holds, given back.
+void clear_shelf(ibvt_coupling* c) {
+  Shelf* h = shelf_of(c);
+  if (!h) return;
+  drop_buffers(h);
+  std::lock_guard<std::mutex> g(h->mu);
+  for (SideStream& x : h->side) destroy_side(x);
+  for (int64_t* p : h->rb) (void)hipHostFree(p);
+  h->side.clear();
+  h->rb.clear();
+}
+}  // namespace
 
 namespace {
 
@@ -192,13 +374,9 @@ void release_all(ibvt_coupling* c) {
                     &c->rowtmpcol, &c->rowtmpval, &c->tetgrad, &c->mcoef,
                     &c->fsiX,     &c->fsinorm,   &c->fvol,      &c->fX,        &c->ftets,
                     &c->frec,     &c->fbox,      &c->forder,    &c->ftree,     &c->ucoo,
-                    &c->rb,       &c->bodyinfo,  &c->tcorder,   &c->rowspilloff,
+                    &c->bodyinfo,  &c->tcorder,   &c->rowspilloff,
                     &c->rowspill};
   for (DevBuf* b : bufs) release(c, *b);
-  if (c->host_rb) {
-    (void)hipHostFree(c->host_rb);
-    c->host_rb = nullptr;
-  }
   // an unstructured coupling's components share B[0] and Bt[0]
   const int own = c->unstructured ? 1 : 3;
   for (int d = 0; d < own; ++d) {
@@ -207,6 +385,15 @@ void release_all(ibvt_coupling* c) {
   }
   for (int d = own; d < 3; ++d) c->B[d] = c->Bt[d] = Csr{};
   release_csr(c, c->M);
+}
+
+// A handle whose creation failed.
+void discard(ibvt_coupling* c, hipStream_t s) {
+  (void)hipStreamSynchronize(s);
+  if (c->side.stream) (void)hipStreamSynchronize(c->side.stream);
+  release_all(c);
+  shelve(c);
+  delete c;
 }
 
 int validate_grid(const ibvt_grid* g) {
@@ -357,9 +544,7 @@ int finish_assembly(ibvt_coupling* c, const double* X, const int32_t* elems, hip
   if (!st) st = assemble_all(c, stream);
   if (st) {
     std::string keep_msg = g_last_error;
-    (void)hipStreamSynchronize(stream);
-    release_all(c);
-    delete c;
+    discard(c, stream);
     g_last_error = keep_msg;
     return st;
   }
@@ -509,8 +694,7 @@ int assemble_coupling(const ibvt_grid* grid, const ibvt_mesh* mesh, int precisio
   for (int e = 0; e < 3; ++e) c->n_cells[e] = grid->n_cells[e];
   st = setup_lattices(c, grid, stream);
   if (st) {
-    release_all(c);
-    delete c;
+    discard(c, stream);
     return st;
   }
   return finish_assembly(c, mesh->X, mesh->tets, stream, out);
@@ -565,9 +749,7 @@ int assemble_coupling_unstructured(const ibvt_mesh* fluid, const ibvt_mesh* mesh
                    "copy fluid tets");
   if (st) {
     std::string keep_msg = g_last_error;
-    (void)hipStreamSynchronize(stream);
-    release_all(c);
-    delete c;
+    discard(c, stream);
     g_last_error = keep_msg;
     return st;
   }
@@ -610,8 +792,7 @@ int assemble_coupling_2d(const ibvt_grid2d* grid, const ibvt_mesh2d* mesh, int p
   c->n_cells[2] = 0;
   st = setup_lattices2d(c, grid, stream);
   if (st) {
-    release_all(c);
-    delete c;
+    discard(c, stream);
     return st;
   }
   return finish_assembly(c, mesh->X, mesh->tris, stream, out);
@@ -864,6 +1045,7 @@ int coupling_release_scratch(ibvt_coupling* c, hipStream_t stream) {
     release(c, c->order);
   }
   c->pool_cap = 0;
+  clear_shelf(c);
   return IBVT_OK;
 }
 
@@ -924,13 +1106,12 @@ int ibvt_set_allocator(const ibvt_alloc* a) {
 
 void coupling_free(ibvt_coupling* c) {
   if (!c) return;
-  (void)hipDeviceSynchronize();
+  // what the handle leaves on the shelf is idle
+  c->idle = hipDeviceSynchronize() == hipSuccess && current_device() == c->device;
   c->stream = nullptr;  // the caller's streams may be gone: free on the null stream
   release_all(c);
   (void)hipStreamSynchronize(nullptr);
-  for (hipEvent_t e : {c->ev_fork, c->ev_join, c->ev_sorted})
-    if (e) (void)hipEventDestroy(e);
-  if (c->side) (void)hipStreamDestroy(c->side);
+  shelve(c);
   delete c;
 }
 

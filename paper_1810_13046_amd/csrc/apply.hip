@@ -340,28 +340,25 @@ inline unsigned nblk_rows(int64_t n) {
 // place), plus double x/res for the residuals and the refinement.
 struct MassWork {
   double* part;
-  double* tmp;
   void* vec;
   double* x64;
   double* res64;
 };
 
 // Layout of the mass-solve workspace for n vertices and value size tsize:
-// residual partials, reduction results, six (3, n) vectors of T, the double
+// residual partials, six (3, n) vectors of T, the double
 // solution and residual.  Returns the bytes it spans; with base non-null
 // also sets w's pointers into [base, base + bytes).
 size_t mass_workspace_layout(int64_t n, size_t tsize, char* base, MassWork* w) {
   // per-block partials of the residual kernel fit
   const int64_t nb = std::max<int64_t>(nblk(n), nblk_rows(n));
   const size_t off_part = 256;
-  const size_t off_tmp = off_part + size_t(nb) * 6 * sizeof(double);
-  const size_t off_vec = (off_tmp + 16 * sizeof(double) + 255) & ~size_t(255);
+  const size_t off_vec = (off_part + size_t(nb) * 6 * sizeof(double) + 255) & ~size_t(255);
   const size_t off_x64 = (off_vec + size_t(6 * 3 * n) * tsize + 255) & ~size_t(255);
   const size_t off_res = (off_x64 + size_t(3 * n) * sizeof(double) + 255) & ~size_t(255);
   const size_t total = off_res + size_t(3 * n) * sizeof(double) + 256;
   if (base && w) {
     w->part = reinterpret_cast<double*>(base + off_part);
-    w->tmp = reinterpret_cast<double*>(base + off_tmp);
     w->vec = base + off_vec;
     w->x64 = reinterpret_cast<double*>(base + off_x64);
     w->res64 = reinterpret_cast<double*>(base + off_res);
@@ -462,11 +459,14 @@ int true_residual(ibvt_coupling* c, const T* b, const double* x, const MassWork&
   k_residual64<T><<<nb, kThreads, 0, s>>>(c->ncomp, n, c->M.rowptr.as<int64_t>(),
                                           c->M.col.as<int32_t>(),
                                           c->M.val.as<double>(), b, x, w.res64, w.part);
-  k_reduce6<<<1, kThreads, 0, s>>>(w.part, nb, w.tmp);
-  double h[6];
-  int st = hip_check(hipMemcpyAsync(h, w.tmp, sizeof(h), hipMemcpyDeviceToHost, s), "res read");
+  // straight to the host: a copy would be one more launch to wait for
+  int st = host_block(c);
   if (st) return st;
+  k_reduce6<<<1, kThreads, 0, s>>>(w.part, nb,
+                                   reinterpret_cast<double*>(c->host_rb_dev + kHostResidual));
+  if ((st = hip_check(hipGetLastError(), "residual launch"))) return st;
   if ((st = hip_check(hipStreamSynchronize(s), "res sync"))) return st;
+  const double* h = reinterpret_cast<const double*>(c->host_rb + kHostResidual);
   for (int d = 0; d < 3; ++d) rel[d] = (h[3 + d] > 0) ? std::sqrt(h[d] / h[3 + d]) : 0.0;
   return IBVT_OK;
 }

@@ -1395,7 +1395,6 @@ int check_flags(ibvt_coupling* c, hipStream_t s) {
 }
 
 namespace {
-constexpr int kMaxCounts = 24;
 struct CountSrc {
   const int64_t* p[kMaxCounts];
 };
@@ -1409,23 +1408,13 @@ __global__ void k_gather_counts(CountSrc src, int n, const unsigned* __restrict_
 
 int read_counts(ibvt_coupling* c, const int64_t* const* srcs, int n, int64_t* out, hipStream_t s) {
   if (n < 0 || n > kMaxCounts) return set_error(IBVT_E_INVALID, "read_counts: too many values");
-  int st = ensure(c, c->rb, (kMaxCounts + 1) * sizeof(int64_t));
+  int st = host_block(c);
   if (st) return st;
-  if (!c->host_rb) {
-    void* h = nullptr;
-    if ((st = hip_check(hipHostMalloc(&h, (kMaxCounts + 1) * sizeof(int64_t), hipHostMallocDefault),
-                        "hipHostMalloc")))
-      return st;
-    c->host_rb = static_cast<int64_t*>(h);
-  }
   CountSrc src{};
   for (int k = 0; k < n; ++k) src.p[k] = srcs[k];
-  k_gather_counts<<<1, 64, 0, s>>>(src, n, c->flags_dev.as<unsigned>(), c->rb.as<int64_t>());
+  // straight to the host: a copy would be one more launch to wait for
+  k_gather_counts<<<1, 64, 0, s>>>(src, n, c->flags_dev.as<unsigned>(), c->host_rb_dev);
   if ((st = hip_check(hipGetLastError(), "count gather launch"))) return st;
-  if ((st = hip_check(hipMemcpyAsync(c->host_rb, c->rb.p, (kMaxCounts + 1) * sizeof(int64_t),
-                                     hipMemcpyDeviceToHost, s),
-                      "read back")))
-    return st;
   if ((st = hip_check(hipStreamSynchronize(s), "stream sync"))) return st;
   for (int k = 0; k < n; ++k) out[k] = c->host_rb[k];
   c->host_flags = unsigned(c->host_rb[kMaxCounts]);
@@ -1445,19 +1434,6 @@ int64_t chunk_items() {
     if (end != e && *end == '\0' && v > 0) return int64_t(v);
   }
   return int64_t(3) << 19;
-}
-
-// The assembly's second stream and its events, made on first use (default
-// priority, no timing) and destroyed with the handle.
-int side_stream(ibvt_coupling* c) {
-  int st;
-  if (!c->side &&
-      (st = hip_check(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking), "stream")))
-    return st;
-  for (hipEvent_t* e : {&c->ev_fork, &c->ev_join, &c->ev_sorted})
-    if (!*e && (st = hip_check(hipEventCreateWithFlags(e, hipEventDisableTiming), "event")))
-      return st;
-  return IBVT_OK;
 }
 
 // Without stored matrices (IBVT_NO_STORE_B): after the overlap candidates,
@@ -1626,7 +1602,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
   auto fork_masses = [&]() -> int {
     if (masses_done) return IBVT_OK;
     masses_done = true;
-    return solid_masses(c, c->side);
+    return solid_masses(c, c->side.stream);
   };
   if constexpr (sizeof(T) == sizeof(double)) if (octants && n_pairs > 0) {
     // (II)-(III) every piece from its boundary integrals
@@ -1638,10 +1614,10 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
       if (nc == 0) continue;
       const bool fork = !masses_done;
       if (fork) {
-        if ((st = hip_check(hipEventRecord(c->ev_fork, s), "event")) ||
-            (st = hip_check(hipStreamWaitEvent(c->side, c->ev_fork, 0), "stream wait")) ||
+        if ((st = hip_check(hipEventRecord(c->side.fork, s), "event")) ||
+            (st = hip_check(hipStreamWaitEvent(c->side.stream, c->side.fork, 0), "stream wait")) ||
             (st = fork_masses()) ||
-            (st = hip_check(hipEventRecord(c->ev_join, c->side), "event")))
+            (st = hip_check(hipEventRecord(c->side.join, c->side.stream), "event")))
           return st;
       }
       {
@@ -1658,7 +1634,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
             c->keep.as<uint8_t>(), c->pval.as<T>(), c->pmom.as<T>(), c->dual ? 1 : 0, counters);
       }
       if ((st = hip_check(hipGetLastError(), "pieces launch"))) return st;
-      if (fork && (st = hip_check(hipStreamWaitEvent(s, c->ev_join, 0), "stream wait"))) return st;
+      if (fork && (st = hip_check(hipStreamWaitEvent(s, c->side.join, 0), "stream wait"))) return st;
       if ((st = gather_rows(ch))) return st;
     }
   }
@@ -1731,14 +1707,14 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
         // slots per lane, more resident waves); each launch reads its
         // class's stretch of the order from the prefix sum of the key counts
         ProfScope ps("clip", s);
-        if ((st = hip_check(hipEventRecord(c->ev_fork, s), "event")) ||
-            (st = hip_check(hipStreamWaitEvent(c->side, c->ev_fork, 0), "stream wait")))
+        if ((st = hip_check(hipEventRecord(c->side.fork, s), "event")) ||
+            (st = hip_check(hipStreamWaitEvent(c->side.stream, c->side.fork, 0), "stream wait")))
           return st;
         if ((st = fork_masses())) return st;
         ClipTables tab;
         if ((st = clip_tables(tab))) return st;
         for (int k = 2; k >= 0; --k) {
-          hipStream_t ks = k == 0 ? s : c->side;
+          hipStream_t ks = k == 0 ? s : c->side.stream;
           const int resident =
               k == 0 ? resident_blocks(k_clip<T, 10>)
                      : (k == 1 ? resident_blocks(k_clip<T, 12>) : resident_blocks(k_clip<T, kMaxV>));
@@ -1753,16 +1729,16 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
 #undef IBVT_CLIP_ARGS
         }
         if ((st = hip_check(hipGetLastError(), "clip launch"))) return st;
-        if ((st = hip_check(hipEventRecord(c->ev_join, c->side), "event")) ||
-            (st = hip_check(hipStreamWaitEvent(s, c->ev_join, 0), "stream wait")))
+        if ((st = hip_check(hipEventRecord(c->side.join, c->side.stream), "event")) ||
+            (st = hip_check(hipStreamWaitEvent(s, c->side.join, 0), "stream wait")))
           return st;
       }
       const bool next = li + 1 < n_live;
       if (next) {
-        if ((st = hip_check(hipEventRecord(c->ev_fork, s), "event")) ||
-            (st = hip_check(hipStreamWaitEvent(c->side, c->ev_fork, 0), "stream wait")) ||
-            (st = order_chunk(live[li + 1], c->side)) ||
-            (st = hip_check(hipEventRecord(c->ev_sorted, c->side), "event")))
+        if ((st = hip_check(hipEventRecord(c->side.fork, s), "event")) ||
+            (st = hip_check(hipStreamWaitEvent(c->side.stream, c->side.fork, 0), "stream wait")) ||
+            (st = order_chunk(live[li + 1], c->side.stream)) ||
+            (st = hip_check(hipEventRecord(c->side.sorted, c->side.stream), "event")))
           return st;
       }
       {
@@ -1777,7 +1753,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
       }
       if ((st = hip_check(hipGetLastError(), "integrate launch"))) return st;
       if ((st = gather_rows(ch))) return st;
-      if (next && (st = hip_check(hipStreamWaitEvent(s, c->ev_sorted, 0), "stream wait")))
+      if (next && (st = hip_check(hipStreamWaitEvent(s, c->side.sorted, 0), "stream wait")))
         return st;
     }
 

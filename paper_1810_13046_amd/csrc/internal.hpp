@@ -116,13 +116,20 @@ struct AsmStats {
   int64_t assemblies = 0;
 };
 
+// A second stream (default priority) and its joins.
+struct SideStream {
+  hipStream_t stream = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr, sorted = nullptr;
+};
+
 }  // namespace ibvt
 
 struct ibvt_coupling {
   hipStream_t stream = nullptr;  // stream of the current call: buffers grow and shrink on it
   ibvt_alloc alloc{};            // allocator of the handle's buffers (null: hipMallocAsync)
-  hipStream_t side = nullptr;    // the assembly's second stream (default priority), and
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_sorted = nullptr;  // its joins
+  ibvt::SideStream side;     // the assembly's second stream, made on first use
+  int device = -1;           // the handle's GPU (-1: not known yet, -2: none to go by)
+  bool idle = false;         // being freed, after a wait for its GPU
   int precision = IBVT_FP64;
   uint32_t flags = 0;
   int dim = 3;    // 3: tetrahedra in a 3D grid; 2: triangles in a planar grid
@@ -200,8 +207,8 @@ struct ibvt_coupling {
   ibvt::DevBuf work;         // transfer scratch (mass-solve vectors etc.)
   ibvt::DevBuf work2;        // shape-gradient per-pair scratch / mass-solve right-hand side
   ibvt::DevBuf zbuf;         // solid-sized scratch of the reverse-mode calls
-  int64_t* host_rb = nullptr;  // pinned host block of the packed read-backs (hipHostMalloc)
-  ibvt::DevBuf rb;           // device block gathered for one read-back
+  int64_t* host_rb = nullptr;  // pinned host block (kHostBlock) that kernels write counts and
+  int64_t* host_rb_dev = nullptr;  // residuals to, at this address on the device
   ibvt::DevBuf bodyinfo;     // coupling_body_info: offsets and per-body sums
   unsigned host_flags = 0;   // status flags of the last packed read-back
   ibvt::AsmStats stats;
@@ -223,6 +230,12 @@ int set_error(int status, const std::string& msg);
 int hip_check(hipError_t e, const char* what);
 int ensure(ibvt_coupling* c, DevBuf& b, size_t bytes);
 void release(ibvt_coupling* c, DevBuf& b);
+// the handle's second stream and its host block (first use)
+int side_stream(ibvt_coupling* c);
+int host_block(ibvt_coupling* c);
+constexpr int kMaxCounts = 24;               // read_counts: values, then the flags
+constexpr int kHostResidual = kMaxCounts + 2;  // six doubles of a mass solve's residual
+constexpr int kHostBlock = 64;
 
 // scan.hip: exclusive prefix sum; out has n+1 entries, out[n] = total.
 int scan_i64(ibvt_coupling* c, const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
