@@ -107,14 +107,15 @@ int launch_spmv_g(const SpmvArgs<T>& a, int nc, hipStream_t s, const char* name)
 
 // Rows averaging fewer than 56 entries (B: a vertex's fluid nodes) take 8
 // lanes with 8 entries each per round; longer rows (B^T: a fluid node's
-// vertices) 16 lanes with 4 (the faster of the shapes measured on MI355X
-// for each).
+// vertices) 16 lanes with 8 (the faster of the shapes measured on MI355X
+// for each: B^T of 4.5M tets, rows of 75, 237 us with 4 entries a round and
+// 220 with 8).
 template <typename T>
 int launch_spmv(const SpmvArgs<T>& a, int nc, int64_t nnz, hipStream_t s, const char* name) {
   int64_t rows = 0;
   for (int d = 0; d < nc; ++d) rows += a.nrows[d];
   if (nnz < 56 * rows) return launch_spmv_g<T, 8, 8>(a, nc, s, name);
-  return launch_spmv_g<T, 16, 4>(a, nc, s, name);
+  return launch_spmv_g<T, 16, 8>(a, nc, s, name);
 }
 
 // ---------------------------------------------------------------------------
@@ -254,6 +255,117 @@ __global__ __launch_bounds__(kThreads) void k_cheb(int64_t n, const int64_t* __r
   }
 }
 
+
+// A whole cycle for few vertices in one block: k_mass_spmv (unless x starts
+// from zero), k_cheb_start and `iters` times k_cheb with every vector in LDS
+// and a lane's first entries of its rows in registers, in the same order and
+// arithmetic, the scalars' recurrence included.
+//
+// Bound: latency of an iteration's LDS reads and its barrier; a launch for
+// each costs 4 us.  63 vertices, two solves of 27 iterations: 389 us with a
+// launch each, 70 so.
+constexpr int kBlockSolve = 512;  // vertices: two rows for every kMG of 1,024 threads
+template <typename T, typename V, int NC>
+__global__ __launch_bounds__(1024) void k_cheb_block(
+    int n, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+    const V* __restrict__ val, const double* __restrict__ dinv, const T* __restrict__ b,
+    T* __restrict__ x, int x_zero, int iters, double theta, double delta, double sigma1) {
+  constexpr int R = kBlockSolve * kMG / 1024, E = 6;
+  __shared__ T sx[NC * kBlockSolve], sr[NC * kBlockSolve], sd0[NC * kBlockSolve],
+      sd1[NC * kBlockSolve];
+  const int g = threadIdx.x % kMG, r0 = threadIdx.x / kMG;
+  int64_t kb[R], ke[R];
+  int c[R][E];
+  T v[R][E];
+  double di[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int i = r0 + q * (1024 / kMG);
+    kb[q] = i < n ? rp[i] + g : 0;
+    ke[q] = i < n ? rp[i + 1] : 0;
+    di[q] = i < n ? dinv[i] : 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int64_t k = kb[q] + e * kMG;
+      c[q][e] = k < ke[q] ? col[k] : 0;
+      v[q][e] = k < ke[q] ? T(val[k]) : T(0);
+    }
+  }
+  for (int k = threadIdx.x; k < NC * n; k += 1024) sx[k] = x_zero ? T(0) : x[k];
+  __syncthreads();
+  // row of round q times the vectors at p, summed over the row's lanes
+  auto product = [&](int q, const T* p, T (&s)[NC]) {
+#pragma unroll
+    for (int m = 0; m < NC; ++m) s[m] = T(0);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (kb[q] + e * kMG < ke[q])
+#pragma unroll
+        for (int m = 0; m < NC; ++m) s[m] += v[q][e] * p[m * n + c[q][e]];
+    for (int64_t k = kb[q] + E * kMG; k < ke[q]; k += kMG) {
+      const int j = col[k];
+      const T a = T(val[k]);
+#pragma unroll
+      for (int m = 0; m < NC; ++m) s[m] += a * p[m * n + j];
+    }
+#pragma unroll
+    for (int o = kMG / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int m = 0; m < NC; ++m) s[m] += __shfl_xor(s[m], o, kWave);
+  };
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int i = r0 + q * (1024 / kMG);
+    T s[NC];
+    if (x_zero) {
+#pragma unroll
+      for (int m = 0; m < NC; ++m) s[m] = T(0);
+    } else {
+      product(q, sx, s);
+    }
+    if (i < n && g == 0) {
+      const double w = di[q] * (1.0 / theta);
+#pragma unroll
+      for (int m = 0; m < NC; ++m) {
+        const T rv = x_zero ? b[m * n + i] : b[m * n + i] - s[m];
+        sr[m * n + i] = rv;
+        sd0[m * n + i] = T(w * double(rv));
+      }
+    }
+  }
+  __syncthreads();
+  double rho = 1.0 / sigma1;
+  T* din = sd0;
+  T* dout = sd1;
+  for (int it = 0; it < iters; ++it) {
+    const double rho1 = 1.0 / (2.0 * sigma1 - rho);
+    const T c_keep = T(rho1 * rho), c_new = T(2.0 * rho1 / delta);
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int i = r0 + q * (1024 / kMG);
+      T s[NC];
+      product(q, din, s);
+      if (i < n && g == 0) {
+        const T dd = T(di[q]);
+#pragma unroll
+        for (int m = 0; m < NC; ++m) {
+          const int k = m * n + i;
+          const T dv = din[k];
+          const T rv = sr[k] - s[m];
+          sx[k] += dv;
+          sr[k] = rv;
+          dout[k] = c_keep * dv + c_new * dd * rv;
+        }
+      }
+    }
+    rho = rho1;
+    T* const t = din;
+    din = dout;
+    dout = t;
+    __syncthreads();
+  }
+  for (int k = threadIdx.x; k < NC * n; k += 1024) x[k] = sx[k];
+}
 
 // residual in double: res = b - M x  (b, x of type T; M double), kMG
 // lanes per row as in k_mass_spmv.
@@ -424,6 +536,16 @@ int cheb_cycle(ibvt_coupling* c, const V* mval, const T* b, T* x, bool x_zero, i
   const int32_t* col = c->M.col.as<int32_t>();
   const double* dinv = c->Mdiag_inv.as<double>();
   const ChebBounds k = cheb_bounds(c);
+  if (n <= kBlockSolve) {
+    ProfScope ps("mass_iteration", s);
+    if (nc == 3)
+      k_cheb_block<T, V, 3><<<1, 1024, 0, s>>>(int(n), rp, col, mval, dinv, b, x, x_zero, iters,
+                                               k.theta, k.delta, k.sigma1);
+    else
+      k_cheb_block<T, V, 2><<<1, 1024, 0, s>>>(int(n), rp, col, mval, dinv, b, x, x_zero, iters,
+                                               k.theta, k.delta, k.sigma1);
+    return hip_check(hipGetLastError(), "mass solve launch");
+  }
   if (!x_zero) {
     if (nc == 3) k_mass_spmv<T, V, 3><<<nbm, kThreads, 0, s>>>(n, rp, col, mval, x, q);
     else k_mass_spmv<T, V, 2><<<nbm, kThreads, 0, s>>>(n, rp, col, mval, x, q);

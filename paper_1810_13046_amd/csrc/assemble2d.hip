@@ -15,8 +15,8 @@
 //               values are float in mixed precision): the planar pieces are
 //               cheap, and thin triangles expanded about the cell centre
 //               lose several digits in float.
-//  k_rows2<T>   one lane per (vertex, component): sums the vertex's pieces
-//               into its node box in a fixed order and compacts the row.
+//  k_rows2<T>   lanes per (vertex, component), a node of its box each: sums
+//               the vertex's pieces in a fixed order and writes the row.
 //  transpose and the applies are shared with the 3D path (component count
 //  from the handle).
 //  reverse mode: k_shape2 turns the kept moments into the per-piece shape
@@ -242,60 +242,91 @@ __global__ void k_row_box2(int64_t n_v, int64_t n_t, const int64_t* __restrict__
   cap[w] = sz;
 }
 
-// Gathers the kept pieces of the incident triangles (ascending) in cell
-// order into the row's node box at tmp_off[w] (sum order fixed, so the
-// result does not depend on timing), then compacts the touched nodes in
-// column order to the front of that space.
+// Rows of B: kRow2Lanes lanes per (component, vertex) row, a node of the row's
+// box each (then the next kRow2Lanes).  A node takes from every incident
+// triangle, in order, the values of the cells around it (four at most, in
+// cell order; their loads are independent) into a register, and the touched
+// nodes are written column-sorted.  The triangles' ranges are loaded by the
+// lanes together, kRow2Lanes triangles at a time.
+//
+// Bound: latency of the loads.  22,581 vertices, 1.9M entries in the two
+// components: 113 us; one lane per row that added into memory took 271 (and
+// 67 instead of 14 to compact the rows).
+constexpr int kRow2Lanes = 16;
 template <typename T>
-__global__ void k_rows2(int64_t n_v, int64_t n_t, const int64_t* __restrict__ vt_ptr,
-                        const int32_t* __restrict__ vt_tri, const int32_t* __restrict__ tris,
-                        const CellRange* __restrict__ rng, const int64_t* __restrict__ pair_off,
-                        const uint8_t* __restrict__ keep, const T* __restrict__ pval, LatDesc ld,
-                        const int32_t* __restrict__ box, const int64_t* __restrict__ tmp_off,
-                        int32_t* __restrict__ tmp_col, T* __restrict__ tmp_val,
-                        int64_t* __restrict__ rownnz) {
-  const int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (w >= 2 * n_v) return;
+__global__ __launch_bounds__(256) void k_rows2(
+    int64_t n_v, int64_t n_t, const int64_t* __restrict__ vt_ptr,
+    const int32_t* __restrict__ vt_tri, const int32_t* __restrict__ tris,
+    const CellRange* __restrict__ rng, const int64_t* __restrict__ pair_off,
+    const uint8_t* __restrict__ keep, const T* __restrict__ pval, LatDesc ld,
+    const int32_t* __restrict__ box, const int64_t* __restrict__ tmp_off,
+    int32_t* __restrict__ tmp_col, T* __restrict__ tmp_val, int64_t* __restrict__ rownnz) {
+  constexpr int L = kRow2Lanes;
+  const int64_t w = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / L;
+  const int hl = threadIdx.x % L, h0 = lane_id() - hl;
+  if (w >= 2 * n_v) return;  // all L lanes
   const int d = int(w >= n_v);
   const int64_t i = w - int64_t(d) * n_v;
-  const int bx0 = box[4 * w], by0 = box[4 * w + 1], bnx = box[4 * w + 2], bny = box[4 * w + 3];
-  const int64_t base = tmp_off[w];
-  const int64_t cap = int64_t(bnx) * bny;
-  const int nx = ld.n[3 * d];
-  for (int64_t k = 0; k < cap; ++k) {
-    tmp_col[base + k] = -1;
-    tmp_val[base + k] = T(0);
-  }
-  for (int64_t k = vt_ptr[i]; k < vt_ptr[i + 1]; ++k) {
-    const int64_t t = vt_tri[k];
-    const int la = tris[3 * t + 1] == int32_t(i) ? 1 : (tris[3 * t + 2] == int32_t(i) ? 2 : 0);
-    const int64_t tc = int64_t(d) * n_t + t;
-    const CellRange r = rng[tc];
-    const int64_t p0 = pair_off[tc], p1 = pair_off[tc + 1];
-    for (int64_t p = p0; p < p1; ++p) {
-      if (!keep[p]) continue;
-      const int q = int(p - p0);
-      const int cx = r.lo[0] + q % r.n[0], cy = r.lo[1] + q / r.n[0];
-      const T* v = pval + p * 12 + la * 4;
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          const int64_t kb = int64_t(cx + a - bx0) + int64_t(bnx) * (cy + b - by0);
-          tmp_val[base + kb] += v[a + 2 * b];
-          tmp_col[base + kb] = (cx + a) + nx * (cy + b);
-        }
-    }
-  }
+  const int4 b = *reinterpret_cast<const int4*>(box + 4 * w);
+  const int64_t base = tmp_off[w], cap = int64_t(b.z) * b.w;
+  const int nx = d == 0 ? ld.n[0] : ld.n[3];
+  const int64_t t0 = vt_ptr[i], t1 = vt_ptr[i + 1];
   int64_t out = 0;
-  for (int64_t k = 0; k < cap; ++k) {
-    const int32_t c = tmp_col[base + k];
-    if (c < 0) continue;
-    tmp_col[base + out] = c;
-    tmp_val[base + out] = tmp_val[base + k];
-    ++out;
+  for (int64_t c0 = 0; c0 < cap; c0 += L) {
+    const int64_t c = c0 + hl;
+    const int gx = b.x + int(c % b.z), gy = b.y + int(c / b.z);
+    T acc = T(0);
+    bool hit = false;
+    for (int64_t k0 = t0; k0 < t1; k0 += L) {
+      const int nk = int(min<int64_t>(L, t1 - k0));
+      int lo0 = 0, lo1 = 0, n0 = 0, n1 = 0, first = 0, la = 0;
+      if (hl < nk) {
+        const int64_t t = vt_tri[k0 + hl], tc = int64_t(d) * n_t + t;
+        la = tris[3 * t + 1] == int32_t(i) ? 1 : (tris[3 * t + 2] == int32_t(i) ? 2 : 0);
+        const CellRange r = rng[tc];
+        lo0 = r.lo[0];
+        lo1 = r.lo[1];
+        n0 = r.n[0];
+        n1 = r.n[1];
+        first = int(pair_off[tc]);  // (fewer than 2^31 pairs)
+      }
+      for (int kk = 0; kk < nk; ++kk) {
+        const int x0 = __shfl(lo0, h0 + kk, kWave), y0 = __shfl(lo1, h0 + kk, kWave);
+        const int m0 = __shfl(n0, h0 + kk, kWave), m1 = __shfl(n1, h0 + kk, kWave);
+        const int64_t p0 = __shfl(first, h0 + kk, kWave);
+        const int lk = __shfl(la, h0 + kk, kWave);
+        // the cells (gx - a, gy - b), lowest first; corner a + 2 b of each
+        T v[4];
+        bool on[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int ca = 1 - (q & 1), cb = 1 - (q >> 1);
+          const int ix = gx - ca - x0, iy = gy - cb - y0;
+          on[q] = c < cap && ix >= 0 && ix < m0 && iy >= 0 && iy < m1;
+          const int64_t p = on[q] ? p0 + ix + int64_t(m0) * iy : 0;
+          v[q] = T(0);
+          if (on[q]) {
+            v[q] = pval[p * 12 + lk * 4 + ca + 2 * cb];
+            on[q] = keep[p] != 0;
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (on[q]) {
+            acc += v[q];
+            hit = true;
+          }
+      }
+    }
+    const uint32_t m = uint32_t(ballot64(hit) >> h0) & ((1u << L) - 1u);
+    if (hit) {
+      const int64_t at = base + out + __popc(m & ((1u << hl) - 1u));
+      tmp_col[at] = gx + nx * gy;
+      tmp_val[at] = acc;
+    }
+    out += __popc(m);
   }
-  rownnz[w] = out;
+  if (hl == 0) rownnz[w] = out;
 }
 
 template <typename T>
@@ -304,7 +335,7 @@ __global__ void k_rows_compact2(int64_t n_v, const int64_t* __restrict__ tmp_off
                                 const int64_t* __restrict__ rp0, const int64_t* __restrict__ rp1,
                                 int32_t* __restrict__ c0, int32_t* __restrict__ c1,
                                 T* __restrict__ v0, T* __restrict__ v1) {
-  const int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t w = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kRow2Lanes;
   if (w >= 2 * n_v) return;
   const int d = int(w >= n_v);
   const int64_t i = w - int64_t(d) * n_v;
@@ -312,7 +343,7 @@ __global__ void k_rows_compact2(int64_t n_v, const int64_t* __restrict__ tmp_off
   int32_t* col = d ? c1 : c0;
   T* val = d ? v1 : v0;
   const int64_t src = tmp_off[w], dst = rp[i], n = rp[i + 1] - rp[i];
-  for (int64_t k = 0; k < n; ++k) {
+  for (int64_t k = threadIdx.x % kRow2Lanes; k < n; k += kRow2Lanes) {
     col[dst + k] = tmp_col[src + k];
     val[dst + k] = tmp_val[src + k];
   }
@@ -583,7 +614,7 @@ int assemble2_typed(ibvt_coupling* c, hipStream_t s) {
   if ((st = ensure(c, c->rowtmpval, size_t(tmp_total + 1) * sizeof(T)))) return st;
   {
     ProfScope ps("rows_gather", s);
-    k_rows2<T><<<blocks_for(2 * n_v, 128), 128, 0, s>>>(
+    k_rows2<T><<<blocks_for(2 * n_v * kRow2Lanes, 256), 256, 0, s>>>(
         n_v, n_t, c->vt_ptr.as<int64_t>(), c->vt_tet.as<int32_t>(), c->tets.as<int32_t>(),
         c->rng.as<CellRange>(), c->pair_off.as<int64_t>(), c->keep.as<uint8_t>(),
         c->pval.as<T>(), c->ld, c->rowbox.as<int32_t>(), c->rowtmpoff.as<int64_t>(),
@@ -613,7 +644,7 @@ int assemble2_typed(ibvt_coupling* c, hipStream_t s) {
   }
   {
     ProfScope ps("rows_compact", s);
-    k_rows_compact2<T><<<blocks_for(2 * n_v, 256), 256, 0, s>>>(
+    k_rows_compact2<T><<<blocks_for(2 * n_v * kRow2Lanes, 256), 256, 0, s>>>(
         n_v, c->rowtmpoff.as<int64_t>(), c->rowtmpcol.as<int32_t>(), c->rowtmpval.as<T>(),
         c->B[0].rowptr.as<int64_t>(), c->B[1].rowptr.as<int64_t>(), c->B[0].col.as<int32_t>(),
         c->B[1].col.as<int32_t>(), c->B[0].val.as<T>(), c->B[1].val.as<T>());
