@@ -930,7 +930,7 @@ __global__ __launch_bounds__(256) void k_shape_u(
     const T* v0, const T* v1, const T* v2, double alpha2, int dual, double* __restrict__ pgt) {
   // the three components of a tet in neighbouring lanes: they read the same
   // pair data (bound by it: 885 us component by component, 690 so, on 200k
-  // tets in 5.3M)
+  // tets in 5.3M; 476 with eight candidates' marks read together)
   const int64_t item = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (item >= 3 * n_s) return;
   const int64_t s = item / 3;
@@ -963,58 +963,64 @@ __global__ __launch_bounds__(256) void k_shape_u(
     const T* v = (d == 0) ? v0 : (d == 1 ? v1 : v2);
     const double* gl = srec + kURec * s + 12;  // ∇λ_a at gl[3a + k]
     const T* u = (d == 0) ? u0 : (d == 1 ? u1 : u2);
-    for (int64_t p = p0; p < p1; ++p) {
-      if (!keep[p]) continue;
-      const int64_t f = pf[p];
-      const int4 fv = *reinterpret_cast<const int4*>(tets_f + 4 * f);
-      const double ul[4] = {double(u[fv.x]), double(u[fv.y]), double(u[fv.z]), double(u[fv.w])};
-      const double* gm = frec + kURec * f + 12;  // ∇μ_j at gm[3j + k]
-      double gu[3];
+    // a quarter of the candidates are kept: their marks eight at a time
+    for (int64_t q0 = p0; q0 < p1; q0 += 8) {
+      unsigned kept = 0;
 #pragma unroll
-      for (int k = 0; k < 3; ++k)
-        gu[k] = ul[0] * gm[k] + ul[1] * gm[3 + k] + ul[2] * gm[6 + k] + ul[3] * gm[9 + k];
-      T V[16], L[kULam];
-      load_row<16>(vals + 16 * p, V);
-      load_row<kULam>(lams + kULam * p, L);
-      double zvu = 0.0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        double r = 0.0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r += double(V[4 * i + j]) * ul[j];
-        zvu += zl[i] * r;
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        double zla = 0.0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) zla += zw[i] * double(L[lam_index(a, i)]);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) acc[a * 3 + k] += gu[k] * zla + gl[3 * a + k] * zvu;
-      }
-      if (TWO) {
-        const double vl[4] = {double(v[fv.x]), double(v[fv.y]), double(v[fv.z]),
-                              double(v[fv.w])};
-        double gv[3];
-#pragma unroll
+      for (int q = 0; q < 8; ++q) kept |= (q0 + q < p1 && keep[q0 + q] ? 1u : 0u) << q;
+      for (; kept; kept &= kept - 1) {
+        const int64_t p = q0 + __builtin_ctz(kept);
+        const int64_t f = pf[p];
+        const int4 fv = *reinterpret_cast<const int4*>(tets_f + 4 * f);
+        const double ul[4] = {double(u[fv.x]), double(u[fv.y]), double(u[fv.z]), double(u[fv.w])};
+        const double* gm = frec + kURec * f + 12;  // ∇μ_j at gm[3j + k]
+        double gu[3];
+  #pragma unroll
         for (int k = 0; k < 3; ++k)
-          gv[k] = vl[0] * gm[k] + vl[1] * gm[3 + k] + vl[2] * gm[6 + k] + vl[3] * gm[9 + k];
-        double zvv = 0.0;
-#pragma unroll
+          gu[k] = ul[0] * gm[k] + ul[1] * gm[3 + k] + ul[2] * gm[6 + k] + ul[3] * gm[9 + k];
+        T V[16], L[kULam];
+        load_row<16>(vals + 16 * p, V);
+        load_row<kULam>(lams + kULam * p, L);
+        double zvu = 0.0;
+  #pragma unroll
         for (int i = 0; i < 4; ++i) {
           double r = 0.0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) r += double(V[4 * i + j]) * vl[j];
-          zvv += zl2[i] * r;
+  #pragma unroll
+          for (int j = 0; j < 4; ++j) r += double(V[4 * i + j]) * ul[j];
+          zvu += zl[i] * r;
         }
-#pragma unroll
+  #pragma unroll
         for (int a = 0; a < 4; ++a) {
           double zla = 0.0;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) zla += zw2[i] * double(L[lam_index(a, i)]);
-#pragma unroll
+  #pragma unroll
+          for (int i = 0; i < 4; ++i) zla += zw[i] * double(L[lam_index(a, i)]);
+  #pragma unroll
+          for (int k = 0; k < 3; ++k) acc[a * 3 + k] += gu[k] * zla + gl[3 * a + k] * zvu;
+        }
+        if (TWO) {
+          const double vl[4] = {double(v[fv.x]), double(v[fv.y]), double(v[fv.z]),
+                                double(v[fv.w])};
+          double gv[3];
+  #pragma unroll
           for (int k = 0; k < 3; ++k)
-            acc[a * 3 + k] += alpha2 * (gv[k] * zla + gl[3 * a + k] * zvv);
+            gv[k] = vl[0] * gm[k] + vl[1] * gm[3 + k] + vl[2] * gm[6 + k] + vl[3] * gm[9 + k];
+          double zvv = 0.0;
+  #pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            double r = 0.0;
+  #pragma unroll
+            for (int j = 0; j < 4; ++j) r += double(V[4 * i + j]) * vl[j];
+            zvv += zl2[i] * r;
+          }
+  #pragma unroll
+          for (int a = 0; a < 4; ++a) {
+            double zla = 0.0;
+  #pragma unroll
+            for (int i = 0; i < 4; ++i) zla += zw2[i] * double(L[lam_index(a, i)]);
+  #pragma unroll
+            for (int k = 0; k < 3; ++k)
+              acc[a * 3 + k] += alpha2 * (gv[k] * zla + gl[3 * a + k] * zvv);
+          }
         }
       }
     }
