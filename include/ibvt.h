@@ -26,11 +26,10 @@
  *     for IBVT_FP32_MIXED couplings.  Coordinates X and the gradient g_X are
  *     always double.
  *   - Work is enqueued on `stream` in order.  Assembly reads counts back
- *     to size its buffers: a grid reassembly synchronizes the stream seven
- *     times (four packed read-backs of counts and status flags, one per
- *     velocity component in the transpose), a few more when a handle is
- *     created (lattices, topology, mass pattern); planar and unstructured
- *     assemblies a similar fixed number.  Transfers synchronize only for
+ *     to size its buffers: a reassembly (grid, planar or unstructured)
+ *     synchronizes the stream three times (packed read-backs of counts and
+ *     status flags), a few more when a handle is
+ *     created (lattices, topology, mass pattern).  Transfers synchronize only for
  *     the consistent-mass solve's convergence checks and when `info` is
  *     requested.
  *   - The library's device buffers grow stream-ordered (hipMallocAsync and

@@ -9,21 +9,21 @@
 //                     run's head adds its count into an LDS hash table, so
 //                     one global atomic per (round, bucket) sums them; every
 //                     nonzero marks its node (a byte per lattice node).
-//   scans             bucket offsets in B^dT (from the counts), row offsets
-//                     (from the marked nodes per bucket) and the list of
-//                     nonempty buckets; one read-back gives the touched-node
-//                     and nonempty-bucket counts.
+//   k_bucket_tiles,   per tile of buckets and then before each bucket: its
+//   _scan, _list      offsets in B^dT (from the counts), row offsets (from the
+//                     marked nodes) and the list of nonempty buckets.
 //   k_bucket_scatter  the same rounds reserve a range per (round, bucket);
 //                     run heads take their runs' places in it and every
 //                     nonzero writes its (value, vertex, node) record.
-//   k_bucket_sort     one block per nonempty bucket: a counting sort of its
+//   k_bucket_sort     nonempty buckets, a block each: a counting sort of its
 //                     records by node in LDS, then each record's place in its
 //                     node's row is the number of that row's vertices below
 //                     its own (a row's vertices are distinct); the block
 //                     writes the bucket's columns, values, row pointers and
 //                     row map.
-// Small operators take a counting sort over the whole lattice instead, the
-// components together and without waiting for a count:
+// The components go through these together while they are not too large, and
+// no count is waited for.  Small operators take a counting sort over the whole
+// lattice instead, together as well:
 //   k_tcount          nonzeros per lattice node.
 //   k_tsums, k_tscan  per tile of nodes: its touched nodes and its nonzeros,
 //                     and their prefix sums.
@@ -275,6 +275,46 @@ struct BucketSpan {
   int32_t b, n;
 };
 
+// Sums over buckets: nonzeros, touched nodes, nonempty buckets.
+struct BucketSums {
+  int64_t nnz, touched, full;
+  __device__ __forceinline__ void add(const BucketSums& o) {
+    nnz += o.nnz;
+    touched += o.touched;
+    full += o.full;
+  }
+};
+
+// One component of a launch.
+template <typename T>
+struct BOne {
+  const int64_t* rowptr;  // B^d
+  const int32_t* col;
+  const T* val;
+  int64_t nnz;
+  int64_t nb;             // buckets
+  int32_t* bcount;        // per bucket: nonzeros
+  int32_t* bfill;         // places taken
+  uint8_t* mark;          // a byte per node (whole buckets)
+  int32_t* boff;          // first place
+  BucketSpan* list;       // nonempty buckets
+  BucketRec<T>* rec;
+  BucketSums* sum;        // per tile of buckets, then before it
+  int64_t tiles, tile0;   // (tile0: its first among the launch's)
+  int64_t* touched;
+  int64_t* trowptr;       // B^dT
+  int32_t* rowmap;
+  int32_t* tcol;
+  T* tval;
+};
+template <typename T>
+struct BBatch {
+  BOne<T> c[3];
+  int n;
+};
+constexpr int64_t kBatchRecords = int64_t(32) << 20;  // (0.25 GiB in float)
+constexpr int kBTile = 4 * kBucketThreads;  // buckets of a tile
+
 // Slot of bucket b in a round's table (open addressing; a round has at most
 // kRound distinct buckets, so a free slot always exists).
 __device__ __forceinline__ int table_slot(int32_t* key, int32_t b) {
@@ -318,9 +358,14 @@ __device__ __forceinline__ WaveRun wave_run(int32_t bucket, bool valid) {
 
 // Per bucket: nonzero count (only run heads touch the round's table), and
 // a byte per node that occurs (plain stores: every writer stores 1).
-__global__ __launch_bounds__(kBucketThreads) void k_bucket_count(
-    int64_t n_rows, int64_t per, const int64_t* __restrict__ rowptr,
-    const int32_t* __restrict__ col, int32_t* __restrict__ bcount, uint8_t* __restrict__ mark) {
+template <typename T>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_count(BBatch<T> bt, int64_t n_rows,
+                                                                 int64_t per) {
+  const BOne<T>& c = blockIdx.y == 0 ? bt.c[0] : (blockIdx.y == 1 ? bt.c[1] : bt.c[2]);
+  const int64_t* __restrict__ rowptr = c.rowptr;
+  const int32_t* __restrict__ col = c.col;
+  int32_t* __restrict__ bcount = c.bcount;
+  uint8_t* __restrict__ mark = c.mark;
   __shared__ int32_t key[kTable];
   __shared__ int32_t cnt[kTable];
   const int64_t r0 = xcd_row_block(per) * kBucketRows;
@@ -358,31 +403,104 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_count(
   }
 }
 
-// Touched nodes per bucket (its marked nodes) and its nonempty flag.
-__global__ void k_bucket_rows(int64_t nb, const uint32_t* __restrict__ mark,
-                              int32_t* __restrict__ tb, int32_t* __restrict__ nonempty) {
-  const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (b < nb) {
-    int m = 0;
+template <typename T>
+__device__ __forceinline__ const BOne<T>& tile_component(const BBatch<T>& b) {
+  const int64_t t = blockIdx.x;
+  return b.n > 2 && t >= b.c[2].tile0 ? b.c[2] : (b.n > 1 && t >= b.c[1].tile0 ? b.c[1] : b.c[0]);
+}
+
+// Bucket b's sums (its touched nodes are its marked ones).
+template <typename T>
+__device__ __forceinline__ BucketSums bucket_sums(const BOne<T>& c, int64_t b) {
+  BucketSums x{0, 0, 0};
+  if (b < c.nb) {
+    const uint4* m = reinterpret_cast<const uint4*>(c.mark + b * kBucketNodes);
+    const uint4 p = m[0], q = m[1];
+    x.nnz = c.bcount[b];
+    x.touched = __popc(p.x) + __popc(p.y) + __popc(p.z) + __popc(p.w) + __popc(q.x) + __popc(q.y) +
+                __popc(q.z) + __popc(q.w);
+    x.full = x.touched != 0;
+  }
+  return x;
+}
+
+// Exclusive prefix of the threads' sums across the block, and the total.
+template <int THREADS>
+__device__ __forceinline__ BucketSums sums_prefix(const BucketSums& v, BucketSums (&sh)[THREADS / kWave],
+                                                  BucketSums& total) {
+  BucketSums x = v;
+  const int l = lane_id(), w = threadIdx.x / kWave;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const BucketSums y{__shfl_up(x.nnz, o, kWave), __shfl_up(x.touched, o, kWave),
+                       __shfl_up(x.full, o, kWave)};
+    if (l >= o) x.add(y);
+  }
+  if (l == kWave - 1) sh[w] = x;
+  __syncthreads();
+  BucketSums pre{0, 0, 0};
+  total = pre;
+  for (int k = 0; k < THREADS / kWave; ++k) {
+    if (k < w) pre.add(sh[k]);
+    total.add(sh[k]);
+  }
+  __syncthreads();
+  pre.add(BucketSums{x.nnz - v.nnz, x.touched - v.touched, x.full - v.full});
+  return pre;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_tiles(BBatch<T> bt) {
+  __shared__ BucketSums sh[kBucketThreads / kWave];
+  const BOne<T>& c = tile_component(bt);
+  const int64_t t = int64_t(blockIdx.x) - c.tile0;
+  BucketSums x{0, 0, 0}, total;
 #pragma unroll
-    for (int w = 0; w < kBucketNodes / 4; ++w) m += __popc(mark[b * (kBucketNodes / 4) + w]);
-    tb[b] = m;
-    nonempty[b] = m != 0;
+  for (int k = 0; k < 4; ++k) x.add(bucket_sums(c, t * kBTile + threadIdx.x * 4 + k));
+  sums_prefix<kBucketThreads>(x, sh, total);
+  if (threadIdx.x == 0) c.sum[t] = total;
+}
+
+// One block per component: its tiles' sums scanned in place, the totals.
+template <typename T>
+__global__ __launch_bounds__(1024) void k_bucket_scan(BBatch<T> bt) {
+  __shared__ BucketSums sh[1024 / kWave];
+  const BOne<T>& c = blockIdx.x == 0 ? bt.c[0] : (blockIdx.x == 1 ? bt.c[1] : bt.c[2]);
+  const int64_t per = ceil_div(c.tiles, 1024);
+  const int64_t b0 = int64_t(threadIdx.x) * per, b1 = min<int64_t>(c.tiles, b0 + per);
+  BucketSums x{0, 0, 0}, total;
+  for (int64_t t = b0; t < b1; ++t) x.add(c.sum[t]);
+  BucketSums pre = sums_prefix<1024>(x, sh, total);
+  for (int64_t t = b0; t < b1; ++t) {
+    const BucketSums v = c.sum[t];
+    c.sum[t] = pre;
+    pre.add(v);
+  }
+  if (threadIdx.x == 0) {
+    c.touched[0] = total.touched;
+    c.touched[1] = total.full;
+    c.trowptr[total.touched] = c.nnz;
   }
 }
 
-// The nonempty buckets in ascending order.
-__global__ void k_bucket_list(int64_t nb, const int32_t* __restrict__ nonempty,
-                              const int64_t* __restrict__ pos, const int64_t* __restrict__ boff,
-                              const int64_t* __restrict__ toff, BucketSpan* __restrict__ list) {
-  const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (b < nb && nonempty[b]) {
-    BucketSpan e;
-    e.a = boff[b];
-    e.t = toff[b];
-    e.b = int32_t(b);
-    e.n = int32_t(boff[b + 1] - boff[b]);
-    list[pos[b]] = e;
+// Every bucket's first place, and the nonempty ones in ascending order.
+template <typename T>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_list(BBatch<T> bt) {
+  __shared__ BucketSums sh[kBucketThreads / kWave];
+  const BOne<T>& c = tile_component(bt);
+  const int64_t t = int64_t(blockIdx.x) - c.tile0, b0 = t * kBTile + threadIdx.x * 4;
+  BucketSums v[4], x{0, 0, 0}, total;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    v[k] = bucket_sums(c, b0 + k);
+    x.add(v[k]);
+  }
+  BucketSums at = sums_prefix<kBucketThreads>(x, sh, total);
+  at.add(c.sum[t]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (b0 + k < c.nb) c.boff[b0 + k] = int32_t(at.nnz);
+    if (v[k].full) c.list[at.full] = BucketSpan{at.nnz, at.touched, int32_t(b0 + k), int32_t(v[k].nnz)};
+    at.add(v[k]);
   }
 }
 
@@ -390,10 +508,15 @@ __global__ void k_bucket_list(int64_t nb, const int32_t* __restrict__ nonempty,
 // of the bucket, run heads take their runs' places in it, and every
 // nonzero writes its record there.
 template <typename T>
-__global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(
-    int64_t n_rows, int64_t per, const int64_t* __restrict__ rowptr,
-    const int32_t* __restrict__ col, const T* __restrict__ val, const int64_t* __restrict__ boff,
-    int32_t* __restrict__ bfill, BucketRec<T>* __restrict__ rec) {
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(BBatch<T> bt, int64_t n_rows,
+                                                                   int64_t per) {
+  const BOne<T>& c = blockIdx.y == 0 ? bt.c[0] : (blockIdx.y == 1 ? bt.c[1] : bt.c[2]);
+  const int64_t* __restrict__ rowptr = c.rowptr;
+  const int32_t* __restrict__ col = c.col;
+  const T* __restrict__ val = c.val;
+  const int32_t* __restrict__ boff = c.boff;
+  int32_t* __restrict__ bfill = c.bfill;
+  BucketRec<T>* __restrict__ rec = c.rec;
   __shared__ int32_t key[kTable];
   __shared__ int32_t cnt[kTable];  // then the slot's first position in the records
   __shared__ int64_t srp[kBucketRows + 1];
@@ -435,7 +558,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(
     __syncthreads();
     for (int h = threadIdx.x; h < kTable; h += kBucketThreads) {
       const int32_t b = key[h];
-      if (b >= 0) cnt[h] = int32_t(boff[b]) + atomicAdd(&bfill[b], cnt[h]);
+      if (b >= 0) cnt[h] = boff[b] + atomicAdd(&bfill[b], cnt[h]);
     }
     __syncthreads();
 #pragma unroll
@@ -458,142 +581,154 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(
   }
 }
 
-// One block per nonempty bucket (each bucket owns its ranges of B^dT): row
+// A block takes nonempty buckets in turn (each owns its ranges of B^dT): row
 // pointers and row map of its nodes, then its records in (node, vertex)
 // order.  A bucket that fits the LDS is read once into registers; counting
 // a record's node also gives it a slot among that node's records, the LDS
 // holds the vertices grouped by node, and each record is ranked from its
 // registers.
 template <typename T>
-__global__ __launch_bounds__(kBucketThreads) void k_bucket_sort(
-    const BucketSpan* __restrict__ list, BucketRec<T>* __restrict__ rec,
-    int32_t* __restrict__ tcol, T* __restrict__ tval, int64_t* __restrict__ trowptr,
-    int32_t* __restrict__ rowmap, int64_t touched, int64_t nnz) {
+__global__ __launch_bounds__(kBucketThreads, sizeof(T) == sizeof(float) ? 5 : 4) void k_bucket_sort(BBatch<T> bt) {
+  const BOne<T>& c = blockIdx.y == 0 ? bt.c[0] : (blockIdx.y == 1 ? bt.c[1] : bt.c[2]);
+  const BucketSpan* __restrict__ list = c.list;
+  BucketRec<T>* __restrict__ rec = c.rec;
+  int32_t* __restrict__ tcol = c.tcol;
+  T* __restrict__ tval = c.tval;
+  int64_t* __restrict__ trowptr = c.trowptr;
+  int32_t* __restrict__ rowmap = c.rowmap;
   constexpr int R = kSortCap / kBucketThreads;
   __shared__ int32_t ncnt[kBucketNodes], noff[kBucketNodes], nfill[kBucketNodes];
   __shared__ int32_t sr[kSortCap];
-  const BucketSpan e = list[blockIdx.x];
-  const int64_t a = e.a;
-  const int n = e.n;
-  const int t = threadIdx.x;
-  const bool fits = n <= kSortCap;
-  if (t < kBucketNodes) {
-    ncnt[t] = 0;
-    nfill[t] = 0;
-  }
-  if (blockIdx.x == 0 && t == 0) trowptr[touched] = nnz;
-  BucketRec<T> x[R];
-  int slot[R];
-  if (fits) {
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-      if (t + i * kBucketThreads < n) x[i] = rec[a + t + i * kBucketThreads];
-  }
-  __syncthreads();
-  if (fits) {
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-      if (t + i * kBucketThreads < n) slot[i] = atomicAdd(&ncnt[x[i].nl()], 1);
-  } else {
-    for (int j = t; j < n; j += kBucketThreads) atomicAdd(&ncnt[rec[a + j].nl()], 1);
-  }
-  __syncthreads();
-  if (t < kWave) {  // the first wave: node offsets, and the touched nodes' rows
-    const int cn = t < kBucketNodes ? ncnt[t] : 0;
-    int y = cn;
-    for (int o = 1; o < kBucketNodes; o <<= 1) {
-      const int z = __shfl_up(y, o, kWave);
-      if (t >= o) y += z;
+  const int64_t full = c.touched[1];
+  for (int64_t at = blockIdx.x; at < full; at += gridDim.x) {
+    const BucketSpan e = list[at];
+    const int64_t a = e.a;
+    const int n = e.n;
+    const int t = threadIdx.x;
+    const bool fits = n <= kSortCap;
+    if (t < kBucketNodes) {
+      ncnt[t] = 0;
+      nfill[t] = 0;
     }
-    const uint64_t m = ballot64(cn > 0);
-    if (t < kBucketNodes) noff[t] = y - cn;
-    if (cn > 0) {
-      const int64_t row = e.t + rank_below(m);
-      trowptr[row] = a + (y - cn);
-      rowmap[row] = (e.b << kBucketBits) | t;
-    }
-  }
-  __syncthreads();
-  if (fits) {
+    BucketRec<T> x[R];
+    int slot[R];
+    if (fits) {
 #pragma unroll
-    for (int i = 0; i < R; ++i)
-      if (t + i * kBucketThreads < n) sr[noff[x[i].nl()] + slot[i]] = x[i].r();
+      for (int i = 0; i < R; ++i)
+        if (t + i * kBucketThreads < n) x[i] = rec[a + t + i * kBucketThreads];
+    }
     __syncthreads();
-    // a record's place in its row: the row's vertices below its own
+    if (fits) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      if (t + i * kBucketThreads >= n) continue;
-      const int nl = x[i].nl();
-      const int s0 = noff[nl], s1 = s0 + ncnt[nl];
-      const int32_t r = x[i].r();
-      int rank = 0, u = s0;
-      for (; u + 8 <= s1; u += 8) {  // eight reads in flight
-        int32_t y[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) y[k] = sr[u + k];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) rank += y[k] < r ? 1 : 0;
+      for (int i = 0; i < R; ++i)
+        if (t + i * kBucketThreads < n) slot[i] = atomicAdd(&ncnt[x[i].nl()], 1);
+    } else {
+      for (int j = t; j < n; j += kBucketThreads) atomicAdd(&ncnt[rec[a + j].nl()], 1);
+    }
+    __syncthreads();
+    if (t < kWave) {  // the first wave: node offsets, and the touched nodes' rows
+      const int cn = t < kBucketNodes ? ncnt[t] : 0;
+      int y = cn;
+      for (int o = 1; o < kBucketNodes; o <<= 1) {
+        const int z = __shfl_up(y, o, kWave);
+        if (t >= o) y += z;
       }
-      for (; u < s1; ++u) rank += sr[u] < r ? 1 : 0;
-      tcol[a + s0 + rank] = r;
-      tval[a + s0 + rank] = x[i].v;
-    }
-  } else {
-    // more records than the LDS holds: group them by node in B^dT's arrays,
-    // copy the grouped records back over the bucket's (consumed) ones, then
-    // rank each node's records against its row, kSortCap of the row's
-    // vertices at a time through LDS
-    for (int j = t; j < n; j += kBucketThreads) {
-      const BucketRec<T> g = rec[a + j];
-      const int64_t q = a + noff[g.nl()] + atomicAdd(&nfill[g.nl()], 1);
-      tcol[q] = g.r();
-      tval[q] = g.v;
+      const uint64_t m = ballot64(cn > 0);
+      if (t < kBucketNodes) noff[t] = y - cn;
+      if (cn > 0) {
+        const int64_t row = e.t + rank_below(m);
+        trowptr[row] = a + (y - cn);
+        rowmap[row] = (e.b << kBucketBits) | t;
+      }
     }
     __syncthreads();
-    for (int j = t; j < n; j += kBucketThreads) {
-      BucketRec<T> g;
-      g.v = tval[a + j];
-      g.rn = uint32_t(tcol[a + j]) << kBucketBits;
-      rec[a + j] = g;
-    }
-    for (int nl = 0; nl < kBucketNodes; ++nl) {
-      const int L = ncnt[nl];
-      const int64_t s0 = a + noff[nl];
-      for (int q0 = 0; q0 < L; q0 += kBucketThreads) {
-        const int q = q0 + t;
+    if (fits) {
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+        if (t + i * kBucketThreads < n) sr[noff[x[i].nl()] + slot[i]] = x[i].r();
+      __syncthreads();
+      // a record's place in its row: the row's vertices below its own
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        if (t + i * kBucketThreads >= n) continue;
+        const int nl = x[i].nl();
+        const int s0 = noff[nl], s1 = s0 + ncnt[nl];
+        const int32_t r = x[i].r();
+        int rank = 0, u = s0;
+        for (; u + 8 <= s1; u += 8) {  // eight reads in flight
+          int32_t y[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) y[k] = sr[u + k];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) rank += y[k] < r ? 1 : 0;
+        }
+        for (; u < s1; ++u) rank += sr[u] < r ? 1 : 0;
+        tcol[a + s0 + rank] = r;
+        tval[a + s0 + rank] = x[i].v;
+      }
+    } else {
+      // more records than the LDS holds: group them by node in B^dT's arrays,
+      // copy the grouped records back over the bucket's (consumed) ones, then
+      // rank each node's records against its row, kSortCap of the row's
+      // vertices at a time through LDS
+      for (int j = t; j < n; j += kBucketThreads) {
+        const BucketRec<T> g = rec[a + j];
+        const int64_t q = a + noff[g.nl()] + atomicAdd(&nfill[g.nl()], 1);
+        tcol[q] = g.r();
+        tval[q] = g.v;
+      }
+      __syncthreads();
+      for (int j = t; j < n; j += kBucketThreads) {
         BucketRec<T> g;
-        g.v = T(0);
-        g.rn = 0;
-        int rank = 0;
-        for (int c0 = 0; c0 < L; c0 += kSortCap) {
-          const int m = min(kSortCap, L - c0);
-          __syncthreads();  // the grouped records are written; sr is free
-          if (c0 == 0 && q < L) g = rec[s0 + q];
-          for (int u = t; u < m; u += kBucketThreads) sr[u] = rec[s0 + c0 + u].r();
-          __syncthreads();
-          if (q < L)
-            for (int u = 0; u < m; ++u) rank += sr[u] < g.r() ? 1 : 0;
-        }
-        if (q < L) {
-          tcol[s0 + rank] = g.r();
-          tval[s0 + rank] = g.v;
+        g.v = tval[a + j];
+        g.rn = uint32_t(tcol[a + j]) << kBucketBits;
+        rec[a + j] = g;
+      }
+      for (int nl = 0; nl < kBucketNodes; ++nl) {
+        const int L = ncnt[nl];
+        const int64_t s0 = a + noff[nl];
+        for (int q0 = 0; q0 < L; q0 += kBucketThreads) {
+          const int q = q0 + t;
+          BucketRec<T> g;
+          g.v = T(0);
+          g.rn = 0;
+          int rank = 0;
+          for (int c0 = 0; c0 < L; c0 += kSortCap) {
+            const int m = min(kSortCap, L - c0);
+            __syncthreads();  // the grouped records are written; sr is free
+            if (c0 == 0 && q < L) g = rec[s0 + q];
+            for (int u = t; u < m; u += kBucketThreads) sr[u] = rec[s0 + c0 + u].r();
+            __syncthreads();
+            if (q < L)
+              for (int u = 0; u < m; ++u) rank += sr[u] < g.r() ? 1 : 0;
+          }
+          if (q < L) {
+            tcol[s0 + rank] = g.r();
+            tval[s0 + rank] = g.v;
+          }
         }
       }
     }
+    __syncthreads();  // the LDS is free for the next bucket
   }
 }
 
-// Nonzeros from which the bucket transpose is taken: 2^22, or
-// IBVT_BUCKET_NNZ from the environment (a positive integer; small values put
-// small operators through the bucket path, as the tests do).  Both paths
-// give the same B^dT.
-int64_t bucket_nnz() {
+// Whether B^d is transposed through the buckets: from 2^18 nonzeros, with
+// fewer than 4,096 rows (whose blocks of 64 rows leave most of the card idle)
+// from 2^22; or from IBVT_BUCKET_NNZ nonzeros (the environment, a positive
+// integer; small values put small operators through the bucket path, as the
+// tests do).  Both paths give the same B^dT.  Microseconds for three
+// components through the buckets / the counting sort, by nonzeros and nodes
+// of each: 47k, 113k: 68 / 51; 129k, 0.3M: 71 / 65; 143k, 2.1M: 69 / 99; 363k, 0.9M:
+// 84 / 100; 0.6M, 2.1M (double): 104 / 267; 2.3M, 7.1M: 221 / 428; with 675 rows
+// 117k, 0.9M: 142 / 52.
+bool use_buckets(int64_t nnz, int64_t n_rows) {
   if (const char* e = std::getenv("IBVT_BUCKET_NNZ")) {
     char* end = nullptr;
     const long long v = std::strtoll(e, &end, 10);
-    if (end != e && *end == '\0' && v > 0) return int64_t(v);
+    if (end != e && *end == '\0' && v > 0) return nnz >= int64_t(v);
   }
-  return int64_t(4) << 20;
+  return nnz >= (n_rows < 4096 ? int64_t(1) << 22 : int64_t(1) << 18);
 }
 
 inline unsigned blocks_for(int64_t n, int threads) {
@@ -617,7 +752,7 @@ int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** t
   int st;
   const size_t node_b = size_t(tiles) * kTTile * sizeof(int32_t);
   if ((st = ensure(c, c->mark, node_b + size_t(tiles) * sizeof(uint64_t)))) return st;
-  if ((st = ensure(c, c->tcnt, 3 * sizeof(int64_t)))) return st;
+  if ((st = ensure(c, c->tcnt, 6 * sizeof(int64_t)))) return st;
   for (int k = 0; k < n; ++k) {
     const Csr& B = c->B[ds[k]];
     Csr& Bt = c->Bt[ds[k]];
@@ -634,7 +769,7 @@ int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** t
     o.nnz = B.nnz;
     o.node = c->mark.as<int32_t>() + o.tile0 * kTTile;
     o.sum = reinterpret_cast<uint64_t*>(c->mark.as<char>() + node_b) + o.tile0;
-    o.touched = c->tcnt.as<int64_t>() + ds[k];
+    o.touched = c->tcnt.as<int64_t>() + 2 * ds[k];
     o.trowptr = Bt.rowptr.template as<int64_t>();
     o.rowmap = Bt.rowmap.template as<int32_t>();
     o.tcol = Bt.col.template as<int32_t>();
@@ -660,89 +795,110 @@ int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** t
   return hip_check(hipGetLastError(), "transpose launch");
 }
 
-// Bucket transpose (large operators).
+// Bucket transpose of the n components in ds; the counts stay on the device
+// (transpose_counting).
 template <typename T>
-int transpose_buckets(ibvt_coupling* c, int d, hipStream_t s) {
-  const int64_t nf = c->n_fluid[d];
-  const Csr& B = c->B[d];
-  Csr& Bt = c->Bt[d];
+int transpose_buckets(ibvt_coupling* c, const int* ds, int n, const int64_t** touched,
+                      hipStream_t s) {
+  BBatch<T> b{};
+  b.n = n;
+  auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   int st;
-  const int64_t nb = ceil_div(nf, kBucketNodes);
-  auto al = [](size_t n) { return (n + 255) & ~size_t(255); };
-  const size_t rec_b = al(size_t(B.nnz) * sizeof(BucketRec<T>));
-  const size_t i32_b = al(size_t(nb) * sizeof(int32_t));
-  const size_t i64_b = al(size_t(nb + 1) * sizeof(int64_t));
-  const size_t mark_b = al(size_t(nb) * kBucketNodes);  // a byte per lattice node
-  const size_t zero_b = 2 * i32_b + mark_b;             // counts, fill levels, marks
-  const size_t list_b = al(size_t(nb) * sizeof(BucketSpan));
-  if ((st = ensure(c, c->tbuf, rec_b + zero_b + 2 * i32_b + 3 * i64_b + list_b))) return st;
-  char* p = c->tbuf.as<char>();
-  BucketRec<T>* rec = reinterpret_cast<BucketRec<T>*>(p);
-  p += rec_b;
-  int32_t* bcount = reinterpret_cast<int32_t*>(p);
-  int32_t* bfill = reinterpret_cast<int32_t*>(p + i32_b);
-  uint8_t* mark = reinterpret_cast<uint8_t*>(p + 2 * i32_b);
-  if ((st = hip_check(hipMemsetAsync(p, 0, zero_b, s), "memset"))) return st;
-  p += zero_b;
-  int32_t* tb = reinterpret_cast<int32_t*>(p);
-  int32_t* nonempty = reinterpret_cast<int32_t*>(p + i32_b);
-  p += 2 * i32_b;
-  int64_t* boff = reinterpret_cast<int64_t*>(p);
-  int64_t* toff = reinterpret_cast<int64_t*>(p + i64_b);
-  int64_t* lpos = reinterpret_cast<int64_t*>(p + 2 * i64_b);
-  BucketSpan* list = reinterpret_cast<BucketSpan*>(p + 3 * i64_b);
-
+  if ((st = ensure(c, c->tcnt, 6 * sizeof(int64_t)))) return st;
+  size_t zero = 0, rest = 0;
+  int64_t tiles = 0, nb_max = 0, nnz_max = 0;
+  size_t zero_at[3], rest_at[3];
+  for (int k = 0; k < n; ++k) {
+    const Csr& B = c->B[ds[k]];
+    Csr& Bt = c->Bt[ds[k]];
+    BOne<T>& o = b.c[k];
+    const int64_t nf = c->n_fluid[ds[k]], rows = std::min<int64_t>(B.nnz, nf);
+    Bt.nnz = B.nnz;
+    if ((st = ensure(c, Bt.rowptr, size_t(rows + 1) * sizeof(int64_t)))) return st;
+    if ((st = ensure(c, Bt.rowmap, size_t(rows + 1) * sizeof(int32_t)))) return st;
+    if ((st = ensure(c, Bt.col, size_t(B.nnz + 1) * sizeof(int32_t)))) return st;
+    if ((st = ensure(c, Bt.val, size_t(B.nnz + 1) * sizeof(T)))) return st;
+    o.rowptr = B.rowptr.template as<int64_t>();
+    o.col = B.col.template as<int32_t>();
+    o.val = B.val.template as<T>();
+    o.nnz = B.nnz;
+    o.nb = ceil_div(nf, kBucketNodes);
+    o.tiles = ceil_div(o.nb, kBTile);
+    o.tile0 = tiles;
+    tiles += o.tiles;
+    nb_max = std::max(nb_max, o.nb);
+    nnz_max = std::max(nnz_max, o.nnz);
+    o.touched = c->tcnt.as<int64_t>() + 2 * ds[k];
+    touched[ds[k]] = o.touched;
+    o.trowptr = Bt.rowptr.template as<int64_t>();
+    o.rowmap = Bt.rowmap.template as<int32_t>();
+    o.tcol = Bt.col.template as<int32_t>();
+    o.tval = Bt.val.template as<T>();
+    zero_at[k] = zero;
+    rest_at[k] = rest;
+    zero += 2 * al(size_t(o.nb) * sizeof(int32_t)) + al(size_t(o.nb) * kBucketNodes);
+    rest += al(size_t(B.nnz) * sizeof(BucketRec<T>)) + al(size_t(o.nb) * sizeof(int32_t)) +
+            al(size_t(o.nb) * sizeof(BucketSpan)) + al(size_t(o.tiles) * sizeof(BucketSums));
+  }
+  if ((st = ensure(c, c->tbuf, zero + rest))) return st;
+  for (int k = 0; k < n; ++k) {
+    BOne<T>& o = b.c[k];
+    char* p = c->tbuf.as<char>() + zero_at[k];
+    const size_t i32 = al(size_t(o.nb) * sizeof(int32_t));
+    o.bcount = reinterpret_cast<int32_t*>(p);
+    o.bfill = reinterpret_cast<int32_t*>(p + i32);
+    o.mark = reinterpret_cast<uint8_t*>(p + 2 * i32);
+    p = c->tbuf.as<char>() + zero + rest_at[k];
+    o.rec = reinterpret_cast<BucketRec<T>*>(p);
+    p += al(size_t(o.nnz) * sizeof(BucketRec<T>));
+    o.boff = reinterpret_cast<int32_t*>(p);
+    p += i32;
+    o.list = reinterpret_cast<BucketSpan*>(p);
+    o.sum = reinterpret_cast<BucketSums*>(p + al(size_t(o.nb) * sizeof(BucketSpan)));
+  }
+  if ((st = hip_check(hipMemsetAsync(c->tbuf.p, 0, zero, s), "memset"))) return st;
   const int64_t n_rows = c->n_vert;
   const int64_t per = ceil_div(ceil_div(n_rows, kBucketRows), 8);
-  const unsigned grid = unsigned(8 * per);
-  k_bucket_count<<<grid, kBucketThreads, 0, s>>>(n_rows, per, B.rowptr.as<int64_t>(),
-                                                 B.col.as<int32_t>(), bcount, mark);
-  k_bucket_rows<<<blocks_for(nb, 256), 256, 0, s>>>(nb, reinterpret_cast<const uint32_t*>(mark),
-                                                    tb, nonempty);
-  if ((st = hip_check(hipGetLastError(), "transpose count launch"))) return st;
-  if ((st = scan_i32_to_i64(c, bcount, boff, nb, s))) return st;
-  if ((st = scan_i32_to_i64(c, tb, toff, nb, s))) return st;
-  if ((st = scan_i32_to_i64(c, nonempty, lpos, nb, s))) return st;
-  k_bucket_list<<<blocks_for(nb, 256), 256, 0, s>>>(nb, nonempty, lpos, boff, toff, list);
-  int64_t got[2] = {0, 0};
-  {
-    const int64_t* src[2] = {toff + nb, lpos + nb};
-    if ((st = read_counts(c, src, 2, got, s))) return st;
-  }
-  const int64_t touched = got[0], n_nonempty = got[1];
-  Bt.nrows = touched;
-  Bt.nnz = B.nnz;
-  if ((st = ensure(c, Bt.rowptr, size_t(touched + 1) * sizeof(int64_t)))) return st;
-  if ((st = ensure(c, Bt.rowmap, size_t(touched + 1) * sizeof(int32_t)))) return st;
-  if ((st = ensure(c, Bt.col, size_t(B.nnz + 1) * sizeof(int32_t)))) return st;
-  if ((st = ensure(c, Bt.val, size_t(B.nnz + 1) * sizeof(T)))) return st;
-  k_bucket_scatter<T><<<grid, kBucketThreads, 0, s>>>(n_rows, per, B.rowptr.as<int64_t>(),
-                                                      B.col.as<int32_t>(), B.val.as<T>(), boff,
-                                                      bfill, rec);
-  k_bucket_sort<T><<<unsigned(n_nonempty), kBucketThreads, 0, s>>>(
-      list, rec, Bt.col.as<int32_t>(), Bt.val.as<T>(), Bt.rowptr.as<int64_t>(),
-      Bt.rowmap.as<int32_t>(), touched, B.nnz);
+  const unsigned un = unsigned(n);
+  const dim3 grid(unsigned(8 * per), un);
+  k_bucket_count<T><<<grid, kBucketThreads, 0, s>>>(b, n_rows, per);
+  k_bucket_tiles<T><<<unsigned(tiles), kBucketThreads, 0, s>>>(b);
+  k_bucket_scan<T><<<un, 1024, 0, s>>>(b);
+  k_bucket_list<T><<<unsigned(tiles), kBucketThreads, 0, s>>>(b);
+  k_bucket_scatter<T><<<grid, kBucketThreads, 0, s>>>(b, n_rows, per);
+  // (the number of nonempty buckets is on the device: a block for 512
+  // nonzeros, the blocks loop)
+  const int64_t sort_blocks = std::min<int64_t>({nb_max, 65536, nnz_max / 512 + 64});
+  k_bucket_sort<T><<<dim3(unsigned(sort_blocks), un), kBucketThreads, 0, s>>>(b);
   return hip_check(hipGetLastError(), "transpose launch");
 }
 
 }  // namespace
 
 // Components with fewer nonzeros than the bucket transpose is for go through
-// the counting sort together; larger ones that have too many vertices for
-// the buckets do so one by one (their scratch is as large as they are).
+// the counting sort together, the others through the buckets: together while
+// their records are few, else one after the other in the same scratch.
+// Large ones that have too many vertices for the buckets take the counting
+// sort one by one.
 template <typename T>
 int transposes(ibvt_coupling* c, int n, const int64_t** touched, hipStream_t s) {
-  const int64_t limit = bucket_nnz();
-  int small[3], ns = 0, st;
+  int small[3], large[3], ns = 0, nl = 0, st;
+  int64_t records = 0;
   for (int d = 0; d < n; ++d) {
-    touched[d] = nullptr;
-    if (c->B[d].nnz < limit) {
+    if (!use_buckets(c->B[d].nnz, c->n_vert)) {
       small[ns++] = d;
     } else if (c->n_vert < kBucketMaxVert) {
-      if ((st = transpose_buckets<T>(c, d, s))) return st;
+      large[nl++] = d;
+      records += c->B[d].nnz;
     } else if ((st = transpose_counting<T>(c, &d, 1, touched, s))) {
       return st;
     }
+  }
+  if (nl && records <= kBatchRecords) {
+    if ((st = transpose_buckets<T>(c, large, nl, touched, s))) return st;
+  } else {
+    for (int k = 0; k < nl; ++k)
+      if ((st = transpose_buckets<T>(c, large + k, 1, touched, s))) return st;
   }
   return ns ? transpose_counting<T>(c, small, ns, touched, s) : IBVT_OK;
 }
