@@ -28,7 +28,8 @@
  *   - Work is enqueued on `stream` in order.  Assembly reads counts back
  *     to size its buffers: a reassembly (grid, planar or unstructured)
  *     synchronizes the stream three times (packed read-backs of counts and
- *     status flags), a few more when a handle is
+ *     status flags), once more for each component of a very large
+ *     operator, a few more when a handle is
  *     created (lattices, topology, mass pattern).  Transfers synchronize only for
  *     the consistent-mass solve's convergence checks and when `info` is
  *     requested.

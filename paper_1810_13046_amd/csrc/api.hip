@@ -68,10 +68,10 @@ ibvt_alloc g_alloc{};  // allocator of new handles (null members: hipMallocAsync
 
 // What the freed handles of one GPU leave for the next ones, so that a
 // coupling made for one call (the autograd form without a kept coupling) costs
-// no driver work: device buffers, oldest first and kShelfBytes at most, and a
+// no runtime work: device buffers, oldest first and kShelfBytes at most, and a
 // few second streams with their events and pinned read-back blocks.  On
-// 47,916 tets the driver took 8 ms of such a call's 10.6 for them (HIP's own
-// pools give their memory back to the driver when nothing of them is in use).
+// 47,916 tets the runtime took 8 ms of such a call's 10.6 for them (HIP's own
+// pools give all their memory back when nothing of them is in use).
 // Only coupling_free puts things here, after it has waited for the device, so
 // a taker may use them on any stream; everything is under the mutex.
 // coupling_release_scratch gives all of it back, and so does an allocation
@@ -126,7 +126,7 @@ bool take_buffer(Shelf* h, DevBuf& b, size_t bytes) {
   return true;
 }
 
-// An idle buffer onto the shelf; the oldest ones leave it for the driver.
+// An idle buffer onto the shelf; the oldest ones leave it and are freed.
 void put_buffer(Shelf* h, DevBuf& b) {
   std::lock_guard<std::mutex> g(h->mu);
   size_t out = 0;
@@ -1033,8 +1033,9 @@ int ibvt_profile_read(const char** names, int64_t* launches, double* ms, int max
 
 int coupling_release_scratch(ibvt_coupling* c, hipStream_t stream) {
   if (!c) return set_error(IBVT_E_INVALID, "NULL handle");
-  if (c->dim != 3 || c->unstructured) return IBVT_OK;
   c->stream = stream;
+  clear_shelf(c);
+  if (c->dim != 3 || c->unstructured) return IBVT_OK;
   for (DevBuf* b : {&c->pool, &c->pinfo, &c->rowtmpcol, &c->rowtmpval, &c->rowbox, &c->rowcap,
                     &c->rowtmpoff, &c->tbuf, &c->pscan, &c->mark, &c->rowspilloff,
                     &c->rowspill})
@@ -1045,7 +1046,6 @@ int coupling_release_scratch(ibvt_coupling* c, hipStream_t stream) {
     release(c, c->order);
   }
   c->pool_cap = 0;
-  clear_shelf(c);
   return IBVT_OK;
 }
 

@@ -478,7 +478,6 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BBatch<T> bt) {
   if (threadIdx.x == 0) {
     c.touched[0] = total.touched;
     c.touched[1] = total.full;
-    c.trowptr[total.touched] = c.nnz;
   }
 }
 
@@ -494,6 +493,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_list(BBatch<T> bt) {
     v[k] = bucket_sums(c, b0 + k);
     x.add(v[k]);
   }
+  if (t == 0 && threadIdx.x == 0) c.trowptr[c.touched[0]] = c.nnz;
   BucketSums at = sums_prefix<kBucketThreads>(x, sh, total);
   at.add(c.sum[t]);
 #pragma unroll
@@ -795,10 +795,12 @@ int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** t
   return hip_check(hipGetLastError(), "transpose launch");
 }
 
-// Bucket transpose of the n components in ds; the counts stay on the device
-// (transpose_counting).
+// Bucket transpose of the n components in ds.  The counts stay on the device
+// (transpose_counting), or are waited for before B^dT's rows are allocated:
+// a large operator's bound would be far more than its rows (three bodies of
+// 4.5M tets: 1.2 GB for 1.4M rows), and its wait is short beside its work.
 template <typename T>
-int transpose_buckets(ibvt_coupling* c, const int* ds, int n, const int64_t** touched,
+int transpose_buckets(ibvt_coupling* c, const int* ds, int n, bool wait, const int64_t** touched,
                       hipStream_t s) {
   BBatch<T> b{};
   b.n = n;
@@ -812,10 +814,8 @@ int transpose_buckets(ibvt_coupling* c, const int* ds, int n, const int64_t** to
     const Csr& B = c->B[ds[k]];
     Csr& Bt = c->Bt[ds[k]];
     BOne<T>& o = b.c[k];
-    const int64_t nf = c->n_fluid[ds[k]], rows = std::min<int64_t>(B.nnz, nf);
+    const int64_t nf = c->n_fluid[ds[k]];
     Bt.nnz = B.nnz;
-    if ((st = ensure(c, Bt.rowptr, size_t(rows + 1) * sizeof(int64_t)))) return st;
-    if ((st = ensure(c, Bt.rowmap, size_t(rows + 1) * sizeof(int32_t)))) return st;
     if ((st = ensure(c, Bt.col, size_t(B.nnz + 1) * sizeof(int32_t)))) return st;
     if ((st = ensure(c, Bt.val, size_t(B.nnz + 1) * sizeof(T)))) return st;
     o.rowptr = B.rowptr.template as<int64_t>();
@@ -830,8 +830,6 @@ int transpose_buckets(ibvt_coupling* c, const int* ds, int n, const int64_t** to
     nnz_max = std::max(nnz_max, o.nnz);
     o.touched = c->tcnt.as<int64_t>() + 2 * ds[k];
     touched[ds[k]] = o.touched;
-    o.trowptr = Bt.rowptr.template as<int64_t>();
-    o.rowmap = Bt.rowmap.template as<int32_t>();
     o.tcol = Bt.col.template as<int32_t>();
     o.tval = Bt.val.template as<T>();
     zero_at[k] = zero;
@@ -864,6 +862,19 @@ int transpose_buckets(ibvt_coupling* c, const int* ds, int n, const int64_t** to
   k_bucket_count<T><<<grid, kBucketThreads, 0, s>>>(b, n_rows, per);
   k_bucket_tiles<T><<<unsigned(tiles), kBucketThreads, 0, s>>>(b);
   k_bucket_scan<T><<<un, 1024, 0, s>>>(b);
+  int64_t rows[3];
+  for (int k = 0; k < n; ++k) rows[k] = std::min<int64_t>(b.c[k].nnz, c->n_fluid[ds[k]]);
+  if (wait) {
+    const int64_t* src[3] = {b.c[0].touched, b.c[1].touched, b.c[2].touched};
+    if ((st = read_counts(c, src, n, rows, s))) return st;
+  }
+  for (int k = 0; k < n; ++k) {
+    Csr& Bt = c->Bt[ds[k]];
+    if ((st = ensure(c, Bt.rowptr, size_t(rows[k] + 1) * sizeof(int64_t)))) return st;
+    if ((st = ensure(c, Bt.rowmap, size_t(rows[k] + 1) * sizeof(int32_t)))) return st;
+    b.c[k].trowptr = Bt.rowptr.template as<int64_t>();
+    b.c[k].rowmap = Bt.rowmap.template as<int32_t>();
+  }
   k_bucket_list<T><<<unsigned(tiles), kBucketThreads, 0, s>>>(b);
   k_bucket_scatter<T><<<grid, kBucketThreads, 0, s>>>(b, n_rows, per);
   // (the number of nonempty buckets is on the device: a block for 512
@@ -895,10 +906,10 @@ int transposes(ibvt_coupling* c, int n, const int64_t** touched, hipStream_t s) 
     }
   }
   if (nl && records <= kBatchRecords) {
-    if ((st = transpose_buckets<T>(c, large, nl, touched, s))) return st;
+    if ((st = transpose_buckets<T>(c, large, nl, false, touched, s))) return st;
   } else {
     for (int k = 0; k < nl; ++k)
-      if ((st = transpose_buckets<T>(c, large + k, 1, touched, s))) return st;
+      if ((st = transpose_buckets<T>(c, large + k, 1, true, touched, s))) return st;
   }
   return ns ? transpose_counting<T>(c, small, ns, touched, s) : IBVT_OK;
 }
