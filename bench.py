@@ -73,7 +73,7 @@ POINTS_PER_SUBTET = 11
 CLIP_TRAFFIC = dict(sources_sha256="3800264d4994daa2c74c70a25de4942cd18f307be5a10b65554dee672c5342f0",
                     bytes_mixed=25436929408)
 CLIP_SOURCES = ["paper_1810_13046_amd/csrc/assemble.hip", "paper_1810_13046_amd/csrc/geometry.hpp",
-                "paper_1810_13046_amd/csrc/common.hpp"]
+                "paper_1810_13046_amd/csrc/common.hpp", "paper_1810_13046_amd/csrc/gen_clip_table.py"]
 # HBM traffic of one lumped velocity apply and one force apply (all three
 # components, mixed precision) on the three-body workload, from the same
 # counter passes (profiles/hbm_traffic_three_bodies4.5M_mixed.txt);
