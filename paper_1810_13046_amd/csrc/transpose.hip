@@ -50,11 +50,11 @@ using ValRow = std::conditional_t<std::is_same<T, float>::value, SortVal32, Sort
 constexpr int kKeyLanes = 16;  // lanes per row of B^d in the counting sort's scatter
 
 // Counting sort for small operators, where the bucket path's fixed launches
-// dominate: one component of a launch.  The components share every launch
-// and no count is waited for: bound by launches and the reading of the
-// lattice's counters, 32 us for a 144-tet beam on 32^3 cells, 220 us for 47,916
-// tets on 128^3 and 430 for 200,232 on 192^3, where component by component with
-// marks, two scans and a read-back for each they were 201, 322 and 598.
+// dominate (use_buckets): one component of a launch.  The components share
+// every launch and no count is waited for: bound by launches and the reading
+// of the lattice's counters, 32 us for a 144-tet beam on 32^3 cells, where
+// component by component with marks, two scans and a read-back for each it
+// was 201.
 template <typename T>
 struct TOne {
   const int64_t* rowptr;  // B^d
