@@ -168,10 +168,11 @@ typedef struct {
   int64_t device_bytes;      /* device memory held by the coupling */
   int64_t assemblies;        /* assemblies done on this handle */
   int64_t subtets;           /* sub-tetrahedra integrated by the last
-                                assembly (11 quadrature points each); 0,
-                                like dist_evals and cut_points, where it
-                                integrated the pieces over their boundary
-                                (FP64, tets of at most 6 cells an axis) */
+                                assembly (11 quadrature points each); like
+                                dist_evals and cut_points, of the pieces
+                                it clipped: an FP64 grid assembly
+                                integrates all but flat and wide tets'
+                                pieces over their boundary */
   int64_t piece_store;       /* 1 if every kept piece's moments are stored
                                 for the reverse mode */
   int64_t dist_evals;        /* plane distances evaluated by the last

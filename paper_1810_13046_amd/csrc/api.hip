@@ -365,7 +365,7 @@ void release_csr(ibvt_coupling* c, Csr& m) {
 
 void release_all(ibvt_coupling* c) {
   DevBuf* bufs[] = {&c->lat,      &c->X,         &c->tets,      &c->vt_ptr,    &c->vt_tet,
-                    &c->tetvol,   &c->tetrec,    &c->rng,       &c->pmom,      &c->cnt,
+                    &c->tetvol,   &c->tetrec,    &c->rng,       &c->pmom,      &c->cnt,       &c->clipped,
                     &c->pair_off, &c->owner,     &c->pval,      &c->keep,      &c->rownnz,
                     &c->mark,     &c->tcnt,      &c->tbuf,      &c->mlump,     &c->minv,
                     &c->Mval32,   &c->Mdiag_inv, &c->flags_dev, &c->counters,  &c->scan_tmp,

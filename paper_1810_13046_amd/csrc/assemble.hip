@@ -10,7 +10,7 @@
 //                  order (key: the cell planes the tet straddles, in
 //                  classes by cut count: vertex slots 10, 12, 16), counted
 //                  and placed per (tet, key) group from the cell ranges.
-//  k_pieces        (FP64, tets of at most kOctantCells cells per axis) the
+//  k_pieces        (FP64, the items within the limits of moments.hpp) the
 //                  pieces' moments and the 32 values ∫ λ_i N_j per pair from
 //                  boundary integrals, without clipped polyhedra; the
 //                  order, k_clip and k_integrate serve the others.
@@ -149,14 +149,17 @@ __global__ void k_mass_pattern(int64_t n_v, const int64_t* __restrict__ vt_ptr,
 // per-tet preparation
 // ---------------------------------------------------------------------------
 
+// clipped (or null): set for the (component, tet) items whose pieces are
+// clipped, not integrated over their boundary (moments.hpp).
 __global__ void k_tet_prep(int64_t n_t, const double* __restrict__ X,
                            const int32_t* __restrict__ tets, const double* __restrict__ lat,
                            LatDesc ld, double* __restrict__ tetvol, CellRange* __restrict__ rng,
                            int64_t* __restrict__ cnt, double* __restrict__ tetrec,
-                           double* __restrict__ tetgrad, unsigned* flags,
-                           unsigned long long* counters) {
+                           double* __restrict__ tetgrad, uint8_t* __restrict__ clipped,
+                           unsigned* flags, unsigned long long* counters) {
   const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  bool zero = false, wide = false;
+  bool zero = false;
+  uint32_t to_clip = 0;  // pairs of the items marked in `clipped`
   if (t < n_t) {
     double P[4][3];
     bool finite = true;
@@ -182,6 +185,7 @@ __global__ void k_tet_prep(int64_t n_t, const double* __restrict__ X,
                        a[2] * (b[0] * c[1] - b[1] * c[0]);
     const double vol = fabs(det) / 6.0;
     tetvol[t] = finite ? vol : 0.0;
+    double range;
     {
       TetGeom G;
       for (int k = 0; k < 4; ++k)
@@ -194,6 +198,7 @@ __global__ void k_tet_prep(int64_t n_t, const double* __restrict__ X,
       for (int k = 0; k < 4; ++k)
         for (int e = 0; e < 3; ++e) g[3 * k + e] = G.g[k][e];
       store_row<12>(tetgrad + t * 12, g);
+      range = hat_range(G.g, mn, mx);
     }
     zero = finite && (vol == 0.0);
     if (!finite) atomicOr(flags, kFlagNonFinite);
@@ -221,13 +226,19 @@ __global__ void k_tet_prep(int64_t n_t, const double* __restrict__ X,
       rng[d * n_t + t] = r;
       cnt[d * n_t + t] = int64_t(r.n[0]) * r.n[1] * r.n[2];
       if (int64_t(r.n[0]) * r.n[1] * r.n[2] > kMaxTetCells) atomicOr(flags, kFlagTetSpan);
-      wide |= ok && max(r.n[0], max(r.n[1], r.n[2])) > kOctantCells;
+      if (clipped) {
+        const bool cl = max(r.n[0], max(r.n[1], r.n[2])) > kOctantCells || !(range <= kOctantRange);
+        clipped[d * n_t + t] = cl ? 1 : 0;
+        if (cl) to_clip += uint32_t(r.n[0]) * uint32_t(r.n[1]) * uint32_t(r.n[2]);
+      }
     }
   }
   const uint64_t zm = ballot64(zero);
-  const uint64_t wm = ballot64(wide);
   if (lane_id() == 0 && zm) atomicAdd(&counters[kCntZeroTets], (unsigned long long)popc64(zm));
-  if (lane_id() == 0 && wm) atomicAdd(&counters[kCntWide], (unsigned long long)popc64(wm));
+  if (clipped) {
+    const unsigned long long n = wave_sum((unsigned long long)to_clip);
+    if (lane_id() == 0 && n) atomicAdd(&counters[kCntToClip], n);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -255,6 +266,7 @@ __global__ void k_tet_prep(int64_t n_t, const double* __restrict__ X,
 //                    pair alone) and writes the groups' descriptors
 //                    (pair_desc's fields), and the owner (the item's index)
 //                    of each of its pairs.
+// Items not marked in `clipped` (null: all are clipped) are left out.
 constexpr int kOrderItems = 256;
 
 struct AxisRuns {
@@ -285,13 +297,14 @@ __device__ __forceinline__ int order_key(int pattern) {
 
 __global__ __launch_bounds__(kOrderItems) void k_order_count(int64_t tc0, int64_t n_items,
                                                              const CellRange* __restrict__ rng,
+                                                             const uint8_t* __restrict__ clipped,
                                                              int32_t* __restrict__ hist) {
   __shared__ int32_t h[256];
   const int64_t nb = gridDim.x;
   h[threadIdx.x] = 0;
   __syncthreads();
   const int64_t w = int64_t(blockIdx.x) * kOrderItems + threadIdx.x;
-  if (w < n_items) {
+  if (w < n_items && (!clipped || clipped[tc0 + w])) {
     const CellRange r = rng[tc0 + w];
     if (int64_t(r.n[0]) * r.n[1] * r.n[2] > 0) {
       const AxisRuns ax = axis_runs(r.n[0]), ay = axis_runs(r.n[1]), az = axis_runs(r.n[2]);
@@ -310,7 +323,8 @@ __global__ __launch_bounds__(kOrderItems) void k_order_count(int64_t tc0, int64_
 
 __global__ __launch_bounds__(kOrderItems) void k_order_scatter(
     int64_t tc0, int64_t n_items, int64_t n_t, const CellRange* __restrict__ rng,
-    const int64_t* __restrict__ pair_off, const int64_t* __restrict__ first,
+    const uint8_t* __restrict__ clipped, const int64_t* __restrict__ pair_off,
+    const int64_t* __restrict__ first,
     PairDesc* __restrict__ order, int32_t* __restrict__ owner) {
   __shared__ unsigned long long cur[256];
   const int64_t nb = gridDim.x;
@@ -319,6 +333,7 @@ __global__ __launch_bounds__(kOrderItems) void k_order_scatter(
   const int64_t w = int64_t(blockIdx.x) * kOrderItems + threadIdx.x;
   if (w >= n_items) return;
   const int64_t tc = tc0 + w;
+  if (clipped && !clipped[tc]) return;
   const CellRange r = rng[tc];
   if (int64_t(r.n[0]) * r.n[1] * r.n[2] == 0) return;
   const int d = (tc >= n_t) + (tc >= 2 * n_t);
@@ -511,22 +526,24 @@ __device__ __forceinline__ int owner_lane(int excl, int s) {
 // turns its pair's moments into the 4 x 8 values ∫ λ_i N_j, written to
 // pval[i][pair - p_begin][j] (the chunk's pairs only; local-vertex major:
 // each vertex row of a pair is 8 contiguous values, planes of plane_pairs
-// pairs).
+// pairs).  Pairs of items not marked in `clipped` (null: all are) are passed by.
 template <typename T>
 __global__ __launch_bounds__(kWave) void k_integrate(
     int64_t plane_pairs, int64_t p_begin, int64_t p_end, int64_t n_t,
-    const uint64_t* __restrict__ pinfo, const T* __restrict__ pool,
-    const int32_t* __restrict__ owner, const int64_t* __restrict__ pair_off,
-    const CellRange* __restrict__ rng, const double* __restrict__ tetrec,
-    const double* __restrict__ lat, LatDesc ld, uint8_t* __restrict__ keep,
-    T* __restrict__ pval, T* __restrict__ pmom, int dual) {
+    const uint8_t* __restrict__ clipped, const uint64_t* __restrict__ pinfo,
+    const T* __restrict__ pool, const int32_t* __restrict__ owner,
+    const int64_t* __restrict__ pair_off, const CellRange* __restrict__ rng,
+    const double* __restrict__ tetrec, const double* __restrict__ lat, LatDesc ld,
+    uint8_t* __restrict__ keep, T* __restrict__ pval, T* __restrict__ pmom, int dual) {
   __shared__ __align__(16) T red[kWave][kMomLds];  // a record's moments per row, padded
   const int lane = threadIdx.x;
   const int64_t g0 = p_begin + int64_t(blockIdx.x) * kWave;
   const int64_t pj = g0 + lane;
   int cnt = 0;
   int64_t beg = 0;
-  if (pj < p_end) {
+  const bool mine = pj < p_end && (!clipped || clipped[owner[pj]]);
+  if (clipped && ballot64(mine) == 0) return;  // (the block is one wave)
+  if (mine) {
     const uint64_t pi = pinfo[pj];
     cnt = int(pi & 0xff);
     beg = int64_t(pi >> 8);
@@ -658,18 +675,19 @@ __device__ __forceinline__ int small_div(int q, int n) {
 // Octant terms of a candidate pair, 0 if the cell surely misses the tet: a
 // barycentric coordinate is negative on all of the cell's part of the tet's
 // box.  The coordinates are affine with gradients good to about κ² ulps, κ =
-// box volume / |det|, so the test is left out for flat tets (κ > 256) and
-// asks for a margin of 1e-8 (far above κ² ulps; what it lets through is
-// integrated and dropped by its volume).
+// box volume / |det|, which is at most kOctantRange³ here (the determinant
+// of the gradients times the box's sides, and each of them sums to at most
+// kOctantRange), so the test asks for a margin of 1e-8 (far above κ² ulps;
+// what it lets through is integrated and dropped by its volume).
 __device__ __forceinline__ int candidate_terms(const PairPlace& o, const double* tetrec,
-                                               const double* tetgrad, const double* tetvol,
-                                               const double* lat, const LatDesc& ld, int& cuts) {
+                                               const double* tetgrad, const double* lat,
+                                               const LatDesc& ld, int& cuts) {
   double rec[kTetRec], g[12];
   load_row<kTetRec>(tetrec + o.t * kTetRec, rec);
   load_row<12>(tetgrad + o.t * 12, g);
   int terms = 1;
   cuts = 0;
-  double top[4] = {1.0, 0.0, 0.0, 0.0}, box = 1.0;
+  double top[4] = {1.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
     const double* L = lat + lattice_offset(ld, o.d, e) + o.r.lo[e] + o.k[e];
@@ -677,14 +695,13 @@ __device__ __forceinline__ int candidate_terms(const PairPlace& o, const double*
     const double mx = fmax(fmax(rec[e], rec[3 + e]), fmax(rec[6 + e], rec[9 + e]));
     const double a = fmax(mn, L[0]) - rec[e];
     const double b = fmin(mx, L[1]) - rec[e];
-    box *= mx - mn;
 #pragma unroll
     for (int i = 0; i < 4; ++i) top[i] += fmax(g[3 * i + e] * a, g[3 * i + e] * b);
     terms <<= axis_two(o.k[e], o.r.n[e]) ? 1 : 0;
     cuts += (o.k[e] > 0) + (o.k[e] < o.r.n[e] - 1);
   }
   const double least = fmin(fmin(top[0], top[1]), fmin(top[2], top[3]));
-  return least < -1e-8 && box <= 256.0 * 6.0 * tetvol[o.t] ? 0 : terms;
+  return least < -1e-8 ? 0 : terms;
 }
 
 // A queued octant term: its pair relative to the block's first (11 bits),
@@ -726,8 +743,8 @@ __device__ __forceinline__ void store_stage(const double* stage, const int rel[8
   wave_lds_sync();
 }
 
-// (II)-(III) of the FP64 couplings whose tets span at most kOctantCells
-// cells per axis.  One wave per `range` candidate pairs: 64 candidates at a
+// (II)-(III) of an FP64 coupling's items that are not marked in `clipped`
+// (null: none is).  One wave per `range` candidate pairs: 64 candidates at a
 // time are tested against the tet's faces, the octant terms of those left
 // are queued, and whole batches of 64 terms are integrated, one lane each
 // (moments.hpp), so the lanes stay filled (94 % of them active) although a
@@ -744,11 +761,12 @@ __device__ __forceinline__ void store_stage(const double* stage, const int rel[8
 // stores of 16 bytes a lane to lines of their own take 0.4 ms more.
 __global__ __launch_bounds__(kWave, 2) void k_pieces(
     int64_t plane_pairs, int64_t p_begin, int64_t p_end, int range, int64_t n_t,
-    const int32_t* __restrict__ owner, const int64_t* __restrict__ pair_off,
-    const CellRange* __restrict__ rng, const double* __restrict__ tetrec,
-    const double* __restrict__ tetgrad, const double* __restrict__ tetvol,
-    const double* __restrict__ lat, LatDesc ld, double drop_rel, uint8_t* __restrict__ keep,
-    double* __restrict__ pval, double* __restrict__ pmom, int dual, unsigned long long* counters) {
+    const uint8_t* __restrict__ clipped, const int32_t* __restrict__ owner,
+    const int64_t* __restrict__ pair_off, const CellRange* __restrict__ rng,
+    const double* __restrict__ tetrec, const double* __restrict__ tetgrad,
+    const double* __restrict__ tetvol, const double* __restrict__ lat, LatDesc ld,
+    double drop_rel, uint8_t* __restrict__ keep, double* __restrict__ pval,
+    double* __restrict__ pmom, int dual, unsigned long long* counters) {
   constexpr int kQueue = 9 * kWave;
   // rows 0..11: the tet in octant coordinates; 12..17: the octant's signs
   // and shifts (here while the faces need the registers); then the stage
@@ -769,15 +787,18 @@ __global__ __launch_bounds__(kWave, 2) void k_pieces(
       PairPlace o;
       if (p < b1) {
         pair_item(p, n_t, owner, rng, o);
-        const int q = int(p - pair_off[int64_t(o.d) * n_t + o.t]);
-        const int qy = small_div(q, o.r.n[0]), qz = small_div(qy, o.r.n[1]);
-        o.k[0] = q - qy * o.r.n[0];
-        o.k[1] = qy - qz * o.r.n[1];
-        o.k[2] = qz;
-        int cuts;
-        terms = candidate_terms(o, tetrec, tetgrad, tetvol, lat, ld, cuts);
-        if (terms == 0) keep[p] = 0;
-        else np += unsigned(cuts);
+        const int64_t tc = int64_t(o.d) * n_t + o.t;
+        if (!clipped || !clipped[tc]) {
+          const int q = int(p - pair_off[tc]);
+          const int qy = small_div(q, o.r.n[0]), qz = small_div(qy, o.r.n[1]);
+          o.k[0] = q - qy * o.r.n[0];
+          o.k[1] = qy - qz * o.r.n[1];
+          o.k[2] = qz;
+          int cuts;
+          terms = candidate_terms(o, tetrec, tetgrad, lat, ld, cuts);
+          if (terms == 0) keep[p] = 0;
+          else np += unsigned(cuts);
+        }
       }
       int incl = terms;
       for (int o2 = 1; o2 < kWave; o2 <<= 1) {
@@ -854,7 +875,7 @@ __global__ __launch_bounds__(kWave, 2) void k_pieces(
       for (int k = 0; k < kMom; ++k) M[k] = fma(on, __shfl_down(M[k], j, kWave), M[k]);
     }
     // the pair again (read again: kept through the faces it would cost
-    // registers the third wave needs)
+    // registers, and two waves a SIMD leave none)
     uint32_t e2 = e;
     asm volatile("" : "+v"(e2));
     PairPlace o;
@@ -887,10 +908,12 @@ __global__ __launch_bounds__(kWave, 2) void k_pieces(
     }
     const double vol = M[0] * cv;
     const bool lead = active && term == 0;
-    const bool kp = lead && vol > drop_rel * tetvol[o.t];
+    const double tv = tetvol[o.t];
+    const bool kp = lead && vol > drop_rel * tv;
     if (lead) keep[p] = kp ? 1 : 0;
     nk += kp ? 1 : 0;
-    nd += lead && !kp && vol > 0.0 ? 1 : 0;
+    // (below a tenth of that a volume may be the roundings of an empty cell)
+    nd += lead && !kp && vol > 0.1 * drop_rel * tv ? 1 : 0;
     const uint64_t rows = ballot64(kp);
     double* stage = lds;
     int rel[8];
@@ -1476,14 +1499,19 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
   if ((st = hip_check(hipMemsetAsync(counters, 0, kCntSlots * sizeof(unsigned long long), s),
                       "memset")))
     return st;
+  // FP64 items are marked for the clip or for the boundary integrals
+  uint8_t* to_clip = nullptr;
+  if (sizeof(T) == sizeof(double) && !c->matrix_free) {
+    if ((st = ensure(c, c->clipped, size_t(3 * n_t + 1)))) return st;
+    to_clip = c->clipped.as<uint8_t>();
+  }
   // (I) overlap candidates
   {
     ProfScope ps("tet_prep", s);
   k_tet_prep<<<blocks_for(n_t, 256), 256, 0, s>>>(
       n_t, c->X.as<double>(), c->tets.as<int32_t>(), c->lat.as<double>(), c->ld,
       c->tetvol.as<double>(), c->rng.as<CellRange>(), c->cnt.as<int64_t>(), c->tetrec.as<double>(),
-      c->tetgrad.as<double>(),
-      flags, counters);
+      c->tetgrad.as<double>(), to_clip, flags, counters);
   }
   if ((st = hip_check(hipGetLastError(), "prep launch"))) return st;
   if ((st = scan_i64(c, c->cnt.as<int64_t>(), c->pair_off.as<int64_t>(), 3 * n_t, s))) return st;
@@ -1526,7 +1554,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     }
   }
   // read-back 1: the chunks' first pairs (the last entry is the pair count),
-  // the row scratch size, the wide tets, the spill size, and status flags
+  // the row scratch size, the pairs to clip, the spill size, and status flags
   int64_t pat[kMaxChunks + 4];
   {
     const int64_t* src[kMaxChunks + 4];
@@ -1534,7 +1562,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     int nsrc = nchunk + 1;
     if (!c->matrix_free) {
       src[nsrc++] = c->rowtmpoff.as<int64_t>() + 3 * n_v;
-      src[nsrc++] = reinterpret_cast<const int64_t*>(counters + kCntWide);
+      src[nsrc++] = reinterpret_cast<const int64_t*>(counters + kCntToClip);
       if (nchunk > 1) src[nsrc++] = c->rowspilloff.as<int64_t>() + 3 * n_v;
     }
     if ((st = read_counts(c, src, nsrc, pat, s))) return st;
@@ -1546,13 +1574,15 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
   c->n_pairs = n_pairs;
   if (c->matrix_free) return finish_matfree<T>(c, s);
   const int64_t tmp_total = pat[nchunk + 1], spill_total = nchunk > 1 ? pat[nchunk + 3] : 0;
-  // Boundary integrals (k_pieces) or clipping: FP64 couplings whose tets are
-  // all small enough for the octants' accuracy (kOctantCells) take the
-  // former, 17.3 ms against 41 on the three-body mesh and 0.37 against 1.3 on
-  // 47,916 tets.  Mixed couplings keep the clip: their moments are float
-  // sums over its sub-tetrahedra, and their results are to stay what they
-  // are to the last bit (the octants' would differ by float roundings).
-  const bool octants = sizeof(T) == sizeof(double) && pat[nchunk + 2] == 0;
+  // Boundary integrals (k_pieces) or clipping: the items of an FP64 coupling
+  // within the limits of moments.hpp take the former (17.3 ms against 41 on
+  // the three-body mesh, 0.37 against 1.3 on 47,916 tets), the others are
+  // clipped, each into its own pairs' places.  Mixed couplings are clipped
+  // throughout: their moments are float sums over the sub-tetrahedra, and a
+  // program that keeps its results keeps the same ones to the last bit.
+  const int64_t clip_pairs = to_clip ? pat[nchunk + 2] : n_pairs;
+  const bool clips = clip_pairs > 0, octants = clip_pairs < n_pairs;
+  if (!octants) to_clip = nullptr;  // all items
   int64_t chunk_max = 0;
   for (int k = 0; k < nchunk; ++k) chunk_max = std::max(chunk_max, pat[k + 1] - pat[k]);
   if ((st = ensure(c, c->owner, size_t(n_pairs + 1) * sizeof(int32_t)))) return st;
@@ -1596,7 +1626,6 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     }
     return scan_i64_rows(c, c->rownnz.as<int64_t>(), out, 3, n_v, s);
   };
-  int64_t nnzs[3] = {-1, -1, -1};
   // the solid masses need only the tet volumes: on the second stream beside
   // the first chunk's pieces, joined after them
   auto fork_masses = [&]() -> int {
@@ -1604,44 +1633,13 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     masses_done = true;
     return solid_masses(c, c->side.stream);
   };
-  if constexpr (sizeof(T) == sizeof(double)) if (octants && n_pairs > 0) {
-    // (II)-(III) every piece from its boundary integrals
-    k_owner<<<blocks_for(n_tc, 256), 256, 0, s>>>(n_tc, c->pair_off.as<int64_t>(),
-                                                  c->owner.as<int32_t>());
-    if ((st = hip_check(hipGetLastError(), "owner launch"))) return st;
-    for (int ch = 0; ch < nchunk; ++ch) {
-      const int64_t p0 = pat[ch], nc = pat[ch + 1] - pat[ch];
-      if (nc == 0) continue;
-      const bool fork = !masses_done;
-      if (fork) {
-        if ((st = hip_check(hipEventRecord(c->side.fork, s), "event")) ||
-            (st = hip_check(hipStreamWaitEvent(c->side.stream, c->side.fork, 0), "stream wait")) ||
-            (st = fork_masses()) ||
-            (st = hip_check(hipEventRecord(c->side.join, c->side.stream), "event")))
-          return st;
-      }
-      {
-        ProfScope ps("pieces", s);
-        // candidates per block: about eight rounds of the resident waves, at
-        // most kPieceRange (a block's last, partly filled batch then weighs
-        // little), at least one batch
-        const int64_t range = std::min<int64_t>(
-            kPieceRange, std::max<int64_t>(1, nc / (16384 * kWave)) * kWave);
-        k_pieces<<<dim3(unsigned(ceil_div(nc, range))), kWave, 0, s>>>(
-            chunk_max, p0, p0 + nc, int(range), n_t, c->owner.as<int32_t>(),
-            c->pair_off.as<int64_t>(), c->rng.as<CellRange>(), c->tetrec.as<double>(),
-            c->tetgrad.as<double>(), c->tetvol.as<double>(), c->lat.as<double>(), c->ld, 1e-14,
-            c->keep.as<uint8_t>(), c->pval.as<T>(), c->pmom.as<T>(), c->dual ? 1 : 0, counters);
-      }
-      if ((st = hip_check(hipGetLastError(), "pieces launch"))) return st;
-      if (fork && (st = hip_check(hipStreamWaitEvent(s, c->side.join, 0), "stream wait"))) return st;
-      if ((st = gather_rows(ch))) return st;
-    }
-  }
-  if (!octants) {
+  int32_t* ohist = nullptr;
+  int64_t* ofirst = nullptr;
+  const int64_t clip_max = std::min(chunk_max, clip_pairs);  // most pairs a chunk clips
+  if (clips) {
     if ((st = ensure(c, c->pinfo, size_t(n_pairs + 1) * sizeof(uint64_t)))) return st;
     // the clip order of one chunk at a time, as pair descriptors
-    if ((st = ensure(c, c->order, size_t(chunk_max + 1) * sizeof(PairDesc)))) return st;
+    if ((st = ensure(c, c->order, size_t(clip_max + 1) * sizeof(PairDesc)))) return st;
     // per chunk: the pair descriptors in clip order (k_order_count, scan,
     // k_order_scatter); the scanned key counts give the clip launches their
     // class stretches on the device
@@ -1650,15 +1648,49 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     const int64_t ob_max = ceil_div(items_max, kOrderItems);
     const size_t hb = (size_t(256 * ob_max) * sizeof(int32_t) + 255) & ~size_t(255);
     if ((st = ensure(c, c->pscan, hb + size_t(256 * ob_max + 1) * sizeof(int64_t)))) return st;
-    int32_t* ohist = c->pscan.as<int32_t>();
-    int64_t* ofirst = reinterpret_cast<int64_t*>(c->pscan.as<char>() + hb);
+    ohist = c->pscan.as<int32_t>();
+    ofirst = reinterpret_cast<int64_t*>(c->pscan.as<char>() + hb);
+  }
+  if (octants) {
+    k_owner<<<blocks_for(n_tc, 256), 256, 0, s>>>(n_tc, c->pair_off.as<int64_t>(),
+                                                  c->owner.as<int32_t>());
+    if ((st = hip_check(hipGetLastError(), "owner launch"))) return st;
+  }
+  // Chunks with pairs, in order.  Per chunk: the clip's classes 12 and 16
+  // run on the side stream beside class 10 (they fill its tail), and the
+  // next chunk's pair order is made on the side stream while this chunk
+  // integrates (the order and the sort scratch are free once the clip has
+  // read them; the store is reused only after the integration).
+  int live[kMaxChunks];
+  int n_live = 0;
+  for (int ch = 0; ch < nchunk; ++ch)
+    if (pat[ch + 1] > pat[ch]) live[n_live++] = ch;
+  auto order_chunk = [&](int ch, hipStream_t q) -> int {
+    // the next chunk's order runs beside the integration: its span is
+    // shared with it
+    ProfScope ps(q == s ? "pair_order" : "pair_order_beside_integrate", q);
+    const int64_t tc0 = tc_at[ch], items = tc_at[ch + 1] - tc_at[ch];
+    const int64_t ob = ceil_div(items, kOrderItems);
+    k_order_count<<<unsigned(ob), kOrderItems, 0, q>>>(tc0, items, c->rng.as<CellRange>(), to_clip,
+                                                       ohist);
+    int r = hip_check(hipGetLastError(), "order count launch");
+    if (r) return r;
+    if ((r = scan_i32_to_i64(c, ohist, ofirst, 256 * ob, q))) return r;
+    k_order_scatter<<<unsigned(ob), kOrderItems, 0, q>>>(
+        tc0, items, n_t, c->rng.as<CellRange>(), to_clip, c->pair_off.as<int64_t>(), ofirst,
+        c->order.as<PairDesc>(), c->owner.as<int32_t>());
+    return hip_check(hipGetLastError(), "order scatter launch");
+  };
+  int64_t nnzs[3];
   for (int attempt = 0; attempt < 2; ++attempt) {
-    const int64_t want = std::max<int64_t>(int64_t(3.25 * double(chunk_max)) + 1024,
-                                           c->pool_needed + c->pool_needed / 32 + 1024);
-    if (int64_t(c->pool.cap / (kRecord * sizeof(T))) < want &&
-        (st = ensure(c, c->pool, size_t(want) * kRecord * sizeof(T))))
-      return st;
-    c->pool_cap = int64_t(c->pool.cap / (kRecord * sizeof(T)));
+    if (clips) {
+      const int64_t want = std::max<int64_t>(int64_t(3.25 * double(clip_max)) + 1024,
+                                             c->pool_needed + c->pool_needed / 32 + 1024);
+      if (int64_t(c->pool.cap / (kRecord * sizeof(T))) < want &&
+          (st = ensure(c, c->pool, size_t(want) * kRecord * sizeof(T))))
+        return st;
+      c->pool_cap = int64_t(c->pool.cap / (kRecord * sizeof(T)));
+    }
     // again: clear the clip's counters (the zero-tet count of the preparation
     // stays)
     if (attempt > 0) {
@@ -1672,45 +1704,23 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
                           "memset")))
         return st;
     }
-    // Chunks with pairs, in order.  Per chunk: the clip's classes 12 and 16
-    // run on the side stream beside class 10 (they fill its tail), and the
-    // next chunk's pair order is made on the side stream while this chunk
-    // integrates (the order and the sort scratch are free once the clip has
-    // read them; the store is reused only after the integration).
-    int live[kMaxChunks];
-    int n_live = 0;
-    for (int ch = 0; ch < nchunk; ++ch)
-      if (pat[ch + 1] > pat[ch]) live[n_live++] = ch;
-    auto order_chunk = [&](int ch, hipStream_t q) -> int {
-      // the next chunk's order runs beside the integration: its span is
-      // shared with it
-      ProfScope ps(q == s ? "pair_order" : "pair_order_beside_integrate", q);
-      const int64_t tc0 = tc_at[ch], items = tc_at[ch + 1] - tc_at[ch];
-      const int64_t ob = ceil_div(items, kOrderItems);
-      k_order_count<<<unsigned(ob), kOrderItems, 0, q>>>(tc0, items, c->rng.as<CellRange>(), ohist);
-      int r = hip_check(hipGetLastError(), "order count launch");
-      if (r) return r;
-      if ((r = scan_i32_to_i64(c, ohist, ofirst, 256 * ob, q))) return r;
-      k_order_scatter<<<unsigned(ob), kOrderItems, 0, q>>>(
-          tc0, items, n_t, c->rng.as<CellRange>(), c->pair_off.as<int64_t>(), ofirst,
-          c->order.as<PairDesc>(), c->owner.as<int32_t>());
-      return hip_check(hipGetLastError(), "order scatter launch");
-    };
-    if (n_live > 0 && (st = order_chunk(live[0], s))) return st;
+    if (clips && n_live > 0 && (st = order_chunk(live[0], s))) return st;
     for (int li = 0; li < n_live; ++li) {
       const int ch = live[li];
       const int64_t p0 = pat[ch], nc = pat[ch + 1] - pat[ch];
       const int64_t* cls_start = ofirst;  // key-major: class k starts at 64 k blocks
       const int64_t ntiles = ceil_div(tc_at[ch + 1] - tc_at[ch], kOrderItems);
-      {
+      const bool fork = clips || !masses_done;
+      if (fork && ((st = hip_check(hipEventRecord(c->side.fork, s), "event")) ||
+                   (st = hip_check(hipStreamWaitEvent(c->side.stream, c->side.fork, 0),
+                                   "stream wait")) ||
+                   (st = fork_masses())))
+        return st;
+      if (clips) {
         // (II) clip the chunk's pairs, one launch per cut class (fewer vertex
         // slots per lane, more resident waves); each launch reads its
         // class's stretch of the order from the prefix sum of the key counts
         ProfScope ps("clip", s);
-        if ((st = hip_check(hipEventRecord(c->side.fork, s), "event")) ||
-            (st = hip_check(hipStreamWaitEvent(c->side.stream, c->side.fork, 0), "stream wait")))
-          return st;
-        if ((st = fork_masses())) return st;
         ClipTables tab;
         if ((st = clip_tables(tab))) return st;
         for (int k = 2; k >= 0; --k) {
@@ -1718,9 +1728,9 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
           const int resident =
               k == 0 ? resident_blocks(k_clip<T, 10>)
                      : (k == 1 ? resident_blocks(k_clip<T, 12>) : resident_blocks(k_clip<T, kMaxV>));
-          const int64_t nb = std::min<int64_t>(ceil_div(nc, kWave), resident);
+          const int64_t nb = std::min<int64_t>(ceil_div(std::min(nc, clip_pairs), kWave), resident);
 #define IBVT_CLIP_ARGS                                                                          \
-  tab, cls_start + 64 * k * ntiles, cls_start + 64 * (k + 1) * ntiles, c->order.as<PairDesc>(),    \
+  tab, cls_start + 64 * k * ntiles, cls_start + 64 * (k + 1) * ntiles, c->order.as<PairDesc>(), \
       c->tetrec.as<double>(), c->lat.as<double>(), c->ld, 1e-14, c->pool.as<T>(), c->pool_cap,  \
       c->pinfo.as<uint64_t>(), counters + kCntChunkPool + ch, flags, counters
           if (k == 0) k_clip<T, 10><<<dim3(unsigned(nb)), kWave, 0, ks>>>(IBVT_CLIP_ARGS);
@@ -1729,11 +1739,29 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
 #undef IBVT_CLIP_ARGS
         }
         if ((st = hip_check(hipGetLastError(), "clip launch"))) return st;
-        if ((st = hip_check(hipEventRecord(c->side.join, c->side.stream), "event")) ||
-            (st = hip_check(hipStreamWaitEvent(s, c->side.join, 0), "stream wait")))
-          return st;
       }
-      const bool next = li + 1 < n_live;
+      if constexpr (sizeof(T) == sizeof(double)) {
+        if (octants) {
+          // (II)-(III) the other pairs' pieces from their boundary integrals
+          ProfScope ps("pieces", s);
+          // candidates per block: about eight rounds of the resident waves, at
+          // most kPieceRange (a block's last, partly filled batch then weighs
+          // little), at least one batch
+          const int64_t range = std::min<int64_t>(
+              kPieceRange, std::max<int64_t>(1, nc / (16384 * kWave)) * kWave);
+          k_pieces<<<dim3(unsigned(ceil_div(nc, range))), kWave, 0, s>>>(
+              chunk_max, p0, p0 + nc, int(range), n_t, clips ? to_clip : nullptr,
+              c->owner.as<int32_t>(), c->pair_off.as<int64_t>(), c->rng.as<CellRange>(),
+              c->tetrec.as<double>(), c->tetgrad.as<double>(), c->tetvol.as<double>(),
+              c->lat.as<double>(), c->ld, 1e-14, c->keep.as<uint8_t>(), c->pval.as<T>(),
+              c->pmom.as<T>(), c->dual ? 1 : 0, counters);
+          if ((st = hip_check(hipGetLastError(), "pieces launch"))) return st;
+        }
+      }
+      if (fork && ((st = hip_check(hipEventRecord(c->side.join, c->side.stream), "event")) ||
+                   (st = hip_check(hipStreamWaitEvent(s, c->side.join, 0), "stream wait"))))
+        return st;
+      const bool next = clips && li + 1 < n_live;
       if (next) {
         if ((st = hip_check(hipEventRecord(c->side.fork, s), "event")) ||
             (st = hip_check(hipStreamWaitEvent(c->side.stream, c->side.fork, 0), "stream wait")) ||
@@ -1741,22 +1769,21 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
             (st = hip_check(hipEventRecord(c->side.sorted, c->side.stream), "event")))
           return st;
       }
-      {
+      if (clips) {
         // (III) integrate the chunk's sub-tetrahedra, summed per pair (pairs
         // whose records did not fit the store read as empty)
         ProfScope ps("integrate", s);
         k_integrate<T><<<dim3(unsigned(ceil_div(nc, kWave))), kWave, 0, s>>>(
-            chunk_max, p0, p0 + nc, n_t, c->pinfo.as<uint64_t>(), c->pool.as<T>(),
+            chunk_max, p0, p0 + nc, n_t, to_clip, c->pinfo.as<uint64_t>(), c->pool.as<T>(),
             c->owner.as<int32_t>(), c->pair_off.as<int64_t>(), c->rng.as<CellRange>(),
             c->tetrec.as<double>(), c->lat.as<double>(), c->ld, c->keep.as<uint8_t>(),
             c->pval.as<T>(), c->pmom.as<T>(), c->dual ? 1 : 0);
+        if ((st = hip_check(hipGetLastError(), "integrate launch"))) return st;
       }
-      if ((st = hip_check(hipGetLastError(), "integrate launch"))) return st;
       if ((st = gather_rows(ch))) return st;
       if (next && (st = hip_check(hipStreamWaitEvent(s, c->side.sorted, 0), "stream wait")))
         return st;
     }
-
     // read-back 2: records each chunk asked for, nonzeros of the three
     // components, flags
     if ((st = count_rows())) return st;
@@ -1775,15 +1802,7 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
     if (c->pool_needed <= c->pool_cap) break;
     if (attempt == 1) return set_error(IBVT_E_CAPACITY, "piece store could not be sized");
   }
-  }
   // (IV) global assembly: rows of B^d (gathered per chunk above)
-  if (nnzs[0] < 0) {
-    if ((st = count_rows())) return st;
-    const int64_t* src[3] = {c->B[0].rowptr.as<int64_t>() + n_v, c->B[1].rowptr.as<int64_t>() + n_v,
-                             c->B[2].rowptr.as<int64_t>() + n_v};
-    if ((st = read_counts(c, src, 3, nnzs, s))) return st;
-    if ((st = flags_status(c->host_flags))) return st;
-  }
   for (int d = 0; d < 3; ++d) {
     const int64_t nnz = nnzs[d];
     c->B[d].nnz = nnz;

@@ -23,7 +23,7 @@ enum Counter : int {
   kCntDropped = 1,
   kCntZeroTets = 2,
   kCntSubtets = 3,
-  kCntWide = 4,  // tets wider than the octant integration takes
+  kCntToClip = 4,  // pairs of the items that the octant integration leaves to the clip
   kCntUnused5 = 5,  // 5, 6, 7: unused
   kCntDist = 8,   // signed distances evaluated by the clip
   kCntCutPts = 9, // cut points made by the clip

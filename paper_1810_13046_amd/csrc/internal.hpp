@@ -162,6 +162,7 @@ struct ibvt_coupling {
   bool fvol_ready = false;
   ibvt::DevBuf rng;          // CellRange 3*n_tet
   ibvt::DevBuf cnt;          // int64 3*n_tet
+  ibvt::DevBuf clipped;      // uint8 3*n_tet: items whose pieces are clipped (FP64 grid)
   ibvt::DevBuf pair_off;     // int64 3*n_tet + 1
   int64_t n_pairs = 0;
   ibvt::DevBuf owner;        // int32 n_pairs

@@ -295,11 +295,10 @@ __host__ __device__ __forceinline__ void centre_moments(double M[kMom], const do
 // cell k is cut by its low plane if k > 0 and by its high plane if
 // k < n − 1.  One plane (or none: the tet's least coordinate takes its
 // place) gives the axis one term.  A cell cut by both is the difference of
-// two half-lines, taken on the side where less of the tet lies beyond, so
-// the sums reach at most (n + 1)/2 cells past the piece: with n <=
-// kOctantCells that is three cells, and the cancellation costs no digits
-// that show (cells beyond are clipped instead).  A piece with m such axes
-// has 2^m terms; bit i of `term` chooses on the i-th of them.
+// two half-lines, taken on the side where fewer of the tet's cells lie
+// beyond.  A piece with m such axes has 2^m terms; bit i of `term` chooses
+// on the i-th of them.  The terms are queued with three bits for k: at most
+// kOctantCells cells an axis.
 constexpr int kOctantCells = 6;
 
 struct AxisOctant {
@@ -320,6 +319,28 @@ __host__ __device__ __forceinline__ AxisOctant axis_octant(int k, int n, double 
   a.c = (low || high) ? (at_lo ? lo : hi) : mn;
   a.minus = second && low && high;
   return a;
+}
+
+// Which tets these sums are for.  The moments' roundings are independent, and
+// λ multiplies them by its gradients, which costs digits that the clip keeps.
+// hat_range is the most λ varies over the tet's box: 2 for the six tets of a
+// box, 4 to 5 when they are jittered and turned, any number for a flat tet
+// askew to the axes.  A tet past kOctantRange is clipped, as is one wider
+// than kOctantCells.  A range of 40 and more costs a factor of tens to
+// thousands against the clip; up to 6, the volume of a cell that the tet
+// misses rounds to at most 5e-16 of the tet's, far below what is kept (1e-14).
+constexpr double kOctantRange = 6.0;
+
+// g[i]: ∇λ_i; [mn, mx]: the tet's box.
+__host__ __device__ inline double hat_range(const double g[4][3], const double mn[3],
+                                            const double mx[3]) {
+  double r = 0.0;
+  for (int i = 0; i < 4; ++i) {
+    double x = 0.0;
+    for (int e = 0; e < 3; ++e) x += fabs(g[i][e]) * (mx[e] - mn[e]);
+    r = fmax(r, x);
+  }
+  return r;
 }
 
 }  // namespace ibvt

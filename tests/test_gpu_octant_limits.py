@@ -1,0 +1,92 @@
+"""FP64 grid couplings with tets past the limits of the boundary integrals:
+flat tets and wide ones are clipped, beside others that are not, against the
+oracle at the FP64 tolerance of B (1e-12) and against the clip's own counts."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from gpu_common import gpu_csr, require_gpu, say, sparse_rel, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def coupling(faces, X, T, dev, **kw):
+    import torch
+    from paper_1810_13046_amd import Coupling
+    return Coupling(faces, to_dev(X, torch.float64, dev), to_dev(T, torch.int32, dev),
+                    consistent=False, **kw)
+
+
+@pytest.mark.parametrize("size", [0.7, 2.5, 5.0])
+@pytest.mark.parametrize("flat", [1e-2, 1e-3, 1e-4, 1e-6])
+def test_flat_tets_keep_the_clips_pieces(size, flat):
+    """Tets apart, their fourth vertex `flat` of the size off the others'
+    plane: as many pieces and entries as a mixed coupling, which clips the
+    same tets in double."""
+    dev = require_gpu()
+    rng = np.random.default_rng(int(10 * size))
+    faces = [wl.uniform_faces(32)] * 3
+    base = np.array([[0, 0, 0], [1, 0, 0], [0.2, 0.9, 0], [0.5, 0.4, flat]]) * size / 32
+    X = []
+    for _ in range(60):
+        R = np.linalg.qr(rng.standard_normal((3, 3)))[0]
+        X.append(base @ R + 0.25 + 0.5 * rng.random(3))
+    X, T = np.concatenate(X), np.arange(240).reshape(60, 4)
+    say(f"[gpu] octant limits: size={size} flat={flat}")
+    c, m = coupling(faces, X, T, dev), coupling(faces, X, T, dev, precision="fp32")
+    assert c.info()["pieces"] == m.info()["pieces"]
+    for d in range(3):
+        a, b = c.export_csr(d), m.export_csr(d)
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    c.free()
+    m.free()
+
+
+@pytest.mark.parametrize("items", [0, 40])
+def test_wide_tets_beside_small_ones(items, monkeypatch):
+    """A block of 0.8-cell elements and one of eight-cell elements: the first
+    as if it were alone, bit for bit, the second clipped; then moved until
+    none and until all are wide."""
+    import torch
+    dev = require_gpu()
+    if items:
+        monkeypatch.setenv("IBVT_CHUNK_ITEMS", str(items))
+    faces = [wl.uniform_faces(32), wl.stretched_faces(32, 1.5), wl.uniform_faces(32)]
+    small = wl.box_body("a", np.array([3, 2, 2]) * 0.8 / 32, (0.3, 0.4, 0.5), (3, 2, 2), 0.1,
+                        np.random.default_rng(1))
+    wide = wl.box_body("b", np.array([8, 8, 8]) / 32, (0.7, 0.6, 0.5), (1, 1, 1), 0.0,
+                       np.random.default_rng(2))
+    say(f"[gpu] octant limits: wide beside small, items={items}")
+    ns = small.X.shape[0]
+    T = np.concatenate([small.tets, wide.tets + ns])
+
+    def check(c, X):
+        R = oracle.assemble(faces, X, T)
+        for d in range(3):
+            fro, mx = sparse_rel(gpu_csr(c, d, oracle.n_fluid(faces, d)), R.B[d])
+            assert fro <= 1e-12 and mx <= 1e-12
+        assert abs(c.info()["pieces"] - R.stats["pieces"]) <= 4
+        return c.info()["subtets"]
+
+    X = np.concatenate([small.X, wide.X])
+    c, alone = coupling(faces, X, T, dev), coupling(faces, small.X, small.tets, dev)
+    some = check(c, X)
+    assert some > 0 and alone.info()["subtets"] == 0
+    for d in range(3):
+        rp, col, val = c.export_csr(d)
+        r2, c2, v2 = alone.export_csr(d)
+        assert np.array_equal(rp[:ns + 1], r2)
+        assert np.array_equal(col[:rp[ns]], c2) and np.array_equal(val[:rp[ns]], v2)
+    def shrunk(factor):
+        Y = X.copy()
+        Y[ns:] = (Y[ns:] - [0.7, 0.6, 0.5]) * factor + [0.7, 0.6, 0.5]
+        return Y
+
+    for Y, want in ((shrunk(0.1), "none"), (X, "some"), ((X - 0.5) * 0.1 + 0.5, "none"),
+                    ((X - 0.5) * 1.1 + 0.5, "some")):
+        c.reassemble(to_dev(Y, torch.float64, dev))
+        got = check(c, Y)
+        assert (got == 0) == (want == "none")
+    c.free()
+    alone.free()
