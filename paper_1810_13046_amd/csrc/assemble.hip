@@ -227,7 +227,16 @@ __global__ void k_tet_prep(int64_t n_t, const double* __restrict__ X,
       cnt[d * n_t + t] = int64_t(r.n[0]) * r.n[1] * r.n[2];
       if (int64_t(r.n[0]) * r.n[1] * r.n[2] > kMaxTetCells) atomicOr(flags, kFlagTetSpan);
       if (clipped) {
-        const bool cl = max(r.n[0], max(r.n[1], r.n[2])) > kOctantCells || !(range <= kOctantRange);
+        bool cl = max(r.n[0], max(r.n[1], r.n[2])) > kOctantCells || !(range <= kOctantRange);
+        if (ok && !cl) {
+          double product = 1.0;
+          for (int e = 0; e < 3; ++e) {
+            const double x = axis_reach(lat + ld.off[3 * d + e] + r.lo[e], r.n[e], mn[e], mx[e]);
+            product *= x;
+            cl |= !(x <= kOctantReach);
+          }
+          cl |= !(product <= kOctantProduct);
+        }
         clipped[d * n_t + t] = cl ? 1 : 0;
         if (cl) to_clip += uint32_t(r.n[0]) * uint32_t(r.n[1]) * uint32_t(r.n[2]);
       }

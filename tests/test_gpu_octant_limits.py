@@ -1,12 +1,13 @@
 """FP64 grid couplings with tets past the limits of the boundary integrals:
-flat tets and wide ones are clipped, beside others that are not, against the
-oracle at the FP64 tolerance of B (1e-12) and against the clip's own counts."""
+cells much narrower than their neighbours, flat tets and wide ones are clipped,
+beside others that are not, against the oracle at the FP64 tolerances (1e-12
+for B, 1e-10 for gradients) and against the clip's own counts."""
 import numpy as np
 import pytest
 
 import oracle
 import workloads as wl
-from gpu_common import gpu_csr, require_gpu, say, sparse_rel, to_dev
+from gpu_common import gpu_csr, rel_fro, require_gpu, say, sparse_rel, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -16,6 +17,41 @@ def coupling(faces, X, T, dev, **kw):
     from paper_1810_13046_amd import Coupling
     return Coupling(faces, to_dev(X, torch.float64, dev), to_dev(T, torch.int32, dev),
                     consistent=False, **kw)
+
+
+def jumped(jump):
+    """16 cells on [0, 1], the middle three `jump` times narrower."""
+    w = np.where(abs(np.arange(16) - 8) <= 1, 1.0 / jump, 1.0)
+    f = np.concatenate([[0.0], np.cumsum(w)])
+    return f / f[-1], 1.0 / f[-1]
+
+
+@pytest.mark.parametrize("axes,jump", [(1, 10), (1, 100), (1, 1000), (3, 10), (3, 100), (3, 1000)])
+def test_spacing_jumps(axes, jump):
+    import torch
+    dev = require_gpu()
+    f, wide = jumped(jump)
+    faces = [f if e < axes else wl.uniform_faces(16) for e in range(3)]
+    centre = [0.5 * (a[8] + a[9]) for a in faces]
+    ext = np.array([1.6 * (wide if e < axes else 1 / 16) for e in range(3)])
+    b = wl.box_body("b", ext, centre, (1, 1, 1), 0.0, np.random.default_rng(0))
+    say(f"[gpu] octant limits: axes={axes} jump={jump}")
+    c = coupling(faces, b.X, b.tets, dev)
+    R = oracle.assemble(faces, b.X, b.tets)
+    for d in range(3):
+        fro, mx = sparse_rel(gpu_csr(c, d, oracle.n_fluid(faces, d)), R.B[d])
+        assert fro <= 1e-12 and mx <= 1e-12
+    rng = np.random.default_rng(3)
+    u = [rng.standard_normal(oracle.lattice_shape(faces, d)[::-1]) for d in range(3)]
+    g = rng.standard_normal((3, b.X.shape[0]))
+    ud = [to_dev(v, torch.float64, dev) for v in u]
+    us = c.velocity(ud)
+    gu = [torch.zeros_like(v) for v in ud]
+    gX = torch.zeros((b.X.shape[0], 3), dtype=torch.float64, device=dev)
+    c.velocity_vjp(to_dev(g, torch.float64, dev), u_f=ud, u_s=us, g_uf=gu, g_X=gX)
+    assert rel_fro(gX.cpu().numpy(), oracle.velocity_vjp(R, u, g)[1]) <= 1e-10
+    assert c.info()["subtets"] > 0
+    c.free()
 
 
 @pytest.mark.parametrize("size", [0.7, 2.5, 5.0])

@@ -138,13 +138,22 @@ static void geom(const double* V, TetGeom& G) {
   tet_geom(G);
 }
 extern "C" void rule(double* out) {
-  out[0] = kOctantRange;
-  out[1] = kOctantCells;
+  out[0] = kOctantReach;
+  out[1] = kOctantProduct;
+  out[2] = kOctantRange;
+  out[3] = kOctantCells;
 }
+// largest reach, their product, and the range
 extern "C" void limits(const double* V, const double* const* L, const int* n, double* out) {
   TetGeom G;
   geom(V, G);
-  out[0] = hat_range(G.g, G.mn, G.mx);
+  out[0] = out[1] = 1.0;
+  for (int e = 0; e < 3; ++e) {
+    const double x = axis_reach(L[e], n[e], G.mn[e], G.mx[e]);
+    out[0] = fmax(out[0], x);
+    out[1] *= x;
+  }
+  out[2] = hat_range(G.g, G.mn, G.mx);
 }
 // largest errors of the 32 values over the cell's share of the tet (octants,
 // clip), the octants' volume, the exact one
@@ -221,14 +230,14 @@ def lib(tmp_path_factory):
     subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-O2", "-std=c++17", "-fPIC",
                     "-shared", "-I", CSRC, src, "-o", so], check=True, capture_output=True)
     lib = ctypes.CDLL(so)
-    o = (ctypes.c_double * 2)()
+    o = (ctypes.c_double * 4)()
     lib.rule(o)
-    lib.range, lib.cells = o
+    lib.reach, lib.product, lib.range, lib.cells = o
     return lib
 
 
 def look(lib, V, lines, cells=lambda n: []):
-    """(range, most cells an axis) and per cell
+    """(largest reach, their product, range, most cells an axis) and per cell
     (octant error, clip error, octant volume, exact volume), of the tet's
     volume."""
     first = [int(np.searchsorted(a, V[:, e].min(), "right")) - 1 for e, a in enumerate(lines)]
@@ -237,7 +246,7 @@ def look(lib, V, lines, cells=lambda n: []):
     arr = [np.ascontiguousarray(a[first[e]:first[e] + n[e] + 1]) for e, a in enumerate(lines)]
     V = np.ascontiguousarray(V)
     ptr = (ctypes.c_void_p * 3)(*[a.ctypes.data for a in arr])
-    ns, at = (ctypes.c_int * 3)(*n), (ctypes.c_double * 1)()
+    ns, at = (ctypes.c_int * 3)(*n), (ctypes.c_double * 3)()
     lib.limits(ctypes.c_void_p(V.ctypes.data), ptr, ns, at)
     out = []
     for k in cells(n):
@@ -248,7 +257,7 @@ def look(lib, V, lines, cells=lambda n: []):
 
 
 def within(lib, at):
-    return all(x <= y for x, y in zip(at, (lib.range, lib.cells)))
+    return all(x <= y for x, y in zip(at, (lib.reach, lib.product, lib.range, lib.cells)))
 
 
 def kuhn(rng, size, jitter, rotate):
@@ -264,7 +273,9 @@ def kuhn(rng, size, jitter, rotate):
 
 @pytest.mark.parametrize("size,rotate,snap,jump", [
     ((0.3,) * 3, False, 0.0, 1), ((0.9,) * 3, False, 0.0, 1), ((0.9,) * 3, True, 0.0, 1),
-    ((1.3,) * 3, False, 0.5, 1)])
+    ((1.3,) * 3, False, 0.5, 1), ((1.6,) * 3, True, 0.0, 1), ((2.0, 0.4, 2.0), True, 0.0, 1),
+    ((1.0, 2.8, 1.0), False, 0.5, 1), ((2.2,) * 3, False, 0.0, 1), ((1.2,) * 3, False, 0.0, 3),
+    ((0.7,) * 3, True, 0.0, 30)])
 def test_within_the_limits(lib, size, rotate, snap, jump):
     """As near as the clip, root mean square over the cells; and no volume where
     there is none (a tenth of the 1e-14 that is kept)."""
@@ -288,6 +299,17 @@ def test_within_the_limits(lib, size, rotate, snap, jump):
     assert sums[0] <= sums[1]
 
 
+@pytest.mark.parametrize("axes,jump", [(1, 10), (1, 100), (1, 1000), (3, 10), (3, 100), (3, 1000)])
+def test_narrow_cells_are_past_the_limits(lib, axes, jump):
+    """Tets over three cells of widths 1, 1/jump, 1: the narrow cell's
+    half-lines reach over a wide one."""
+    rng = np.random.default_rng(jump + axes)
+    lines = [np.array([0.0, 1.0, 1.0 + (1.0 / jump if e < axes else 1.0), 3.0, 4.0]) for e in range(3)]
+    for _ in range(20):
+        V = kuhn(rng, (1.6,) * 3, 0.1, False) + 0.3
+        assert not within(lib, look(lib, V, lines)[0])
+
+
 @pytest.mark.parametrize("size", [0.7, 2.5, 5.0])
 @pytest.mark.parametrize("flat", [1e-2, 1e-3, 1e-4, 1e-6])
 def test_flat_tets_are_past_the_limits(lib, size, flat):
@@ -299,12 +321,15 @@ def test_flat_tets_are_past_the_limits(lib, size, flat):
         while np.abs(R[2]).min() < 0.3:  # the normal
             R = np.linalg.qr(rng.standard_normal((3, 3)))[0]
         V = np.array([[0, 0, 0], [1, 0, 0], [0.2, 0.9, 0], [0.5, 0.4, flat]]) * size @ R + 15.3
-        assert look(lib, V, lines)[0][0] > lib.range
+        assert look(lib, V, lines)[0][2] > lib.range
 
 
 def test_wide_tets_are_past_the_limits(lib):
-    """More than six cells along an axis."""
+    """More than six cells along an axis, a reach of more than 1.7 along one, or
+    of more than 1.4 along three."""
     rng = np.random.default_rng(0)
     lines = [np.arange(40.0)] * 3
     for _ in range(20):
-        assert look(lib, kuhn(rng, (6.6, 0.5, 0.5), 0.02, False) + 15.3, lines)[0][1] > lib.cells
+        assert look(lib, kuhn(rng, (6.6, 0.5, 0.5), 0.02, False) + 15.3, lines)[0][3] > lib.cells
+        assert look(lib, kuhn(rng, (3.9, 0.5, 0.5), 0.02, False) + 15.3, lines)[0][0] > lib.reach
+        assert look(lib, kuhn(rng, (2.2,) * 3, 0.02, False) + 15.3, lines)[0][1] > lib.product
