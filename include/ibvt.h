@@ -433,7 +433,7 @@ int coupling_info(const ibvt_coupling* c, ibvt_info* info);
  *   reassemblies; the next reassembly allocates the scratch again.  Other
  *   couplings: nothing is released.  Stream-ordered on `stream`.
  *   Also gives back what freed couplings left for the next ones on this GPU
- *   (coupling_free).
+ *   (ibvt_release_cached).
  *   Errors: IBVT_E_INVALID (NULL handle).
  */
 int coupling_release_scratch(ibvt_coupling* c, hipStream_t stream);
@@ -480,8 +480,15 @@ int coupling_export_csr(const ibvt_coupling* c, int comp, int transposed, int64_
 /* coupling_free — release the handle and its device memory (synchronizes
  * the device).  NULL is a no-op.  Up to 1 GiB of the memory (none of a
  * caller's allocator's) stays with the library for the couplings made next
- * on the GPU, until coupling_release_scratch or an allocation needs it. */
+ * on the GPU.  Other allocators in the process cannot take it:
+ * ibvt_release_cached, coupling_release_scratch and an allocation of this
+ * library's own that fails give it back. */
 void coupling_free(ibvt_coupling* c);
+
+/* ibvt_release_cached — give back all that freed couplings left with the
+ * library on the current GPU; needs no handle, and couplings in use keep
+ * theirs.  Synchronizes the null stream.  Errors: IBVT_E_HIP. */
+int ibvt_release_cached(void);
 
 /* ibvt_status_string — static text for a status code. */
 const char* ibvt_status_string(int status);

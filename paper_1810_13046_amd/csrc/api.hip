@@ -74,8 +74,8 @@ ibvt_alloc g_alloc{};  // allocator of new handles (null members: hipMallocAsync
 // pools give all their memory back when nothing of them is in use).
 // Only coupling_free puts things here, after it has waited for the device, so
 // a taker may use them on any stream; everything is under the mutex.
-// coupling_release_scratch gives all of it back, and so does an allocation
-// that fails.
+// coupling_release_scratch and ibvt_release_cached give all of it back, and
+// so does an allocation here that fails.
 constexpr int kMaxDevices = 64;
 constexpr size_t kShelfBytes = size_t(1) << 30;
 constexpr size_t kShelfMost = 4;
@@ -290,9 +290,8 @@ void shelve(ibvt_coupling* c) {
   c->host_rb = nullptr;
 }
 
-// Everything the handle's shelf holds, given back.
-void clear_shelf(ibvt_coupling* c) {
-  Shelf* h = shelf_of(c);
+// Everything the shelf holds, given back.
+void clear_shelf(Shelf* h) {
   if (!h) return;
   drop_buffers(h);
   std::lock_guard<std::mutex> g(h->mu);
@@ -1034,7 +1033,7 @@ int ibvt_profile_read(const char** names, int64_t* launches, double* ms, int max
 int coupling_release_scratch(ibvt_coupling* c, hipStream_t stream) {
   if (!c) return set_error(IBVT_E_INVALID, "NULL handle");
   c->stream = stream;
-  clear_shelf(c);
+  clear_shelf(shelf_of(c));
   if (c->dim != 3 || c->unstructured) return IBVT_OK;
   for (DevBuf* b : {&c->pool, &c->pinfo, &c->rowtmpcol, &c->rowtmpval, &c->rowbox, &c->rowcap,
                     &c->rowtmpoff, &c->tbuf, &c->pscan, &c->mark, &c->rowspilloff,
@@ -1113,6 +1112,13 @@ void coupling_free(ibvt_coupling* c) {
   (void)hipStreamSynchronize(nullptr);
   shelve(c);
   delete c;
+}
+
+int ibvt_release_cached(void) {
+  Shelf* h = shelf_at(current_device());
+  if (!h) return IBVT_OK;
+  clear_shelf(h);
+  return hip_check(hipStreamSynchronize(nullptr), "release sync");
 }
 
 }  // extern "C"

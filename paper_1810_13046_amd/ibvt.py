@@ -39,7 +39,7 @@ EXPORTED = [
     "ibvt_profile_enable", "ibvt_profile_read", "fsi_step", "ibvt_fluid_lumped_volume",
     "assemble_coupling_2d", "ibvt_lattice_coords_2d", "assemble_coupling_unstructured",
     "transfer_vjp", "ibvt_fluid_lumped_volume_2d", "transfer_velocity_noalloc",
-    "coupling_body_info", "ibvt_set_allocator", "coupling_release_scratch",
+    "coupling_body_info", "ibvt_set_allocator", "coupling_release_scratch", "ibvt_release_cached",
 ]
 
 
@@ -170,13 +170,14 @@ def load_library(path: str = LIB_PATH):
     lib.coupling_body_info.argtypes = [vp, i32, P(i64), P(_BodyInfo), vp]
     lib.ibvt_set_allocator.argtypes = [P(_Alloc)]
     lib.coupling_release_scratch.argtypes = [vp, vp]
+    lib.ibvt_release_cached.argtypes = []
     for name in ("assemble_coupling", "reassemble_coupling", "transfer_velocity", "transfer_force",
                  "transfer_velocity_vjp", "transfer_force_vjp", "coupling_info",
                  "coupling_export_csr", "ibvt_lattice_coords", "fsi_step",
                  "ibvt_fluid_lumped_volume", "assemble_coupling_2d", "ibvt_lattice_coords_2d",
                  "assemble_coupling_unstructured", "transfer_vjp", "ibvt_fluid_lumped_volume_2d",
                  "transfer_velocity_noalloc", "coupling_body_info", "ibvt_set_allocator",
-                 "coupling_release_scratch"):
+                 "coupling_release_scratch", "ibvt_release_cached"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib
@@ -212,6 +213,12 @@ def use_torch_allocator(enable: bool = True):
     lib = load_library()
     _check(lib.ibvt_set_allocator(ctypes.byref(_TORCH_ALLOC) if enable else None),
            "ibvt_set_allocator")
+
+
+def release_cached():
+    """Give back what freed couplings left with the library on the current
+    GPU (ibvt_release_cached)."""
+    _check(load_library().ibvt_release_cached(), "ibvt_release_cached")
 
 
 def _check(st: int, where: str):
