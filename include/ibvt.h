@@ -28,11 +28,11 @@
  *   - Work is enqueued on `stream` in order.  Assembly reads counts back
  *     to size its buffers: a reassembly (grid, planar or unstructured)
  *     synchronizes the stream three times (packed read-backs of counts and
- *     status flags), once more for each component of a very large
- *     operator, a few more when a handle is
- *     created (lattices, topology, mass pattern).  Transfers synchronize only for
- *     the consistent-mass solve's convergence checks and when `info` is
- *     requested.
+ *     status flags), once more where the row arrays of B^T could exceed 128
+ *     MiB (planar and unstructured: 32 MiB; very large operators: for each
+ *     component), a few more when a handle is created (lattices, topology,
+ *     mass pattern).  Transfers synchronize only for the consistent-mass
+ *     solve's convergence checks and when `info` is requested.
  *   - The library's device buffers grow stream-ordered (hipMallocAsync and
  *     hipFreeAsync on the call's stream), so growing them does not
  *     synchronize the device.  Calls on one handle with different streams

@@ -364,7 +364,8 @@ void release_csr(ibvt_coupling* c, Csr& m) {
 
 void release_all(ibvt_coupling* c) {
   DevBuf* bufs[] = {&c->lat,      &c->X,         &c->tets,      &c->vt_ptr,    &c->vt_tet,
-                    &c->tetvol,   &c->tetrec,    &c->rng,       &c->pmom,      &c->cnt,       &c->clipped,
+                    &c->tetvol,   &c->tetrec,    &c->rng,       &c->pmom,      &c->cnt,
+                    &c->clipped,  &c->trows,
                     &c->pair_off, &c->owner,     &c->pval,      &c->keep,      &c->rownnz,
                     &c->mark,     &c->tcnt,      &c->tbuf,      &c->mlump,     &c->minv,
                     &c->Mval32,   &c->Mdiag_inv, &c->flags_dev, &c->counters,  &c->scan_tmp,
@@ -1036,8 +1037,8 @@ int coupling_release_scratch(ibvt_coupling* c, hipStream_t stream) {
   clear_shelf(shelf_of(c));
   if (c->dim != 3 || c->unstructured) return IBVT_OK;
   for (DevBuf* b : {&c->pool, &c->pinfo, &c->rowtmpcol, &c->rowtmpval, &c->rowbox, &c->rowcap,
-                    &c->rowtmpoff, &c->tbuf, &c->pscan, &c->mark, &c->rowspilloff,
-                    &c->rowspill})
+                    &c->rowtmpoff, &c->tbuf, &c->trows, &c->clipped, &c->pscan, &c->mark,
+                    &c->rowspilloff, &c->rowspill})
     release(c, *b);
   // the matrix-free products keep their per-tet buffer and item order
   if (!c->matrix_free) {

@@ -1841,14 +1841,10 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
   {
     const int64_t* src[kCntSlots + 3];
     for (int k = 0; k < kCntSlots; ++k) src[k] = reinterpret_cast<const int64_t*>(counters + k);
-    int n = kCntSlots;
-    for (int d = 0; d < 3; ++d)
-      if (touched[d]) src[n++] = touched[d];
-    if ((st = read_counts(c, src, n, cnt, s))) return st;
-    n = kCntSlots;
-    for (int d = 0; d < 3; ++d)
-      if (touched[d]) c->Bt[d].nrows = cnt[n++];
+    for (int d = 0; d < 3; ++d) src[kCntSlots + d] = touched[d];
+    if ((st = read_counts(c, src, kCntSlots + 3, cnt, s))) return st;
   }
+  if ((st = transpose_done(c, 3, cnt + kCntSlots, s))) return st;
   c->stats.pairs = n_pairs;
   c->stats.pieces = cnt[kCntPieces];
   c->stats.dropped = cnt[kCntDropped];

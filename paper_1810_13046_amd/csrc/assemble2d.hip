@@ -676,13 +676,10 @@ int assemble2_typed(ibvt_coupling* c, hipStream_t s) {
     int n = 0;
     for (int k : {int(kCntPieces), int(kCntDropped), int(kCntZeroTets)})
       src[n++] = reinterpret_cast<const int64_t*>(counters + k);
-    for (int d = 0; d < 2; ++d)
-      if (touched[d]) src[n++] = touched[d];
+    for (int d = 0; d < 2; ++d) src[n++] = touched[d];
     if ((st = read_counts(c, src, n, cnt, s))) return st;
-    n = 3;
-    for (int d = 0; d < 2; ++d)
-      if (touched[d]) c->Bt[d].nrows = cnt[n++];
   }
+  if ((st = transpose_done(c, 2, cnt + 3, s))) return st;
   c->stats.pairs = n_pairs;
   c->stats.pieces = cnt[0];
   c->stats.dropped = cnt[1];

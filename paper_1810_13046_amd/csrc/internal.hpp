@@ -196,6 +196,11 @@ struct ibvt_coupling {
   ibvt::DevBuf mark;         // int32 per fluid node and sums (transposes of small operators)
   ibvt::DevBuf tcnt;         // their touched nodes (int64 per component)
   ibvt::DevBuf tbuf;         // transpose scratch (bucket records and tables)
+  ibvt::DevBuf trows;        // row pointers and row maps of B^T until their rows are counted
+  struct StagedRows {
+    int64_t* rowptr = nullptr;
+    int32_t* rowmap = nullptr;
+  } trows_from[3];           // of the last transposes (null: in place)
   ibvt::DevBuf mlump;        // double n_vert
   ibvt::DevBuf minv;         // T n_vert
   bool has_M = false;
@@ -284,9 +289,10 @@ int shape_gradient_2d(ibvt_coupling* c, const void* z, const void* const u[3], c
                       int mass, double alpha, double* gX, hipStream_t s);
 
 // transpose.hip: B^dT, d < n.  Its rows' number is left on the device, at
-// touched[d] (to be read into Bt[d].nrows), or set (touched[d] null).
+// touched[d]; once read, transpose_done takes it and finishes the row arrays.
 template <typename T>
 int transposes(ibvt_coupling* c, int n, const int64_t** touched, hipStream_t s);
+int transpose_done(ibvt_coupling* c, int n, const int64_t* rows, hipStream_t s);
 
 // sort.hip: stable sorts by small integer keys (n < 2^31).
 // A nonzero carried through the small operators' transpose: its value and

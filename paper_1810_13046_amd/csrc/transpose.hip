@@ -21,9 +21,9 @@
 //                     its own (a row's vertices are distinct); the block
 //                     writes the bucket's columns, values, row pointers and
 //                     row map.
-// The components go through these together while they are not too large, and
-// no count is waited for.  Small operators take a counting sort over the whole
-// lattice instead, together as well:
+// The components go through these together while they are not too large.
+// Small operators take a counting sort over the whole lattice instead,
+// together as well:
 //   k_tcount          nonzeros per lattice node.
 //   k_tsums, k_tscan  per tile of nodes: its touched nodes and its nonzeros,
 //                     and their prefix sums.
@@ -51,10 +51,10 @@ constexpr int kKeyLanes = 16;  // lanes per row of B^d in the counting sort's sc
 
 // Counting sort for small operators, where the bucket path's fixed launches
 // dominate (use_buckets): one component of a launch.  The components share
-// every launch and no count is waited for: bound by launches and the reading
-// of the lattice's counters, 32 us for a 144-tet beam on 32^3 cells, where
-// component by component with marks, two scans and a read-back for each it
-// was 201.
+// every launch and the counts stay on the device: bound by launches and the
+// reading of the lattice's counters, 32 us for a 144-tet beam on 32^3 cells,
+// where component by component with marks, two scans and a read-back for each
+// it was 201.
 template <typename T>
 struct TOne {
   const int64_t* rowptr;  // B^d
@@ -147,9 +147,8 @@ __device__ __forceinline__ uint64_t block_prefix(uint64_t v, uint64_t (&sh)[THRE
   return pre + x - v;
 }
 
-// One block per component scans its tiles' sums in place and ends its row
-// pointers (fewer than 2^31 nonzeros and lattice nodes: the halves of a sum
-// do not overflow).
+// One block per component scans its tiles' sums in place (fewer than 2^31
+// nonzeros and lattice nodes: the halves of a sum do not overflow).
 template <typename T>
 __global__ __launch_bounds__(1024) void k_tscan(TBatch<T> b) {
   __shared__ uint64_t sh[1024 / kWave];
@@ -165,10 +164,7 @@ __global__ __launch_bounds__(1024) void k_tscan(TBatch<T> b) {
     c.sum[t] = pre;
     pre += v;
   }
-  if (threadIdx.x == 0) {
-    *c.touched = int64_t(total >> 32);
-    c.trowptr[total >> 32] = c.nnz;
-  }
+  if (threadIdx.x == 0) *c.touched = int64_t(total >> 32);
 }
 
 template <typename T>
@@ -181,6 +177,7 @@ __global__ __launch_bounds__(kTThreads) void k_ttiles(TBatch<T> b) {
   uint64_t total;
   uint64_t at = c.sum[t] + block_prefix<kTThreads>(nodes_sum(v), sh, total);
   const int64_t n0 = t * kTTile + int64_t(threadIdx.x) * kTItems;
+  if (t == 0 && threadIdx.x == 0) c.trowptr[*c.touched] = c.nnz;
 #pragma unroll
   for (int k = 0; k < kTItems; ++k) {
     if (v[k] > 0) {
@@ -735,11 +732,94 @@ inline unsigned blocks_for(int64_t n, int threads) {
   return unsigned(ceil_div(n > 0 ? n : 1, threads));
 }
 
+// Where B^dT's row pointers and row maps go: its rows are counted on the
+// device, and waiting for the counts costs some 45 us of a step.  They cannot
+// exceed the nonzeros or the lattice's nodes, but may be tens of times fewer
+// (200k tets in 192^3 cells: 83 MB by that bound, 3 by the rows), and the
+// arrays live as long as the handle.  So they are allocated by the bound only
+// where that is little; otherwise the rows go to scratch, which
+// coupling_release_scratch gives back, and are copied once the counts have
+// been read with the assembly's others (transpose_done); and where the scratch
+// would be large (three bodies of 4.5M tets: 1.2 GB), or is never given back
+// (planar and tet backgrounds), the counts are waited for.
+constexpr int64_t kLooseRows = int64_t(32) << 20, kStagedRows = int64_t(128) << 20;  // bytes
+int64_t rows_bound(const ibvt_coupling* c, int d) {
+  return std::min<int64_t>(c->B[d].nnz, c->n_fluid[d]);
+}
+
+// For all components of an assembly together; wait: the counts are to be
+// waited for.
+int stage_rows(ibvt_coupling* c, int n, bool& wait) {
+  constexpr int64_t per_row = sizeof(int64_t) + sizeof(int32_t);
+  int64_t all = 0;
+  for (int d = 0; d < n; ++d) {
+    all += rows_bound(c, d) + 2;
+    c->trows_from[d] = ibvt_coupling::StagedRows{};
+  }
+  const bool little = all * per_row <= kLooseRows;
+  const bool scratch = all * per_row <= kStagedRows && c->dim == 3 && !c->unstructured;
+  wait = !little && !scratch;
+  if (little || wait) return IBVT_OK;
+  if (int st = ensure(c, c->trows, size_t(all * per_row))) return st;
+  int64_t* rp = c->trows.as<int64_t>();
+  int32_t* rm = reinterpret_cast<int32_t*>(rp + all);
+  for (int d = 0; d < n; ++d) {
+    c->trows_from[d] = {rp, rm};
+    rp += rows_bound(c, d) + 2;
+    rm += rows_bound(c, d) + 2;
+  }
+  return IBVT_OK;
+}
+
+// The row arrays of the components of one launch, their counts enqueued.
+template <typename One>
+int transpose_rows(ibvt_coupling* c, const int* ds, int n, bool wait, One* one, hipStream_t s) {
+  int64_t rows[3];
+  const int64_t* src[3];
+  int st;
+  for (int k = 0; k < n; ++k) {
+    rows[k] = rows_bound(c, ds[k]);
+    src[k] = one[k].touched;
+  }
+  if (wait && (st = read_counts(c, src, n, rows, s))) return st;
+  for (int k = 0; k < n; ++k) {
+    Csr& Bt = c->Bt[ds[k]];
+    one[k].trowptr = c->trows_from[ds[k]].rowptr;
+    one[k].rowmap = c->trows_from[ds[k]].rowmap;
+    if (one[k].trowptr) continue;
+    if ((st = ensure(c, Bt.rowptr, size_t(rows[k] + 1) * sizeof(int64_t)))) return st;
+    if ((st = ensure(c, Bt.rowmap, size_t(rows[k] + 1) * sizeof(int32_t)))) return st;
+    one[k].trowptr = Bt.rowptr.template as<int64_t>();
+    one[k].rowmap = Bt.rowmap.template as<int32_t>();
+  }
+  return IBVT_OK;
+}
+
+// Staged rows into the arrays of B^dT (blockIdx.y: the component).
+struct RowCopies {
+  const int64_t* rp[3];
+  const int32_t* rm[3];
+  int64_t* to_rp[3];
+  int32_t* to_rm[3];
+  int64_t rows[3];
+};
+__global__ __launch_bounds__(256) void k_copy_rows(RowCopies r) {
+  const int d = blockIdx.y;
+  const int64_t n = d == 0 ? r.rows[0] : (d == 1 ? r.rows[1] : r.rows[2]);
+  const int64_t* rp = d == 0 ? r.rp[0] : (d == 1 ? r.rp[1] : r.rp[2]);
+  const int32_t* rm = d == 0 ? r.rm[0] : (d == 1 ? r.rm[1] : r.rm[2]);
+  int64_t* to_rp = d == 0 ? r.to_rp[0] : (d == 1 ? r.to_rp[1] : r.to_rp[2]);
+  int32_t* to_rm = d == 0 ? r.to_rm[0] : (d == 1 ? r.to_rm[1] : r.to_rm[2]);
+  const int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (k <= n) to_rp[k] = rp[k];
+  if (k < n) to_rm[k] = rm[k];
+}
+
 // Counting sort over the whole lattice (small operators; nnz == 0 too) of
 // the n components in ds.  The counts of touched nodes stay on the device,
-// in touched: B^dT's arrays are sized by what the counts cannot exceed.
+// in touched.
 template <typename T>
-int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** touched,
+int transpose_counting(ibvt_coupling* c, const int* ds, int n, bool wait, const int64_t** touched,
                        hipStream_t s) {
   TBatch<T> b{};
   b.n = n;
@@ -759,8 +839,6 @@ int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** t
     TOne<T>& o = b.c[k];
     const int64_t rows = std::min<int64_t>(B.nnz, c->n_fluid[ds[k]]);
     Bt.nnz = B.nnz;
-    if ((st = ensure(c, Bt.rowptr, size_t(rows + 1) * sizeof(int64_t)))) return st;
-    if ((st = ensure(c, Bt.rowmap, size_t(rows + 1) * sizeof(int32_t)))) return st;
     if ((st = ensure(c, Bt.col, size_t(B.nnz + 1) * sizeof(int32_t)))) return st;
     if ((st = ensure(c, Bt.val, size_t(B.nnz + 1) * sizeof(T)))) return st;
     o.rowptr = B.rowptr.template as<int64_t>();
@@ -770,8 +848,6 @@ int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** t
     o.node = c->mark.as<int32_t>() + o.tile0 * kTTile;
     o.sum = reinterpret_cast<uint64_t*>(c->mark.as<char>() + node_b) + o.tile0;
     o.touched = c->tcnt.as<int64_t>() + 2 * ds[k];
-    o.trowptr = Bt.rowptr.template as<int64_t>();
-    o.rowmap = Bt.rowmap.template as<int32_t>();
     o.tcol = Bt.col.template as<int32_t>();
     o.tval = Bt.val.template as<T>();
     touched[ds[k]] = o.touched;
@@ -786,8 +862,9 @@ int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** t
   if (nnz_max) k_tcount<T><<<dim3(blocks_for(nnz_max, 256), un), 256, 0, s>>>(b);
   k_tsums<T><<<unsigned(tiles), kTThreads, 0, s>>>(b);
   k_tscan<T><<<un, 1024, 0, s>>>(b);
+  if ((st = transpose_rows(c, ds, n, wait, b.c, s))) return st;
+  k_ttiles<T><<<unsigned(tiles), kTThreads, 0, s>>>(b);
   if (nnz_max) {
-    k_ttiles<T><<<unsigned(tiles), kTThreads, 0, s>>>(b);
     k_tscatter<T><<<dim3(blocks_for(c->n_vert * kKeyLanes, 256), un), 256, 0, s>>>(b, c->n_vert);
     k_trow_order<T><<<dim3(std::min(blocks_for(rows_max * kWave, 256), kTOrderBlocks), un), 256, 0,
                       s>>>(b);
@@ -795,10 +872,8 @@ int transpose_counting(ibvt_coupling* c, const int* ds, int n, const int64_t** t
   return hip_check(hipGetLastError(), "transpose launch");
 }
 
-// Bucket transpose of the n components in ds.  The counts stay on the device
-// (transpose_counting), or are waited for before B^dT's rows are allocated:
-// a large operator's bound would be far more than its rows (three bodies of
-// 4.5M tets: 1.2 GB for 1.4M rows), and its wait is short beside its work.
+// Bucket transpose of the n components in ds; the counts as in
+// transpose_counting.
 template <typename T>
 int transpose_buckets(ibvt_coupling* c, const int* ds, int n, bool wait, const int64_t** touched,
                       hipStream_t s) {
@@ -862,19 +937,7 @@ int transpose_buckets(ibvt_coupling* c, const int* ds, int n, bool wait, const i
   k_bucket_count<T><<<grid, kBucketThreads, 0, s>>>(b, n_rows, per);
   k_bucket_tiles<T><<<unsigned(tiles), kBucketThreads, 0, s>>>(b);
   k_bucket_scan<T><<<un, 1024, 0, s>>>(b);
-  int64_t rows[3];
-  for (int k = 0; k < n; ++k) rows[k] = std::min<int64_t>(b.c[k].nnz, c->n_fluid[ds[k]]);
-  if (wait) {
-    const int64_t* src[3] = {b.c[0].touched, b.c[1].touched, b.c[2].touched};
-    if ((st = read_counts(c, src, n, rows, s))) return st;
-  }
-  for (int k = 0; k < n; ++k) {
-    Csr& Bt = c->Bt[ds[k]];
-    if ((st = ensure(c, Bt.rowptr, size_t(rows[k] + 1) * sizeof(int64_t)))) return st;
-    if ((st = ensure(c, Bt.rowmap, size_t(rows[k] + 1) * sizeof(int32_t)))) return st;
-    b.c[k].trowptr = Bt.rowptr.template as<int64_t>();
-    b.c[k].rowmap = Bt.rowmap.template as<int32_t>();
-  }
+  if ((st = transpose_rows(c, ds, n, wait, b.c, s))) return st;
   k_bucket_list<T><<<unsigned(tiles), kBucketThreads, 0, s>>>(b);
   k_bucket_scatter<T><<<grid, kBucketThreads, 0, s>>>(b, n_rows, per);
   // (the number of nonempty buckets is on the device: a block for 512
@@ -895,23 +958,49 @@ template <typename T>
 int transposes(ibvt_coupling* c, int n, const int64_t** touched, hipStream_t s) {
   int small[3], large[3], ns = 0, nl = 0, st;
   int64_t records = 0;
+  bool wait;
+  if ((st = stage_rows(c, n, wait))) return st;
   for (int d = 0; d < n; ++d) {
     if (!use_buckets(c->B[d].nnz, c->n_vert)) {
       small[ns++] = d;
     } else if (c->n_vert < kBucketMaxVert) {
       large[nl++] = d;
       records += c->B[d].nnz;
-    } else if ((st = transpose_counting<T>(c, &d, 1, touched, s))) {
+    } else if ((st = transpose_counting<T>(c, &d, 1, wait, touched, s))) {
       return st;
     }
   }
   if (nl && records <= kBatchRecords) {
-    if ((st = transpose_buckets<T>(c, large, nl, false, touched, s))) return st;
+    if ((st = transpose_buckets<T>(c, large, nl, wait, touched, s))) return st;
   } else {
     for (int k = 0; k < nl; ++k)
-      if ((st = transpose_buckets<T>(c, large + k, 1, true, touched, s))) return st;
+      if ((st = transpose_buckets<T>(c, large + k, 1, wait, touched, s))) return st;
   }
-  return ns ? transpose_counting<T>(c, small, ns, touched, s) : IBVT_OK;
+  return ns ? transpose_counting<T>(c, small, ns, wait, touched, s) : IBVT_OK;
+}
+
+int transpose_done(ibvt_coupling* c, int n, const int64_t* rows, hipStream_t s) {
+  RowCopies r{};
+  int64_t most = -1;
+  int st;
+  for (int d = 0; d < n; ++d) {
+    Csr& Bt = c->Bt[d];
+    Bt.nrows = rows[d];
+    r.rows[d] = -1;  // nothing to copy
+    const auto from = c->trows_from[d];
+    if (!from.rowptr) continue;
+    if ((st = ensure(c, Bt.rowptr, size_t(rows[d] + 1) * sizeof(int64_t)))) return st;
+    if ((st = ensure(c, Bt.rowmap, size_t(rows[d] + 1) * sizeof(int32_t)))) return st;
+    r.rows[d] = rows[d];
+    r.rp[d] = from.rowptr;
+    r.rm[d] = from.rowmap;
+    r.to_rp[d] = Bt.rowptr.as<int64_t>();
+    r.to_rm[d] = Bt.rowmap.as<int32_t>();
+    most = std::max(most, rows[d]);
+  }
+  if (most < 0) return IBVT_OK;
+  k_copy_rows<<<dim3(blocks_for(most + 1, 256), unsigned(n)), 256, 0, s>>>(r);
+  return hip_check(hipGetLastError(), "transpose rows launch");
 }
 
 template int transposes<float>(ibvt_coupling*, int, const int64_t**, hipStream_t);

@@ -892,9 +892,9 @@ int assemble_u_typed(ibvt_coupling* c, hipStream_t s) {
   {
     const int64_t* src[3] = {reinterpret_cast<const int64_t*>(counters + kCntPieces),
                              reinterpret_cast<const int64_t*>(counters + kCntDropped), touched[0]};
-    if ((st = read_counts(c, src, touched[0] ? 3 : 2, cnt, s))) return st;
-    if (touched[0]) c->Bt[0].nrows = cnt[2];
+    if ((st = read_counts(c, src, 3, cnt, s))) return st;
   }
+  if ((st = transpose_done(c, 1, cnt + 2, s))) return st;
   // the three velocity components share the fluid nodes: one B
   c->B[1] = c->B[2] = c->B[0];
   c->Bt[1] = c->Bt[2] = c->Bt[0];
