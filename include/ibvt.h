@@ -28,7 +28,7 @@
  *   - Work is enqueued on `stream` in order.  Assembly reads counts back
  *     to size its buffers: a reassembly (grid, planar or unstructured)
  *     synchronizes the stream three times (packed read-backs of counts and
- *     status flags), once more where the row arrays of B^T could exceed 128
+ *     status flags), once more where the row arrays of B^T could exceed 384
  *     MiB (planar and unstructured: 32 MiB; very large operators: for each
  *     component), a few more when a handle is created (lattices, topology,
  *     mass pattern).  Transfers synchronize only for the consistent-mass

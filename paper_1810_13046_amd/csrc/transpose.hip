@@ -739,10 +739,11 @@ inline unsigned blocks_for(int64_t n, int threads) {
 // arrays live as long as the handle.  So they are allocated by the bound only
 // where that is little; otherwise the rows go to scratch, which
 // coupling_release_scratch gives back, and are copied once the counts have
-// been read with the assembly's others (transpose_done); and where the scratch
-// would be large (three bodies of 4.5M tets: 1.2 GB), or is never given back
-// (planar and tet backgrounds), the counts are waited for.
-constexpr int64_t kLooseRows = int64_t(32) << 20, kStagedRows = int64_t(128) << 20;  // bytes
+// been read with the assembly's others (transpose_done); and where the
+// components do not go through the buckets together (kBatchRecords; three
+// bodies of 4.5M tets: 1.2 GB), or their scratch is never given back (planar
+// and tet backgrounds), the counts are waited for.
+constexpr int64_t kLooseRows = int64_t(32) << 20, kStagedRows = int64_t(384) << 20;  // bytes
 int64_t rows_bound(const ibvt_coupling* c, int d) {
   return std::min<int64_t>(c->B[d].nnz, c->n_fluid[d]);
 }
