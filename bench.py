@@ -70,16 +70,16 @@ POINTS_PER_SUBTET = 11
 # passes, scaled by the copy-kernel calibration (FETCH x 2, WRITE x 1): the
 # summary and its commands are in profiles/.  Reported only while the clip
 # sources are the ones the counters were taken on.
-CLIP_TRAFFIC = dict(sources_sha256="3800264d4994daa2c74c70a25de4942cd18f307be5a10b65554dee672c5342f0",
-                    bytes_mixed=25436929408)
+CLIP_TRAFFIC = dict(sources_sha256="24a12315427b43b7b2f3930671284f699727e8504a4044338c0f580be660c3ae",
+                    bytes_mixed=25750689941)
 CLIP_SOURCES = ["paper_1810_13046_amd/csrc/assemble.hip", "paper_1810_13046_amd/csrc/geometry.hpp",
                 "paper_1810_13046_amd/csrc/common.hpp", "paper_1810_13046_amd/csrc/gen_clip_table.py"]
 # HBM traffic of one lumped velocity apply and one force apply (all three
 # components, mixed precision) on the three-body workload, from the same
 # counter passes (profiles/hbm_traffic_three_bodies4.5M_mixed.txt);
 # reported while apply.hip is the source they were taken on.
-APPLY_TRAFFIC = dict(sources_sha256="2364d30cd6bae5f50fd603c4ed7fdc3e6a156ff37b34dcc7efd560032113be06",
-                     velocity_bytes=972426558, force_bytes=980883005)
+APPLY_TRAFFIC = dict(sources_sha256="57670bb211375e90dd86489ce3c6523c9c70c31dfba40f9af1e77afbb8e538bf",
+                     velocity_bytes=972417677, force_bytes=980847424)
 APPLY_SOURCES = ["paper_1810_13046_amd/csrc/apply.hip"]
 
 

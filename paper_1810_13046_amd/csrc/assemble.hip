@@ -758,18 +758,18 @@ __device__ __forceinline__ void store_stage(const double* stage, const int rel[8
 // (null: none is).  One wave per `range` candidate pairs: 64 candidates at a
 // time are tested against the tet's faces, the octant terms of those left
 // are queued, and whole batches of 64 terms are integrated, one lane each
-// (moments.hpp), so the lanes stay filled (94 % of them active) although a
-// fifth of the candidates is empty.  A pair's terms are consecutive; its
+// (moments.hpp), so the lanes stay filled although a fifth of the candidates
+// is empty.  A pair's terms are consecutive; its
 // first lane adds them in order and turns the 32 moments into the values
 // ∫ λ_i N_j, so a pair's results depend on the pair alone.
 //
-// Measured on 84.4M pairs (4.5M tets on 512 x 256 x 256): 17.3 ms, where the
-// clip (19.6), the integration of its sub-tetrahedra (20.9) and the pair
-// order between them took 41 ms.  Of the 17.3, candidates, set-up and the
-// values take 5.7, the faces 6.2 (FP64 issue: 730 VALU instructions a face)
-// and the 33 GB written 5.4; at 205 registers two waves a SIMD do not hide
-// all of the stores.  Three waves (168 registers) spill and take 18.3;
-// stores of 16 bytes a lane to lines of their own take 0.4 ms more.
+// Measured on 84.4M pairs (4.5M tets on 512 x 256 x 256): 17.7 ms, where the
+// pair order, the clip and the integration of its sub-tetrahedra take 36 (a
+// step 43.4 ms for 61.6).  Bound: 5.1e9 VALU instructions (702 a face, 576 of
+// them FP64; 8.2 ms of issue) and 32.5 GB written and 8.3 read (8 ms at a
+// copy's rate), neither hidden behind the other at two waves a SIMD (207
+// registers).  Three waves (168 registers) spill and take 0.5 ms more; stores
+// of 16 bytes a lane to lines of their own 0.4 ms.
 __global__ __launch_bounds__(kWave, 2) void k_pieces(
     int64_t plane_pairs, int64_t p_begin, int64_t p_end, int range, int64_t n_t,
     const uint8_t* __restrict__ clipped, const int32_t* __restrict__ owner,
@@ -1586,11 +1586,13 @@ int assemble_typed(ibvt_coupling* c, hipStream_t s) {
   if (c->matrix_free) return finish_matfree<T>(c, s);
   const int64_t tmp_total = pat[nchunk + 1], spill_total = nchunk > 1 ? pat[nchunk + 3] : 0;
   // Boundary integrals (k_pieces) or clipping: the items of an FP64 coupling
-  // within the limits of moments.hpp take the former (17.3 ms against 41 on
-  // the three-body mesh, 0.37 against 1.3 on 47,916 tets), the others are
-  // clipped, each into its own pairs' places.  Mixed couplings are clipped
-  // throughout: their moments are float sums over the sub-tetrahedra, and a
-  // program that keeps its results keeps the same ones to the last bit.
+  // within the limits of moments.hpp take the former (a step of the three-body
+  // mesh takes 43.4 ms so and 61.6 clipped, of 47,916 tets 1.51 and 2.12), the
+  // others are clipped, each into its own pairs' places.  Mixed couplings are clipped
+  // throughout: the boundary integrals would take a three-body step from 40 to
+  // 33 ms, and be no further off, but move every float result in its last
+  // digits (g_X by 3e-7 to 5e-6 of its norm), and a caller who compares a run
+  // with a stored one gets the same bits.
   const int64_t clip_pairs = to_clip ? pat[nchunk + 2] : n_pairs;
   const bool clips = clip_pairs > 0, octants = clip_pairs < n_pairs;
   if (!octants) to_clip = nullptr;  // all items

@@ -370,9 +370,10 @@ __host__ __device__ __forceinline__ void table_clip_by(const PolyView& P, TableP
   if (cc) cc->cuts += uint32_t(n);
 }
 
-// Clip by the six planes of the box [lo, hi].  mn/mx bound the original
-// tet: the piece never leaves them, so a plane the tet does not straddle is
-// skipped, and a box the tet only touches gives an empty piece.
+// Clip by the six planes of the box [lo, hi], keeping the vertex graph: what
+// clip_piece_box is held to by the host tests (no kernel calls this).  mn/mx
+// bound the original tet: the piece never leaves them, so a plane the tet does
+// not straddle is skipped, and a box the tet only touches gives an empty piece.
 template <int NS = kMaxV>
 __host__ __device__ inline bool poly_clip_box(const PolyView& P, uint32_t& live, const double lo[3],
                                               const double hi[3], const double mn[3],

@@ -257,7 +257,14 @@ __global__ __launch_bounds__(256) void k_shape_tet(
 //   36,162,  5:   28 /  21 /  22 /  33     104,400,  5:   39 /  37 /  48 /  85
 //  289,296,  5:   81 /  94 / 133 / 243     289,296,  8:  128 / 122 / 150 / 247
 //  1,190,250, 14: 641 / 727 / 974 / 1233    13,510,206, 6: 3.70 / 4.56 / 6.52 / 11.6 ms
-// and in double 143,748, 10: 230 / 161 / 191 / 253.
+// and in double, whose rows are twice as long,
+//      432, 37:  149 /  50 /  26 /  17       5,760, 22:  130 /  40 /  24 /  24
+//   19,440, 35:  221 /  96 /  60 /  58      46,080,  7:   53 /  38 /  34 /  49
+//  143,748, 10:  225 / 157 / 134 / 169     155,520,  7:  134 / 119 / 104 / 160
+//  364,500,  7:  249 / 262 / 230 / 367     364,500, 16:  487 / 500 / 419 / 511
+//  1,443,510, 13: 1588 / 1650 / 1390 / 1743   13,510,206, 6: 7.70 / 9.08 / 8.40 / 13.6 ms
+// The lines are the float kernel's: in double they cost nothing against one
+// lane, but eight would be 8 to 15 % ahead from 46,000 items to 1.4M.
 int shape_lanes(int64_t items, int64_t pairs) {
   if (items <= 4000 || (items <= 16000 && pairs > 12 * items) ||
       (items <= 30000 && pairs > 24 * items))

@@ -715,10 +715,19 @@ __global__ __launch_bounds__(kBucketThreads, sizeof(T) == sizeof(float) ? 5 : 4)
 // from 2^22; or from IBVT_BUCKET_NNZ nonzeros (the environment, a positive
 // integer; small values put small operators through the bucket path, as the
 // tests do).  Both paths give the same B^dT.  Microseconds for three
-// components through the buckets / the counting sort, by nonzeros and nodes
-// of each: 47k, 113k: 68 / 51; 129k, 0.3M: 71 / 65; 143k, 2.1M: 69 / 99; 363k, 0.9M:
-// 84 / 100; 0.6M, 2.1M (double): 104 / 267; 2.3M, 7.1M: 221 / 428; with 675 rows
-// 117k, 0.9M: 142 / 52.
+// components through the buckets / the counting sort (double within 5 % of
+// float), by rows, nonzeros and lattice nodes of each:
+//      63,   8k, 0.03M:  82 /  36       63,  95k,  2.1M: 868 / 195
+//     756,  40k, 0.1M:   69 /  44      756, 491k,  7.1M: 463 / 158
+//   1,519,  82k, 0.3M:   75 /  60    1,519, 774k, 11.3M: 426 / 197
+//   3,321, 129k, 0.3M:   72 /  90    3,321, 778k,  7.1M: 208 / 169
+//   3,969, 367k, 2.1M:  109 / 143    3,969, 1.0M, 11.3M: 252 / 225
+//   9,648, 432k, 0.9M:   95 / 123    9,648, 1.4M, 11.3M: 182 / 288
+//   9,648, 576k, 2.1M:  100 / 265   37,544, 2.4M,  7.1M: 216 / 427
+// The buckets take 55 us and 0.55 for each nonzero of a row (a block's rounds
+// follow one another), the counting sort 35 us and some 14 for each million
+// nodes: below the lines the one or the other wins by up to a third, by its
+// lattice and its rows' length, past them the buckets.
 bool use_buckets(int64_t nnz, int64_t n_rows) {
   if (const char* e = std::getenv("IBVT_BUCKET_NNZ")) {
     char* end = nullptr;

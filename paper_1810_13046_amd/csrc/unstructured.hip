@@ -975,49 +975,49 @@ __global__ __launch_bounds__(256) void k_shape_u(
         const double ul[4] = {double(u[fv.x]), double(u[fv.y]), double(u[fv.z]), double(u[fv.w])};
         const double* gm = frec + kURec * f + 12;  // ∇μ_j at gm[3j + k]
         double gu[3];
-  #pragma unroll
+#pragma unroll
         for (int k = 0; k < 3; ++k)
           gu[k] = ul[0] * gm[k] + ul[1] * gm[3 + k] + ul[2] * gm[6 + k] + ul[3] * gm[9 + k];
         T V[16], L[kULam];
         load_row<16>(vals + 16 * p, V);
         load_row<kULam>(lams + kULam * p, L);
         double zvu = 0.0;
-  #pragma unroll
+#pragma unroll
         for (int i = 0; i < 4; ++i) {
           double r = 0.0;
-  #pragma unroll
+#pragma unroll
           for (int j = 0; j < 4; ++j) r += double(V[4 * i + j]) * ul[j];
           zvu += zl[i] * r;
         }
-  #pragma unroll
+#pragma unroll
         for (int a = 0; a < 4; ++a) {
           double zla = 0.0;
-  #pragma unroll
+#pragma unroll
           for (int i = 0; i < 4; ++i) zla += zw[i] * double(L[lam_index(a, i)]);
-  #pragma unroll
+#pragma unroll
           for (int k = 0; k < 3; ++k) acc[a * 3 + k] += gu[k] * zla + gl[3 * a + k] * zvu;
         }
         if (TWO) {
           const double vl[4] = {double(v[fv.x]), double(v[fv.y]), double(v[fv.z]),
                                 double(v[fv.w])};
           double gv[3];
-  #pragma unroll
+#pragma unroll
           for (int k = 0; k < 3; ++k)
             gv[k] = vl[0] * gm[k] + vl[1] * gm[3 + k] + vl[2] * gm[6 + k] + vl[3] * gm[9 + k];
           double zvv = 0.0;
-  #pragma unroll
+#pragma unroll
           for (int i = 0; i < 4; ++i) {
             double r = 0.0;
-  #pragma unroll
+#pragma unroll
             for (int j = 0; j < 4; ++j) r += double(V[4 * i + j]) * vl[j];
             zvv += zl2[i] * r;
           }
-  #pragma unroll
+#pragma unroll
           for (int a = 0; a < 4; ++a) {
             double zla = 0.0;
-  #pragma unroll
+#pragma unroll
             for (int i = 0; i < 4; ++i) zla += zw2[i] * double(L[lam_index(a, i)]);
-  #pragma unroll
+#pragma unroll
             for (int k = 0; k < 3; ++k)
               acc[a * 3 + k] += alpha2 * (gv[k] * zla + gl[3 * a + k] * zvv);
           }
