@@ -126,3 +126,31 @@ def test_wide_tets_beside_small_ones(items, monkeypatch):
         assert (got == 0) == (want == "none")
     c.free()
     alone.free()
+
+
+def test_piece_store_overflow_beside_boundary_integrals():
+    """Long tets cut in more sub-tetrahedra than the store first holds (3.25 a
+    pair), beside small elements: both are integrated again."""
+    dev = require_gpu()
+    rng = np.random.default_rng(4)
+    faces = [wl.uniform_faces(32)] * 3
+    small = wl.box_body("a", np.array([3, 2, 2]) * 0.8 / 32, (0.3, 0.4, 0.5), (3, 2, 2), 0.1, rng)
+    rod = np.array([[0, 0, 0], [0, 1.9, 1.9], [24, 0, 1.9], [24, 1.9, 0]]) / 32
+    X = [rod + (0.05 + rng.random(3) * [0.15, 0.8, 0.8]) for _ in range(60)]
+    ns = small.X.shape[0]
+    T = np.concatenate([small.tets, ns + np.arange(240).reshape(60, 4)])
+    X = np.concatenate([small.X, *X])
+    c, alone = coupling(faces, X, T, dev), coupling(faces, small.X, small.tets, dev)
+    i = c.info()
+    clipped = i["pairs"] - alone.info()["pairs"]
+    say(f"[gpu] octant limits: overflow, {clipped} clipped pairs, {i['subtets']} sub-tetrahedra")
+    assert i["subtets"] > 3.25 * clipped + 1024
+    R = oracle.assemble(faces, X, T)
+    assert abs(i["pieces"] - R.stats["pieces"]) <= 4
+    for d in range(3):
+        fro, mx = sparse_rel(gpu_csr(c, d, oracle.n_fluid(faces, d)), R.B[d])
+        assert fro <= 1e-12 and mx <= 1e-12
+    for d in range(3):
+        assert np.array_equal(c.export_csr(d)[2][:c.export_csr(d)[0][ns]], alone.export_csr(d)[2])
+    c.free()
+    alone.free()
