@@ -159,7 +159,9 @@ typedef struct {
   int64_t n_fluid[3];        /* lattice nodes of component d */
   int64_t pairs;             /* candidate (tet, component, cell) pairs */
   int64_t pieces;            /* non-empty pieces kept (vol > 1e-14 |T|) */
-  int64_t dropped;           /* non-empty pieces with vol <= 1e-14 |T| */
+  int64_t dropped;           /* non-empty pieces with vol <= 1e-14 |T|
+                                (integrated over their boundary: down to
+                                1e-15 |T|, where rounding begins) */
   int64_t zero_tets;         /* tets of zero volume (skipped) */
   int64_t nnz[3];            /* nonzeros of B^d (and of B^dT) */
   int64_t touched[3];        /* fluid nodes of component d with a nonzero
