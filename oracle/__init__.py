@@ -20,7 +20,7 @@ L2-Projection Approach") directly:
   (∫_T λ_j ψ_i = δ_ij |T|/4), so S = diag(∫ψ_i) = the lumped P1 mass and
   B_ij = ∫ ψ_i N_j.
 
-Readings where the paper is silent are listed in the design doc; the main ones:
+The main readings where the paper is silent:
 lattice of component d = face coordinates along axis d and face midpoints
 along the other two axes; lumped S = row sums of M; force transfer
 f_f = alpha * B^T f_s with f_s as P1 nodal density coefficients (the
